@@ -196,7 +196,7 @@ def _flatten(length, width, rows_of):
     offsets = torch.zeros(n + 1, dtype=torch.int64, device=length.device)
     torch.cumsum(length, 0, out=offsets[1:])
     frames = torch.empty(int(offsets[-1]), dtype=torch.int32, device=length.device)
-    step = max(1, (1 << 27) // max(width, 1))
+    step = max(1, (1 << 25) // max(width, 1))
     cut = offsets[torch.arange(0, n + step, step, device=length.device).clamp_(max=n)].tolist()
     col = torch.arange(width, device=length.device)[None, :]
     for k, a in enumerate(range(0, n, step)):
@@ -405,9 +405,19 @@ def _nodes(c):
     n = c["events"] + (c["batches"] * c["batch"] if c["op"] in ("merge", "activity") else 0)
     if c["program"] == "deep":
         cells = 64 * 8 * (c["dmax"] - c["dmin"] + 1)
-        return int(min(c["ids"], n / 100) + 3.5 * cells * (1 - math.exp(-n / cells)))
-    w = np.arange(1, c["templates"] + 1) ** -c["zipf"]
-    paths = float(np.sum(1 - np.exp(-n * w / w.sum())))
+        return int(min(c["ids"], n / 100) + cells * (1 - math.exp(-n / cells)))
+    T, z = c["templates"], c["zipf"]
+    hot = min(1.0, 8 / c["roots"])
+    pools = [(T, n)]
+    if c["batches"]:  # batches draw a fifth of their events from paths new to them
+        extra = min(0.4 * T / 8, 0.2 * n)
+        pools = [(0.6 * T, n - extra), (extra, 3 * extra)]
+    elif c["hot"] and hot < 1:
+        pools = [(hot * T, c["hot"] * n), ((1 - hot) * T, (1 - c["hot"]) * n)]
+    paths = 0.0
+    for size, drawn in pools:
+        w = np.arange(1, int(size) + 2) ** -z
+        paths += float(np.sum(1 - np.exp(-drawn * w / w.sum())))
     share = 0.5 if c["dmax"] > 250 else 0.25
     return int(1 + paths * min(_mean_length(c), 9 + share * _mean_length(c)))
 
@@ -591,8 +601,8 @@ def _by_frame(o, f, w):
     z = torch.zeros(frames.numel(), w.shape[1], dtype=torch.int64, device=w.device)
     out["excl"] = z.clone().index_add_(0, last, w[full])
     out["incl"] = z
-    for a in range(0, length.numel(), 1 << 20):
-        b = min(length.numel(), a + (1 << 20))
+    for a in range(0, length.numel(), 1 << 18):
+        b = min(length.numel(), a + (1 << 18))
         ev = torch.repeat_interleave(torch.arange(a, b, device=o.device), length[a:b])
         pair = torch.unique((ev << 32) | _u32(f[int(o[a]):int(o[b])]))
         z.index_add_(0, torch.searchsorted(frames, pair & 0xFFFFFFFF), w[pair >> 32])

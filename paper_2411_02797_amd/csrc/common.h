@@ -277,6 +277,12 @@ void launch_trie_sort(const TrieArgs &a, hipStream_t s, hipStream_t s2, hipEvent
                       hipEvent_t join);
 void launch_canon(const CanonArgs &a, hipStream_t s);  // lcp, scans, sparse table, emission
 
+struct alignas(32) PathRec {  // the path at a canonical position
+  int64_t start;             // first frame in the store
+  uint32_t len, lcp;         // length, common prefix with the path before it
+  int64_t base;              // id of its first node (of depth lcp + 1)
+  int64_t pad;
+};
 struct QueryArgs {
   int64_t q;
   int64_t qn_frames;
@@ -294,8 +300,8 @@ struct QueryArgs {
   const uint64_t *excl, *incl;
   int64_t *node_ids;
   uint64_t *qexcl, *qincl;
-  unsigned long long *err;
-  int64_t *sorted;           // [D][2]: first frame and length of the path at each canonical position
+  unsigned long long *err;   // [2]: [0] malformed offsets (nothing is looked up), [1] inconsistent tree
+  PathRec *sorted;           // [D]
   uint64_t *qtab;            // prefix index [qcap][2] {key, (length << 32) | position}, or null
   uint64_t qcap_mask;
   uint64_t qhash_mask;       // test setting: keys keep only these bits (forced collisions)

@@ -13,6 +13,8 @@
 //     hashes its frames, probes, and verifies every candidate frame by frame against the
 //     stored path, so a lookup costs a few round trips;
 //   - binary search over the sorted paths (when the index cannot be allocated).
+#include <algorithm>
+
 #include "common.h"
 
 namespace cct {
@@ -29,8 +31,8 @@ struct __attribute__((aligned(4))) Frames4 {
 // and length come from one 16-byte record; four frames per step, then one at a time.
 __device__ int cmp_path_query(const QueryArgs &a, int64_t i, const uint32_t *qf, int64_t ql, int64_t k0,
                               int64_t *lcp) {
-  const int64_t *rec = a.sorted + 2 * i;
-  const int64_t fs = rec[0], lp = rec[1];
+  const PathRec *rec = a.sorted + i;
+  const int64_t fs = rec->start, lp = rec->len;
   const uint32_t *pf = a.pframes + fs;
   const int64_t n = min(lp, ql);
   int64_t k = k0;
@@ -52,8 +54,15 @@ __device__ int cmp_path_query(const QueryArgs &a, int64_t i, const uint32_t *qf,
 // frames does not cancel: both factors move with the position), then a murmur3-style
 // finalizer with the length.  Sums extend frame by frame, so one scan along a path gives
 // the hash of every prefix.  Correctness never depends on it: every match is verified.
+struct PrefixFactors {
+  uint32_t x, y;
+};
+__device__ inline PrefixFactors prefix_factors(uint32_t f, uint32_t k) {
+  return {f + k * 0x9E3779B9u, ((f ^ 0x5BD1E995u) + k * 0x85EBCA6Bu) | 1u};
+}
 __device__ inline uint64_t prefix_term(uint32_t f, uint32_t k) {
-  return (uint64_t)(f + k * 0x9E3779B9u) * (uint64_t)(((f ^ 0x5BD1E995u) + k * 0x85EBCA6Bu) | 1u);
+  const PrefixFactors t = prefix_factors(f, k);
+  return (uint64_t)t.x * t.y;
 }
 __device__ inline uint64_t prefix_key(uint64_t sum, uint64_t len, uint64_t mask) {
   uint64_t h = sum ^ (len * 0xD6E8FEB86659FD93ull);
@@ -82,8 +91,8 @@ __global__ __launch_bounds__(256) void query_index_kernel(QueryArgs a) {
   const int lane = threadIdx.x & 63;
   const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   if (i >= a.d) return;
-  const int64_t fs = a.sorted[2 * i], len = a.sorted[2 * i + 1];
-  const int64_t L = a.lcp[i];
+  const int64_t fs = a.sorted[i].start, len = a.sorted[i].len;
+  const int64_t L = a.sorted[i].lcp;
   const uint32_t *pf = a.pframes + fs;
   uint64_t carry = 0;
   for (int64_t k0 = 0; k0 < len; k0 += 64) {
@@ -111,57 +120,167 @@ __global__ __launch_bounds__(256) void query_index_kernel(QueryArgs a) {
   }
 }
 
-// record of canonical position i: the path's first frame in the store and its length
+// record of canonical position i: all that a lookup needs of the path, in one 32-byte load
 __global__ void sorted_paths_kernel(QueryArgs a) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= a.d) return;
   const uint32_t p = a.order[i];
-  a.sorted[2 * i] = a.pstart[p];
-  a.sorted[2 * i + 1] = a.plen[p];
+  PathRec r;
+  r.start = a.pstart[p];
+  r.len = a.plen[p];
+  r.lcp = a.lcp[i];
+  r.base = (int64_t)(1 + a.scan_out[i * (1 + a.m)]);
+  r.pad = 0;
+  a.sorted[i] = r;
 }
 
-// node id of the query through the prefix index, or -1: probe from the query's key; an
-// entry with the same key and length is checked frame by frame against its path
-__device__ int64_t index_lookup(const QueryArgs &a, const uint32_t *qf, int64_t ql) {
-  const int C = 1 + a.m;
-  uint64_t sum = 0;
-  int64_t k = 0;
-  for (; k + 4 <= ql; k += 4) {
-    const Frames4 x = *reinterpret_cast<const Frames4 *>(qf + k);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) sum += prefix_term(x.f[j], (uint32_t)(k + j));
+// ---- lookup through the index -----------------------------------------------------------
+// Eight lanes per query (eight queries per wave).  A lookup is a chain of dependent reads
+// (offsets, frames, table entry, path record, stored frames, sums), so its time is the
+// number of queries in flight; with one lane per query every 16-byte load of a wave
+// touched 64 different lines, and the frames of a query were read in a serial loop.  The
+// eight lanes read 32 consecutive frames per instruction, keep up to kQueryKeep of them in
+// registers for the comparison with the stored path (longer queries read theirs again),
+// and meet by cross-lane moves.  1,048,576 queries of 68 frames on average in a tree of
+// 4.2 million nodes: one lane per query 694 us; sixteen lanes 268 us (too few queries in
+// flight); four lanes 218 us; eight lanes 214 us with three pieces at 7 waves per SIMD,
+// 219 us with four at 6, 222 us with two at 8.  It moves about 0.9 GB (queries, stored
+// frames, a table line and two rows of sums per query), 4.2 TB/s.
+constexpr int kQueryLanes = 8;
+constexpr int kQueryVecs = 3;                               // 16-byte pieces of a query per lane
+constexpr int kQueryStep = 4 * kQueryLanes;                 // frames per piece of the eight lanes
+constexpr int kQueryKeep = kQueryStep * kQueryVecs;         // frames held in registers
+
+// sum over the eight lanes of a query, on all of them
+__device__ inline uint64_t sum8(uint64_t v) {
+#define CCT_DPP_ADD(ctrl)                                                                                    \
+  {                                                                                                          \
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)v, ctrl, 0xF, 0xF, true);          \
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(v >> 32), ctrl, 0xF, 0xF, true);  \
+    v += ((uint64_t)hi << 32) | lo;                                                                          \
   }
-  for (; k < ql; ++k) sum += prefix_term(qf[k], (uint32_t)k);
-  const uint64_t key = prefix_key(sum, (uint64_t)ql, a.qhash_mask);
-  uint64_t slot = key & a.qcap_mask;
-  for (uint64_t probe = 0; probe <= a.qcap_mask; ++probe) {
-    const uint64_t kk = a.qtab[2 * slot];
-    if (kk == 0) return -1;  // an empty slot ends the probe sequence
-    if (kk == key) {
-      const uint64_t v = a.qtab[2 * slot + 1];
-      const int64_t i = (int64_t)(uint32_t)v, l = (int64_t)(v >> 32);
-      int64_t common;
-      if (l == ql && cmp_path_query(a, i, qf, ql, 0, &common) >= 0 && common == ql) {
-        const int64_t id = (int64_t)(1 + a.scan_out[i * C]) + ql - (int64_t)a.lcp[i] - 1;
-        if (id >= a.u || ql <= (int64_t)a.lcp[i]) {  // cannot happen on a canonical tree
-          atomicOr(a.err, 2ull);
-          return -1;
-        }
-        return id;
+  CCT_DPP_ADD(0xB1)   // quad_perm 1,0,3,2
+  CCT_DPP_ADD(0x4E)   // quad_perm 2,3,0,1
+  CCT_DPP_ADD(0x141)  // row_half_mirror: the other quad of the eight lanes
+#undef CCT_DPP_ADD
+  return v;
+}
+
+// frames k .. k + 3 of a query of n frames (those below n; the others are unspecified).
+// avail: frames readable from its first one (to the end of the batch).
+template <class Int>
+__device__ inline Frames4 query_frames(const uint32_t *qf, Int k, Int n, Int avail) {
+  Frames4 v = {{0u, 0u, 0u, 0u}};
+  if (k + 4 <= avail) {
+    if (k < n) v = *reinterpret_cast<const Frames4 *>(qf + k);
+  } else {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (k + j < n) v.f[j] = qf[k + j];
+  }
+  return v;
+}
+
+__device__ inline void query_one(const QueryArgs &a, int64_t q, int lane) {
+  int g = lane % kQueryLanes;
+  // (opaque to the compiler here, or it keeps every lane-derived constant of the pieces
+  // in registers across the queries: 138 VGPRs instead of 72)
+  asm volatile("" : "+v"(g));
+  const int64_t qs = a.qoff[q], qe = a.qoff[q + 1], ql = qe - qs, avail = a.qn_frames - qs;
+  const uint32_t *qf = a.qfr + qs;
+  int64_t id = -1;
+  if (ql == 0) {
+    id = 0;  // the empty path is the root
+  } else {
+    // the frames kept in registers, in 32-bit arithmetic (n of them)
+    const int n = (int)min(ql, (int64_t)kQueryKeep), av = (int)min(avail, (int64_t)kQueryKeep);
+    Frames4 f[kQueryVecs];
+    uint64_t sum = 0;
+#pragma unroll
+    for (int c = 0; c < kQueryVecs; ++c) f[c] = query_frames<int>(qf, c * kQueryStep + 4 * g, n, av);
+#pragma unroll
+    for (int c = 0; c < kQueryVecs; ++c)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int k = c * kQueryStep + 4 * g + j;
+        const PrefixFactors t = prefix_factors(f[c].f[j], (uint32_t)k);
+        sum += (uint64_t)(k < n ? t.x : 0u) * t.y;
+      }
+    for (int64_t k0 = kQueryKeep; k0 < ql; k0 += kQueryStep) {
+      const Frames4 x = query_frames<int64_t>(qf, k0 + 4 * g, ql, avail);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int64_t k = k0 + 4 * g + j;
+        sum += k < ql ? prefix_term(x.f[j], (uint32_t)k) : 0ull;
       }
     }
-    slot = (slot + 1) & a.qcap_mask;
+    const uint64_t key = prefix_key(sum8(sum), (uint64_t)ql, a.qhash_mask);
+    uint64_t slot = key & a.qcap_mask;
+    // probe from the query's key: an empty slot ends the sequence; an entry with the same
+    // key and length is checked frame by frame against its path
+    for (uint64_t probe = 0; probe <= a.qcap_mask; ++probe) {
+      const ulonglong2 e = *reinterpret_cast<const ulonglong2 *>(a.qtab + 2 * slot);
+      if (e.x == 0) break;
+      if (e.x == key && (int64_t)(e.y >> 32) == ql) {
+        const PathRec rec = a.sorted[(uint32_t)e.y];
+        const uint32_t *pf = a.pframes + rec.start;
+        uint32_t differ = (int64_t)rec.len < ql;
+        if (!differ) {
+          // (a stored path is padded to whole 16-frame blocks and holds the query's
+          // frames, so a piece that starts below n stays in it)
+          Frames4 p[kQueryVecs];
+#pragma unroll
+          for (int c = 0; c < kQueryVecs; ++c) {
+            const int k = c * kQueryStep + 4 * g;
+            p[c] = *reinterpret_cast<const Frames4 *>(pf + (k < n ? k : 0));
+          }
+#pragma unroll
+          for (int c = 0; c < kQueryVecs; ++c)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) differ |= c * kQueryStep + 4 * g + j < n ? p[c].f[j] ^ f[c].f[j] : 0u;
+          for (int64_t k0 = kQueryKeep; k0 < ql; k0 += kQueryStep) {
+            const int64_t k = k0 + 4 * g;
+            const Frames4 x = query_frames<int64_t>(qf, k, ql, avail);
+            const Frames4 y = *reinterpret_cast<const Frames4 *>(pf + (k < ql ? k : 0));
+#pragma unroll
+            for (int j = 0; j < 4; ++j) differ |= k + j < ql ? x.f[j] ^ y.f[j] : 0u;
+          }
+        }
+        if (((__ballot(differ != 0) >> (lane - g)) & ((1u << kQueryLanes) - 1)) == 0) {
+          id = rec.base + ql - (int64_t)rec.lcp - 1;
+          if (id >= a.u || ql <= (int64_t)rec.lcp) {  // cannot happen on a canonical tree
+            if (g == 0) atomicOr(a.err + 1, 2ull);
+            id = -1;
+          }
+          break;
+        }
+      }
+      slot = (slot + 1) & a.qcap_mask;
+    }
   }
-  return -1;
+  if (g == 0) a.node_ids[q] = id;
+  for (int j = g; j < a.m; j += kQueryLanes) {
+    const uint64_t x = a.qexcl && id >= 0 ? a.excl[id * a.m + j] : 0, y = a.qincl && id >= 0 ? a.incl[id * a.m + j] : 0;
+    if (a.qexcl) a.qexcl[q * a.m + j] = x;
+    if (a.qincl) a.qincl[q * a.m + j] = y;
+  }
 }
 
+__global__ __launch_bounds__(256, 7) void query_kernel(QueryArgs a) {
+  if (*a.err) return;  // malformed offsets (query_check_kernel): nothing is written
+  const int lane = threadIdx.x & 63;
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x / kQueryLanes;
+  for (int64_t q = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kQueryLanes; q < a.q; q += stride)
+    query_one(a, q, lane);
+}
+
+// ---- lookup by binary search ------------------------------------------------------------
 // node id of the query by binary search over the sorted paths, or -1: the first i with
 // path_i >= q.  llo and lhi: common prefix of q with the path below the range (path_{lo-1})
 // and with the path above it (path_hi), 0 for the open ends.  Every path between two paths
 // that share a prefix with q shares it too (paths with a given prefix are consecutive in
 // lexicographic order), so a comparison can skip min(llo, lhi) frames.
 __device__ int64_t search_lookup(const QueryArgs &a, const uint32_t *qf, int64_t ql) {
-  const int C = 1 + a.m;
   int64_t lo = 0, hi = a.d, llo = 0, lhi = 0;
   int64_t l;
   while (lo < hi) {
@@ -177,9 +296,10 @@ __device__ int64_t search_lookup(const QueryArgs &a, const uint32_t *qf, int64_t
   int64_t id = -1;
   if (lo < a.d) {
     l = lhi;  // lo = hi < D: set by the comparison with path_hi, which measured its prefix
-    if (l == ql) id = (int64_t)(1 + a.scan_out[lo * C]) + ql - (int64_t)a.lcp[lo] - 1;
-    if (id >= a.u || (l == ql && ql <= (int64_t)a.lcp[lo])) {  // cannot happen on a canonical tree
-      atomicOr(a.err, 2ull);
+    const PathRec rec = a.sorted[lo];
+    if (l == ql) id = rec.base + ql - (int64_t)rec.lcp - 1;
+    if (id >= a.u || (l == ql && ql <= (int64_t)rec.lcp)) {  // cannot happen on a canonical tree
+      atomicOr(a.err + 1, 2ull);
       id = -1;
     }
   }
@@ -196,20 +316,12 @@ __global__ void query_check_kernel(QueryArgs a) {
     atomicOr(a.err, 1ull);
 }
 
-__global__ void query_kernel(QueryArgs a) {
+__global__ void query_search_kernel(QueryArgs a) {
+  if (*a.err) return;  // malformed offsets: nothing is written
   const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (q >= a.q) return;
   const int64_t qs = a.qoff[q], qe = a.qoff[q + 1];
-  int64_t id = -1;
-  if (qs < 0 || qe < qs || qe > a.qn_frames || (q == 0 && qs != 0) || (q + 1 == a.q && qe != a.qn_frames)) {
-    atomicOr(a.err, 1ull);
-  } else if (qe == qs) {
-    id = 0;  // the empty path is the root
-  } else if (a.qtab) {
-    id = index_lookup(a, a.qfr + qs, qe - qs);
-  } else {
-    id = search_lookup(a, a.qfr + qs, qe - qs);
-  }
+  const int64_t id = qe == qs ? 0 : search_lookup(a, a.qfr + qs, qe - qs);  // (the empty path is the root)
   a.node_ids[q] = id;
   for (int j = 0; j < a.m; ++j) {
     if (a.qexcl) a.qexcl[q * a.m + j] = id >= 0 ? a.excl[id * a.m + j] : 0;
@@ -232,7 +344,14 @@ void launch_query_check(const QueryArgs &a, hipStream_t s) {
 }
 
 void launch_query(const QueryArgs &a, hipStream_t s) {
-  if (a.q > 0) hipLaunchKernelGGL(query_kernel, dim3((unsigned)((a.q + 255) / 256)), dim3(256), 0, s, a);
+  if (a.q <= 0) return;
+  if (a.qtab) {
+    // (a launch holds fewer than 2^32 work items: larger batches loop)
+    const int64_t blocks = std::min<int64_t>((a.q * kQueryLanes + 255) / 256, 1 << 22);
+    hipLaunchKernelGGL(query_kernel, dim3((unsigned)blocks), dim3(256), 0, s, a);
+  } else {
+    hipLaunchKernelGGL(query_search_kernel, dim3((unsigned)((a.q + 255) / 256)), dim3(256), 0, s, a);
+  }
 }
 
 }  // namespace cct

@@ -1180,7 +1180,7 @@ cct_status cct_query(const cct_tree *tree, const cct_paths *q, void *hip_stream,
   if (!hs) return fail(CCT_ENOMEM, "pinned host allocation failed");
   g_alloc_countdown = 0;  // queries allocate only what the index needs; the hook is not armed
   Buf err;
-  if (!err.alloc(8)) return fail(CCT_ENOMEM, "device allocation failed");
+  if (!err.alloc(16)) return fail(CCT_ENOMEM, "device allocation failed");
   QueryArgs a{};
   a.q = q->n_events; a.qn_frames = q->n_frames; a.qoff = q->offsets; a.qfr = q->frames;
   a.d = tree->d; a.u = tree->u; a.m = tree->m;
@@ -1188,13 +1188,11 @@ cct_status cct_query(const cct_tree *tree, const cct_paths *q, void *hip_stream,
   a.order = tree->order.as<uint32_t>(); a.lcp = tree->lcp.as<uint32_t>(); a.scan_out = tree->scan_out.as<uint64_t>();
   a.excl = tree->excl.as<uint64_t>(); a.incl = tree->incl.as<uint64_t>();
   a.node_ids = node_ids; a.qexcl = excl; a.qincl = incl; a.err = err.as<unsigned long long>();
-  // the batch's offsets are checked before anything is written to the outputs
-  HIP_TRY(hipMemsetAsync(err.p, 0, 8, s));
+  // the batch's offsets are checked before anything is written to the outputs: the lookup
+  // kernel reads the check's verdict on the device
+  HIP_TRY(hipMemsetAsync(err.p, 0, 16, s));
   launch_query_check(a, s);
   HIP_TRY(hipGetLastError());
-  HIP_TRY(hipMemcpyAsync(hs, err.p, 8, hipMemcpyDeviceToHost, s));
-  HIP_TRY(spin_sync(s));
-  if (hs[0]) return fail(CCT_EINVAL, "malformed query offsets");
   // the index: every node under the hash of its prefix (a test setting keeps fewer key bits,
   // forcing collisions, on trees of at most 2^15 nodes: on larger ones a few keys would
   // make probing quadratic; another one uses the binary search); a table at most half full
@@ -1203,12 +1201,15 @@ cct_status cct_query(const cct_tree *tree, const cct_paths *q, void *hip_stream,
   const bool use_index = !env_int("CCT_TEST_QUERY_SEARCH", 0);
   g_qindex_ms = 0;
   if (!tree->q_ready || tree->q_hash_mask != hash_mask || (tree->q_cap != 0) != use_index) {
+    HIP_TRY(hipMemcpyAsync(hs, err.p, 8, hipMemcpyDeviceToHost, s));
+    HIP_TRY(spin_sync(s));
+    if (hs[0]) return fail(CCT_EINVAL, "malformed query offsets");  // (no index is built for it)
     tree->q_ready = false;
     Timer ti;
     ti.mark(0, s);
-    if (!tree->q_sorted.alloc((size_t)std::max<int64_t>(tree->d, 1) * 16))
+    if (!tree->q_sorted.alloc((size_t)std::max<int64_t>(tree->d, 1) * sizeof(PathRec)))
       return fail(CCT_ENOMEM, "device allocation failed");
-    a.sorted = tree->q_sorted.as<int64_t>();
+    a.sorted = tree->q_sorted.as<PathRec>();
     launch_sorted_paths(a, s);
     tree->q_cap = 0;
     tree->q_tab.release();
@@ -1226,7 +1227,7 @@ cct_status cct_query(const cct_tree *tree, const cct_paths *q, void *hip_stream,
     tree->q_hash_mask = hash_mask;
     tree->q_ready = true;
   }
-  a.sorted = tree->q_sorted.as<int64_t>();
+  a.sorted = tree->q_sorted.as<PathRec>();
   if (tree->q_cap) {
     a.qtab = tree->q_tab.as<uint64_t>(); a.qcap_mask = tree->q_cap - 1; a.qhash_mask = hash_mask;
   }
@@ -1235,10 +1236,10 @@ cct_status cct_query(const cct_tree *tree, const cct_paths *q, void *hip_stream,
   launch_query(a, s);
   tm.mark(1, s);
   HIP_TRY(hipGetLastError());
-  HIP_TRY(hipMemcpyAsync(hs, err.p, 8, hipMemcpyDeviceToHost, s));
+  HIP_TRY(hipMemcpyAsync(hs, err.p, 16, hipMemcpyDeviceToHost, s));
   HIP_TRY(spin_sync(s));
   g_query_ms = tm.ok ? tm.span(0, 1) : 0.0;
-  if (hs[0] & 2) return fail(CCT_EDEVICE, "query found an inconsistent tree");
+  if (hs[1]) return fail(CCT_EDEVICE, "query found an inconsistent tree");
   if (hs[0]) return fail(CCT_EINVAL, "malformed query offsets");
   return CCT_OK;
 }

@@ -229,31 +229,72 @@ __global__ __launch_bounds__(256) void place_old_kernel(const uint32_t *A, int64
 }
 
 // ---- exact verification, lcp, scan rows ------------------------------------------------
-__global__ void lcp_kernel(CanonArgs a) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i > a.d) return;
+// Sixteen lanes per pair of neighbours: a step compares 64 frames of both with one 16-byte
+// load each (256 consecutive bytes per path), and the first lane with a difference holds
+// the LCP.  With one lane per pair the longest paths of a wave set its time, eight
+// dependent 16-byte loads per 16 frames: 60,013 events with paths of up to 2,500 frames
+// and 14,444 distinct ones 186 -> 22 us, 149,201 paths of 256 to 512 frames 83 -> 55 us (their
+// frames at 8 TB/s from the caches), 154,413 paths of 72 frames on average 24 -> 23 us.
+constexpr int kLcpLanes = 16;
+__device__ inline void lcp_one(const CanonArgs &a, int64_t i, int lane) {
+  const int g = lane % kLcpLanes;
   const int C = 1 + a.m;
-  if (i == a.d) { a.lcp[i] = 0; a.sparse[i] = 0; return; }
+  if (i == a.d) {
+    if (g == 0) { a.lcp[i] = 0; a.sparse[i] = 0; }
+    return;
+  }
   // an order from a misleading hash may hold entries that are not path ids: they raise
   // the flag and read as path 0 here and in the kernels after this one
-  uint32_t p = a.order[i];
-  if (p >= (uint64_t)a.d) {
-    atomicOr(&a.u_out[1], 1ull);
-    p = 0;
-    a.order[i] = 0;
-  }
+  uint32_t p = a.order[i], q = i > 0 ? a.order[i - 1] : 0u;
+  const bool bad = p >= (uint64_t)a.d;
+  if (bad) p = 0;
+  if (q >= (uint64_t)a.d) q = 0;
+  const uint32_t len = a.plen[p];
   uint32_t l = 0;
   if (i > 0) {
-    uint32_t q = a.order[i - 1];
-    if (q >= (uint64_t)a.d) q = 0;
-    const int r = path_cmp_exact(a, q, p, 0, &l);
-    if (r >= 0) atomicOr(&a.u_out[1], 1ull);  // not strictly increasing
+    const uint32_t lq = a.plen[q], n = min(lq, len);
+    const uint32_t *pq = a.pframes + a.pstart[q], *pp = a.pframes + a.pstart[p];
+    bool less = lq < len;  // the order of the two if they agree on n frames
+    l = n;
+    for (uint32_t k0 = 0; k0 < n; k0 += 4 * kLcpLanes) {
+      // (starts are 16-frame aligned and tails are padded: a lane whose first frame is
+      // below n stays in both paths' slots)
+      const uint32_t k = k0 + 4 * g;
+      int e = 4;  // this lane's first difference
+      bool lt = false;
+      if (k < n) {
+        const u32x4 x = ld4(pq + k), y = ld4(pp + k);
+#pragma unroll
+        for (int c = 3; c >= 0; --c)
+          if (k + c < n && x[c] != y[c]) { e = c; lt = x[c] < y[c]; }
+      }
+      const uint32_t found = (uint32_t)(__ballot(e < 4) >> (lane - g)) & ((1u << kLcpLanes) - 1);
+      const uint32_t lts = (uint32_t)(__ballot(lt) >> (lane - g)) & ((1u << kLcpLanes) - 1);
+      if (found) {
+        const int f = __builtin_ctz(found);
+        l = k0 + 4 * f + (uint32_t)__shfl(e, lane - g + f, 64);
+        less = (lts >> f) & 1;
+        break;
+      }
+    }
+    if (!less && g == 0) atomicOr(&a.u_out[1], 1ull);  // not strictly increasing
   }
-  a.lcp[i] = l;
-  a.sparse[i] = l;  // level 0 of the range-minimum table
+  if (g == 0) {
+    if (bad) {
+      atomicOr(&a.u_out[1], 1ull);
+      a.order[i] = 0;
+    }
+    a.lcp[i] = l;
+    a.sparse[i] = l;  // level 0 of the range-minimum table
+  }
   uint64_t *row = a.scan_in + i * C;
-  row[0] = (uint64_t)(a.plen[p] - l);
-  for (int j = 0; j < a.m; ++j) row[1 + j] = a.psums[(int64_t)p * a.m + j];
+  for (int j = g; j < C; j += kLcpLanes) row[j] = j == 0 ? (uint64_t)(len - l) : a.psums[(int64_t)p * a.m + j - 1];
+}
+
+__global__ __launch_bounds__(256) void lcp_kernel(CanonArgs a) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x / kLcpLanes;
+  for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kLcpLanes; i <= a.d; i += stride)
+    lcp_one(a, i, threadIdx.x & 63);
 }
 
 // ---- multi-column exclusive scan (uint64, mod 2^64) -------------------------------------
@@ -625,7 +666,8 @@ void launch_scan(const uint64_t *in, int64_t rows, int C, uint64_t *blk, uint64_
 void launch_canon(const CanonArgs &a, hipStream_t s) {
   const int C = 1 + a.m;
   const int64_t n = a.d + 1;
-  hipLaunchKernelGGL(lcp_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, a);
+  // (a launch holds fewer than 2^32 work items: more pairs loop)
+  hipLaunchKernelGGL(lcp_kernel, dim3(std::min(blocks_for(n, 256 / kLcpLanes), 1u << 22)), dim3(256), 0, s, a);
   launch_scan(a.scan_in, a.d, C, a.scan_blk, a.scan_out, s);
   // range-minimum table: level 0 (lcp itself) written by lcp_kernel, levels up to
   // kTileLevels in LDS tiles, the rest one level per launch

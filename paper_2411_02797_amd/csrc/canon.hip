@@ -228,7 +228,7 @@ __global__ __launch_bounds__(256) void place_old_kernel(const uint32_t *A, int64
   dst[i + lo] = A[i];
 }
 
-// ---- exact verification, lcp, scan rows ------------------------------------------------
+// ---- exact verification, lcp, sums, scan rows ------------------------------------------------
 // Sixteen lanes per pair of neighbours: a step compares 64 frames of both with one 16-byte
 // load each (256 consecutive bytes per path), and the first lane with a difference holds
 // the LCP.  With one lane per pair the longest paths of a wave set its time, eight
@@ -288,7 +288,19 @@ __device__ inline void lcp_one(const CanonArgs &a, int64_t i, int lane) {
     a.sparse[i] = l;  // level 0 of the range-minimum table
   }
   uint64_t *row = a.scan_in + i * C;
-  for (int j = g; j < C; j += kLcpLanes) row[j] = j == 0 ? (uint64_t)(len - l) : a.psums[(int64_t)p * a.m + j - 1];
+  // the path's sums after the batch: every path sits at one position of a good order, so
+  // this pass folds each path's batch sums into its old ones, into the fresh array (a bad
+  // order's leftovers are overwritten when the corrected order comes through here)
+  const uint32_t sl = a.pslot[p];
+  for (int j = g; j < C; j += kLcpLanes) {
+    uint64_t v = (uint64_t)(len - l);
+    if (j > 0) {
+      const int64_t at = (int64_t)p * a.m + j - 1;
+      v = a.delta[(uint64_t)sl * a.m + j - 1] + (p < (uint64_t)a.d_old ? a.old_sums[at] : 0);
+      a.psums[at] = v;
+    }
+    row[j] = v;
+  }
 }
 
 __global__ __launch_bounds__(256) void lcp_kernel(CanonArgs a) {

@@ -179,10 +179,6 @@ void launch_publish(const PublishArgs &a, hipStream_t s);
 // Exclusive prefix sums of `rows` rows of C uint64 columns (mod 2^64) into out[0..rows),
 // totals into out row `rows`; blk holds (rows / 1024 + 1) * C scratch words.
 void launch_scan(const uint64_t *in, int64_t rows, int C, uint64_t *blk, uint64_t *out, hipStream_t s);
-// sums[d] for d < D after a batch: old paths (d < d_old) add their slot's delta to
-// old_sums[d], new ones take it (sums and old_sums are distinct arrays)
-void launch_fold_sums(int64_t D, int64_t d_old, int32_t m, const uint32_t *pslot, const uint64_t *delta,
-                      const uint64_t *old_sums, uint64_t *sums, hipStream_t s);
 // slot[list[i]] = empty for i < n (the slots published by a call that failed afterwards)
 void launch_reset_slots(Slot *slot, const uint32_t *list, int64_t n, hipStream_t s);
 void launch_unclaim(Slot *slot, uint64_t cap, hipStream_t s);
@@ -199,7 +195,13 @@ struct CanonArgs {
   const uint64_t *pcp;
   const int64_t *pstart;
   const uint32_t *plen;
-  const uint64_t *psums; // [D][m]
+  // sums after the batch, written by launch_canon (a fresh array): old paths (d < d_old)
+  // add their slot's delta to old_sums, new ones take it
+  int64_t d_old;
+  const uint32_t *pslot;
+  const uint64_t *delta;     // [slots][m]
+  const uint64_t *old_sums;  // [d_old][m]
+  uint64_t *psums;           // [D][m]
   // outputs / scratch
   uint32_t *order;       // [D] path ids in lexicographic order
   uint32_t *order_tmp;   // [D]

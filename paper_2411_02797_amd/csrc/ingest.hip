@@ -895,7 +895,7 @@ __global__ __launch_bounds__(256) void collect_sum_kernel(const unsigned long lo
 // Publish the paths first seen in this call: give each a path id, copy its frames into
 // the tree's path store (16-frame aligned, zero tail up to its padded length), write its
 // checkpoint hashes, its start, length and table slot, and point the slot at the path id
-// and the stored frames (the sums are folded in later, by fold_sums_kernel).  Sixteen
+// and the stored frames (the sums are folded in later, by lcp_kernel).  Sixteen
 // lanes per path, four paths per wave: a lane moves four frames of every 64-frame chunk
 // with one 16-byte load (the source, a 4-byte aligned stretch of the batch) and one
 // 16-byte store (the store is 64-byte aligned), so a wave has four paths' frames in
@@ -970,18 +970,6 @@ __global__ __launch_bounds__(256) void publish_kernel(PublishArgs a) {
     a.slot[s].word = (w & 0xFFFFFFFF00000000ull) | (uint64_t)id;
     a.slot[s].info = make_info((uint64_t)start, true, (uint64_t)len);
   }
-}
-
-// Every path's sums after the batch, into a fresh array (the tree's own sums stay as
-// they were until the call commits): paths from earlier calls add their slot's batch
-// sums to their old sums, new paths (d >= d_old) take them.
-__global__ void fold_sums_kernel(int64_t D, int64_t d_old, int32_t m, const uint32_t *pslot, const uint64_t *delta,
-                                 const uint64_t *old_sums, uint64_t *sums) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= D * m) return;
-  const int64_t d = t / m, j = t - d * m;
-  const uint64_t x = delta[(uint64_t)pslot[d] * m + j];
-  sums[t] = d < d_old ? old_sums[t] + x : x;
 }
 
 // Empty the slots published in a call that then failed (they name path ids that the
@@ -1086,12 +1074,6 @@ void launch_collect_new(const Slot *slot, uint64_t cap, const int64_t *off, uint
 void launch_publish(const PublishArgs &a, hipStream_t s) {
   if (a.n_new <= 0) return;
   hipLaunchKernelGGL(publish_kernel, dim3(blocks_for(a.n_new * 16, 256)), dim3(256), 0, s, a);
-}
-void launch_fold_sums(int64_t D, int64_t d_old, int32_t m, const uint32_t *pslot, const uint64_t *delta,
-                      const uint64_t *old_sums, uint64_t *sums, hipStream_t s) {
-  if (D <= 0) return;
-  hipLaunchKernelGGL(fold_sums_kernel, dim3(blocks_for(D * m, 256)), dim3(256), 0, s, D, d_old, m, pslot, delta,
-                     old_sums, sums);
 }
 void launch_reset_slots(Slot *slot, const uint32_t *list, int64_t n, hipStream_t s) {
   if (n <= 0) return;

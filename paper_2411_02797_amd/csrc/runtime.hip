@@ -202,15 +202,18 @@ struct SideGuard {
 
 // Wait for the work queued on s so far by polling an event (the host spins; a blocking
 // wait adds its wake-up latency to the call's critical path).
+hipError_t spin_event(hipEvent_t e) {
+  hipError_t r;
+  while ((r = hipEventQuery(e)) == hipErrorNotReady) {
+  }
+  return r;
+}
 hipError_t spin_sync(hipStream_t s) {
   hipEvent_t e = nullptr;
   hipError_t r = hipEventCreateWithFlags(&e, hipEventDisableTiming);
   if (r != hipSuccess) return hipStreamSynchronize(s);
   r = hipEventRecord(e, s);
-  if (r == hipSuccess) {
-    while ((r = hipEventQuery(e)) == hipErrorNotReady) {
-    }
-  }
+  if (r == hipSuccess) r = spin_event(e);
   (void)hipEventDestroy(e);
   return r;
 }
@@ -383,6 +386,13 @@ cct_status rehash(cct_tree *t, uint64_t cap, uint64_t hash_mask, hipStream_t s) 
   return CCT_OK;
 }
 
+// Batches of up to this many events keep the whole call on the caller's stream and flush
+// the aggregation's maps with device atomics: each wait between two streams costs about
+// 10 us, the staging two launches.  Builds, one stream and atomics against two streams and
+// staging: 10,000 events 308 against 327 us (1 metric), 319 against 332 (2); 40,000 events
+// 353 against 357 (2 metrics), 364 against 362 (4); 100,000 events 386 against 369.
+constexpr int64_t kOneStreamEvents = 1 << 15;
+
 // Aggregate one batch into `t` (fresh or existing).  Strong guarantee: on error the
 // tree's table, path store, sums and node arrays are as before.  Every array the call
 // changes is either new (sums and statistics are folded into fresh copies, swapped in
@@ -448,19 +458,24 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
   uint64_t new_frames = 0, new_store = 0;
   // The metric sums run on a second stream of the library, from the moment the ingest's
   // slot ids are complete: they overlap the host's reading of the counters, the publish
-  // and the ordering.  Per-workgroup LDS maps, flushed through staging buckets of slots;
-  // two workgroups per CU (run one after the other) halve the distinct slots each map
-  // must hold, so fewer events overflow into device atomics.  (A test setting keeps
+  // and the ordering.  Per-workgroup LDS maps, flushed through staging buckets of slots.
+  // From 8,192 events per CU on, two workgroups per CU (run one after the other) halve the
+  // distinct slots each map must hold, so fewer events overflow into device atomics; below,
+  // a workgroup for every 1,024 events, up to one per CU (a workgroup for every 8,192 left
+  // most CUs idle: 1,048,576 events of 3 metrics 38 us in 128 workgroups; 60,013 events of
+  // 8 metrics 77 us in 8).  (A test setting keeps
   // everything on the caller's stream, the path taken when no second stream can be
   // created.)
   SideGuard side_guard;
-  Event slots_ready;
+  Event counted, summed;
   AggStage stg{};
-  const int agg_grid = (int)std::max<int64_t>(1, std::min<int64_t>((N + 8191) / 8192, (int64_t)cu_count() * 2));
+  const int64_t cus = cu_count();
+  const int agg_grid = (int)std::max<int64_t>(1, N <= 8192 * cus ? std::min<int64_t>((N + 1023) / 1024, cus)
+                                                                : std::min<int64_t>((N + 8191) / 8192, 2 * cus));
   if (N > 0) {
-    hipStream_t ss = env_int("CCT_TEST_ONE_STREAM", 0) ? nullptr : side_guard.acquire();
+    hipStream_t ss = env_int("CCT_TEST_ONE_STREAM", 0) || N <= kOneStreamEvents ? nullptr : side_guard.acquire();
     if (ss) side = ss;
-    if (side != s && !slots_ready.ev) return fail(CCT_EDEVICE, "event creation failed");
+    if (!counted.ev || (side != s && !summed.ev)) return fail(CCT_EDEVICE, "event creation failed");
   }
   if (N > 0) {
     if (!slot_of.alloc((size_t)N * 4)) return fail(CCT_ENOMEM, "device allocation failed");
@@ -490,22 +505,25 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
                          nlen.as<uint64_t>(), dctr, cpart.as<unsigned long long>(), s);
       claimed = true;  // (from the launch on: the table may hold this call's claims)
       AGG_TRY(hipGetLastError());
+      AGG_TRY(hipMemcpyAsync(hs, dctr, kCtrCount * 8, hipMemcpyDeviceToHost, s));
+      AGG_TRY(hipEventRecord(counted.ev, s));
       {
-        // (the side stream's work, the staging's zeroing included, starts after the collection)
-        if (side != s) {
-          AGG_TRY(hipEventRecord(slots_ready.ev, s));
-          AGG_TRY(hipStreamWaitEvent(side, slots_ready.ev, 0));
+        // (the side stream's work, the staging's zeroing included, starts after the collection;
+        // on one stream the sums follow the counters' copy, which the host reads meanwhile)
+        if (side != s) AGG_TRY(hipStreamWaitEvent(side, counted.ev, 0));
+        if (N > kOneStreamEvents) {
+          cct_status sst = setup_stage(m, t->cap, agg_grid, agg_count, agg_keys, agg_sums, stg, side);
+          if (sst) return undo(sst);
         }
-        cct_status sst = setup_stage(m, t->cap, agg_grid, agg_count, agg_keys, agg_sums, stg, side);
-        if (sst) return undo(sst);
         launch_aggregate(slot_of.as<uint32_t>(), p->metrics, N, m, delta.as<uint64_t>(), t->cap, agg_grid, stg, side);
         AGG_TRY(hipGetLastError());
+        if (side != s) AGG_TRY(hipEventRecord(summed.ev, side));
       }
-      AGG_TRY(hipMemcpyAsync(hs, dctr, kCtrCount * 8, hipMemcpyDeviceToHost, s));
-      AGG_TRY(spin_sync(s));
+      AGG_TRY(spin_event(counted.ev));
       if (hs[kCtrError]) return undo(fail(CCT_EINVAL, "malformed offsets"));
       if (hs[kCtrOverflow]) {
-        // the sums of this attempt are discarded: their buffers are reused once idle
+        // the sums of this attempt are discarded: their buffers are reused once idle (on
+        // one stream, once rehash has synchronised it)
         if (side != s) AGG_TRY(hipStreamSynchronize(side));
         // a larger table holding only the tree's paths; the old one, with this call's
         // claims, is discarded once rehash has synchronised the stream
@@ -673,11 +691,8 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
   Timer ts;
   g_stats_ms = 0;
 
-  // ---- publish new paths, fold this call's sums into the old ones -----------------------
-  // events that order the side stream's fold after the publish, and the emission after
-  // the fold: created before anything is published
-  Event published_ev, folded, trie_fork, trie_mid, trie_join;
-  if (N > 0 && side != s && (!published_ev.ev || !folded.ev)) return undo(fail(CCT_EDEVICE, "event creation failed"));
+  // ---- publish new paths ----------------------------------------------------------------
+  Event trie_fork, trie_mid, trie_join;
   AGG_TRY(hipMemsetAsync(cursor.p, 0, 64, s));
   if (n_new) {
     // place the new paths in the store: exclusive scan of their padded lengths (listed
@@ -698,17 +713,6 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
     published = true;  // from here on, a failure empties the published slots
     launch_publish(pa, s);
   }
-  // every path's sums, once both the side stream's aggregation and the publish (which
-  // records the new paths' slots) are done; the emission waits for them
-  if (N > 0) {
-    if (side != s) {
-      AGG_TRY(hipEventRecord(published_ev.ev, s));
-      AGG_TRY(hipStreamWaitEvent(side, published_ev.ev, 0));
-    }
-    launch_fold_sums(D, t->d, m, t->pslot.as<uint32_t>(), delta.as<uint64_t>(), t->psums.as<uint64_t>(),
-                     nsums.as<uint64_t>(), side);
-    if (side != s) AGG_TRY(hipEventRecord(folded.ev, side));
-  }
   if (keep_stats) {  // the batch's samples into the fresh path arrays (new paths start empty)
     ts.mark(0, s);
     PathStats ps{ncnt.as<uint64_t>(), nmin.as<uint64_t>(), nsq.as<uint64_t>()};
@@ -719,7 +723,7 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
   }
   AGG_TRY(hipGetLastError());
   tm.mark(3, s);
-  // test setting: fail once everything is published and folded, to check that the
+  // test setting: fail once everything is published, to check that the
   // tree is left as it was
   if (env_int("CCT_TEST_FAIL_AFTER_PUBLISH", 0)) return undo(fail(CCT_EDEVICE, "test failure after publish"));
 
@@ -728,6 +732,8 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
   ca.d = D; ca.m = m; ca.exact = exact_sort ? 1 : 0;
   ca.pframes = t->pframes.as<uint32_t>(); ca.pcp = t->pcp.as<uint64_t>(); ca.pstart = t->pstart.as<int64_t>();
   ca.plen = t->plen.as<uint32_t>(); ca.psums = nsums.as<uint64_t>();
+  ca.d_old = t->d; ca.pslot = t->pslot.as<uint32_t>(); ca.delta = delta.as<uint64_t>();
+  ca.old_sums = t->psums.as<uint64_t>();
   ca.order = order.as<uint32_t>(); ca.order_tmp = order_tmp.as<uint32_t>(); ca.lcp = lcp.as<uint32_t>();
   ca.scan_in = scan_in.as<uint64_t>(); ca.scan_out = scan_out.as<uint64_t>(); ca.scan_blk = scan_blk.as<uint64_t>();
   ca.scan_blocks = nblk; ca.sparse = sparse.as<uint32_t>(); ca.levels = levels;
@@ -746,7 +752,7 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
     else if (mode == 3) launch_merge_order(run, t->order.as<uint32_t>(), t->d, merge_scratch.as<uint32_t>(), s);
     else launch_sort(run, s);
     tm.mark(4, s);
-    if (N > 0 && side != s) AGG_TRY(hipStreamWaitEvent(s, folded.ev, 0));  // the emission reads the sums
+    if (N > 0 && side != s) AGG_TRY(hipStreamWaitEvent(s, summed.ev, 0));  // launch_canon folds the sums
     launch_canon(run, s);
     AGG_TRY(hipGetLastError());
     tm.mark(5, s);

@@ -35,7 +35,7 @@ constexpr int kWaveFrames = 64 * 16 * kLaneBlocks;  // frames of a wave tile
 constexpr int kCacheEntries = 4096;     // LDS resolved-path cache entries per workgroup
 
 // ---- counters written by the ingest kernels --------------------------------------
-enum Counter { kCtrNew = 0, kCtrNewFrames = 1, kCtrError = 2, kCtrOverflow = 3, kCtrNewLen = 4,
+enum Counter { kCtrNew = 0, kCtrError = 2, kCtrOverflow = 3, kCtrNewLen = 4,
                kCtrCount = 8 };
 enum ErrorBits { kErrOffsets = 1 };
 constexpr uint32_t kNoSlot = 0xFFFFFFFFu;  // event not resolved (the call fails or retries)
@@ -138,15 +138,17 @@ int64_t agg_map_entries(int32_t m);
 void launch_aggregate(const uint32_t *slot_of, const uint64_t *w, int64_t n, int32_t m, uint64_t *delta,
                       uint64_t cap, int grid, const AggStage &st, hipStream_t s);
 // List the slots claimed in this call (word ref with kEventRef): new_slots, each new
-// path's first frame in the batch and length (src_len, two words per path) and padded
-// store length (padded, the input of the scan that places the paths in the store), and
-// into ctr: kCtrNew (count), kCtrNewFrames (sum of padded store lengths), kCtrNewLen
-// (sum of lengths).  new_slots, src_len and padded hold room for every possible new
-// path: min(cap, events of the batch).
-// part: 2 * collect_blocks(cap) words of scratch.
-int64_t collect_blocks(uint64_t cap);
+// path's first frame in the batch and length (src_len, two words per path) and its place
+// in the store relative to the frames already there (starts, 16-frame aligned, growing
+// with the list position), and into ctr: kCtrNew (count << kNewShift | 16-frame blocks of
+// store), kCtrNewLen (sum of lengths).  new_slots, src_len and starts hold room for list_cap
+// paths, every possible new one: min(cap, events of the batch).  A batch of N <= CCT_MAX_EVENTS events
+// has fewer than 2^31 new paths; the blocks of its new paths must fit kNewShift bits
+// (2^37 frames and more than a GPU holds).
+constexpr int kNewShift = 33;
+constexpr unsigned long long kNewBlocksMask = (1ull << kNewShift) - 1;
 void launch_collect_new(const Slot *slot, uint64_t cap, const int64_t *off, uint32_t *new_slots, int64_t *src_len,
-                        uint64_t *padded, unsigned long long *ctr, unsigned long long *part, hipStream_t s);
+                        uint64_t *starts, int64_t list_cap, unsigned long long *ctr, hipStream_t s);
 
 // Path store: path d occupies frames [pstart[d], pstart[d] + round16(plen[d])) of
 // pframes (pstart is a multiple of kStoreAlign, the tail is zero-filled), and its
@@ -171,7 +173,7 @@ struct PublishArgs {
   uint32_t *plen;
   uint32_t *pslot;
   int64_t store_used;        // frames already used in the store
-  const uint64_t *starts;    // [n_new] exclusive prefix sums of the padded lengths
+  const uint64_t *starts;    // [n_new] place of each new path past store_used
   const int64_t *src_len;    // [n_new][2] first frame in the batch and length of each new path
   uint64_t cp_mask;          // all ones, except under a test setting that forces collisions
 };

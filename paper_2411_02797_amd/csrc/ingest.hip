@@ -813,23 +813,25 @@ __global__ __launch_bounds__(kAggThreads) void agg_reduce_kernel(AggStage st, ui
   }
 }
 
-// Slots claimed in this call: a block of 1024 threads scans 4096 slots, counts its
-// claims, reserves list positions with one atomic, and writes them (the list order
-// is irrelevant: paths get their canonical ids later).  Lengths come from the slot's
-// info word; per-block sums of padded and exact lengths go to part[block][2].
+// Slots claimed in this call: a block of 1024 threads scans 4096 slots, counts its claims,
+// reserves list positions and store blocks for them, and writes them.  One 64-bit atomic
+// reserves both (the count in the bits from kNewShift on, 16-frame store blocks below), so
+// that path ids and places in the store grow together: the trie kernels walk the store
+// and read per-path arrays beside it.  (As a list followed by a scan of the padded
+// lengths, a totals kernel and a copy, the placement took four more launches: 22 us of a
+// 10,000-event call.)  The same packing in LDS places the block's own claims.
 constexpr int kCollectThreads = 1024, kCollectPerThread = 4;
 __global__ __launch_bounds__(kCollectThreads) void collect_new_kernel(const Slot *slot, uint64_t cap,
                                                                       const int64_t *off, uint32_t *new_slots,
-                                                                      int64_t *src_len, uint64_t *padded,
-                                                                      unsigned long long *ctr,
-                                                                      unsigned long long *part) {
-  __shared__ uint32_t cnt;
-  __shared__ unsigned long long base, frames, lens;
-  if (threadIdx.x == 0) { cnt = 0; frames = 0; lens = 0; }
+                                                                      int64_t *src_len, uint64_t *starts,
+                                                                      uint64_t list_cap, unsigned long long *ctr) {
+  __shared__ unsigned long long mine, base, lens;
+  if (threadIdx.x == 0) { mine = 0; lens = 0; }
   __syncthreads();
-  uint32_t found[kCollectPerThread], pos[kCollectPerThread];
+  uint32_t found[kCollectPerThread];
+  unsigned long long pos[kCollectPerThread];
   int64_t fsrc[kCollectPerThread], flen[kCollectPerThread];
-  uint64_t my_frames = 0, my_lens = 0;
+  uint64_t my_lens = 0;
   int nf = 0;
   for (int r = 0; r < kCollectPerThread; ++r) {
     const uint64_t s = ((uint64_t)blockIdx.x * kCollectPerThread + r) * kCollectThreads + threadIdx.x;
@@ -850,46 +852,27 @@ __global__ __launch_bounds__(kCollectThreads) void collect_new_kernel(const Slot
       found[nf] = (uint32_t)s;
       fsrc[nf] = src;
       flen[nf] = len;
-      pos[nf] = atomicAdd(&cnt, 1u);
+      pos[nf] = atomicAdd(&mine, (1ull << kNewShift) | (unsigned long long)(round_store(len) / kStoreAlign));
       ++nf;
-      my_frames += (uint64_t)round_store(len);
       my_lens += (uint64_t)len;
     }
   }
-  if (nf) {
-    atomicAdd(&frames, (unsigned long long)my_frames);
-    atomicAdd(&lens, (unsigned long long)my_lens);
-  }
+  if (nf) atomicAdd(&lens, (unsigned long long)my_lens);
   __syncthreads();
-  if (threadIdx.x == 0) {
-    base = cnt ? atomicAdd(&ctr[kCtrNew], (unsigned long long)cnt) : 0;
-    part[blockIdx.x * 2] = frames;
-    part[blockIdx.x * 2 + 1] = lens;
+  if (threadIdx.x == 0 && mine) {
+    base = atomicAdd(&ctr[kCtrNew], mine);
+    atomicAdd(&ctr[kCtrNewLen], lens);
   }
   __syncthreads();
   for (int i = 0; i < nf; ++i) {
-    const uint64_t j = base + pos[i];
+    const unsigned long long at = base + pos[i];
+    const uint64_t j = at >> kNewShift;
+    if (j >= list_cap) break;  // (lengths of malformed offsets can overflow the blocks: the call fails)
     new_slots[j] = found[i];
     src_len[2 * j] = fsrc[i];
     src_len[2 * j + 1] = flen[i];
-    padded[j] = (uint64_t)round_store(flen[i]);
+    starts[j] = (at & kNewBlocksMask) * kStoreAlign;
   }
-}
-
-// Totals of the per-block length sums into ctr (one block).
-__global__ __launch_bounds__(256) void collect_sum_kernel(const unsigned long long *part, int64_t nblk,
-                                                          unsigned long long *ctr) {
-  __shared__ unsigned long long sf[256], sl[256];
-  unsigned long long f = 0, l = 0;
-  for (int64_t i = threadIdx.x; i < nblk; i += 256) { f += part[i * 2]; l += part[i * 2 + 1]; }
-  sf[threadIdx.x] = f;
-  sl[threadIdx.x] = l;
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) { sf[threadIdx.x] += sf[threadIdx.x + o]; sl[threadIdx.x] += sl[threadIdx.x + o]; }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) { ctr[kCtrNewFrames] = sf[0]; ctr[kCtrNewLen] = sl[0]; }
 }
 
 // Publish the paths first seen in this call: give each a path id, copy its frames into
@@ -1062,14 +1045,11 @@ void launch_aggregate(const uint32_t *slot_of, const uint64_t *w, int64_t n, int
     default: break;
   }
 }
-int64_t collect_blocks(uint64_t cap) { return (int64_t)((cap + kCollectThreads * kCollectPerThread - 1) /
-                                                         (kCollectThreads * kCollectPerThread)); }
 void launch_collect_new(const Slot *slot, uint64_t cap, const int64_t *off, uint32_t *new_slots, int64_t *src_len,
-                        uint64_t *padded, unsigned long long *ctr, unsigned long long *part, hipStream_t s) {
-  const int64_t nb = collect_blocks(cap);
-  hipLaunchKernelGGL(collect_new_kernel, dim3((unsigned)nb), dim3(kCollectThreads), 0, s, slot, cap, off, new_slots,
-                     src_len, padded, ctr, part);
-  hipLaunchKernelGGL(collect_sum_kernel, dim3(1), dim3(256), 0, s, part, nb, ctr);
+                        uint64_t *starts, int64_t list_cap, unsigned long long *ctr, hipStream_t s) {
+  const uint64_t per = (uint64_t)kCollectThreads * kCollectPerThread;
+  hipLaunchKernelGGL(collect_new_kernel, dim3((unsigned)((cap + per - 1) / per)), dim3(kCollectThreads), 0, s, slot,
+                     cap, off, new_slots, src_len, starts, (uint64_t)list_cap, ctr);
 }
 void launch_publish(const PublishArgs &a, hipStream_t s) {
   if (a.n_new <= 0) return;

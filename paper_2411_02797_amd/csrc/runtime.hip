@@ -454,7 +454,7 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
     cct_status st = rehash(t, pow2_at_least((uint64_t)t->d * 4), hash_mask, s);
     if (st) return st;
   }
-  Buf delta, slot_of, cpart, agg_count, agg_keys, agg_sums, nlen, nsrc;
+  Buf delta, slot_of, agg_count, agg_keys, agg_sums, nstart, nsrc;
   uint64_t new_frames = 0, new_store = 0;
   // The metric sums run on a second stream of the library, from the moment the ingest's
   // slot ids are complete: they overlap the host's reading of the counters, the publish
@@ -483,8 +483,7 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
       if (attempt > 12) return fail(CCT_EOVERFLOW, "unique-path table cannot grow further");
       const int64_t max_new = (int64_t)std::min<uint64_t>(t->cap, (uint64_t)N);  // distinct paths of the batch
       if (!delta.alloc(t->cap * m * 8) || !new_slots.alloc(t->cap * 4) ||
-          !cpart.alloc((size_t)collect_blocks(t->cap) * 16) || !nsrc.alloc((size_t)max_new * 16) ||
-          !nlen.alloc((size_t)(max_new + 1) * 8))
+          !nsrc.alloc((size_t)max_new * 16) || !nstart.alloc((size_t)max_new * 8))
         return fail(CCT_ENOMEM, "device allocation failed");
       AGG_TRY(hipMemsetAsync(delta.p, 0, t->cap * m * 8, s));
       AGG_TRY(hipMemsetAsync(dctr, 0, kCtrCount * 8, s));
@@ -502,7 +501,7 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
       launch_ingest(a, grid, s);
       tm.mark(2, s);
       launch_collect_new(t->slot.as<Slot>(), t->cap, p->offsets, new_slots.as<uint32_t>(), nsrc.as<int64_t>(),
-                         nlen.as<uint64_t>(), dctr, cpart.as<unsigned long long>(), s);
+                         nstart.as<uint64_t>(), max_new, dctr, s);
       claimed = true;  // (from the launch on: the table may hold this call's claims)
       AGG_TRY(hipGetLastError());
       AGG_TRY(hipMemcpyAsync(hs, dctr, kCtrCount * 8, hipMemcpyDeviceToHost, s));
@@ -532,10 +531,10 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
         claimed = false;
         continue;
       }
-      n_new = hs[kCtrNew];
+      n_new = hs[kCtrNew] >> kNewShift;
       claimed = n_new > 0;
       new_frames = hs[kCtrNewLen];
-      new_store = hs[kCtrNewFrames];
+      new_store = (hs[kCtrNew] & kNewBlocksMask) * kStoreAlign;
       break;
     }
   }
@@ -634,14 +633,13 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
   const int levels = floor_log2((uint64_t)n1) + 1;
   const int64_t nblk = (D + 1023) / 1024 + 1;
   const int64_t u_max = sum_len + 1;
-  Buf order, order_tmp, lcp, scan_in, scan_out, scan_blk, sparse, chain, win_path, cursor, nstart, nblkbuf;
+  Buf order, order_tmp, lcp, scan_in, scan_out, scan_blk, sparse, chain, win_path, cursor;
   Buf n_parent, n_frame, n_depth, n_subend, n_excl, n_incl;  // canonical arrays of the new tree
   if (!order.alloc(dneed * 4) || !order_tmp.alloc(dneed * 4) || !lcp.alloc(n1 * 4) || !scan_in.alloc(dneed * C * 8) ||
       !scan_out.alloc(n1 * C * 8) || !scan_blk.alloc(nblk * C * 8) || !sparse.alloc((int64_t)levels * n1 * 4) ||
       !chain.alloc(dneed * 4) || !win_path.alloc((u_max / 64 + 2) * 4) || !cursor.alloc(64) || !n_parent.alloc(u_max * 4) || !n_subend.alloc(u_max * 4) ||
       !n_frame.alloc(u_max * 4) || !n_depth.alloc(u_max * 4) || !n_excl.alloc(u_max * m * 8) ||
-      !n_incl.alloc(u_max * m * 8) || !nstart.alloc((n_new + 1) * 8) ||
-      !nblkbuf.alloc(((int64_t)n_new / 1024 + 2) * 8))
+      !n_incl.alloc(u_max * m * 8))
     return undo(fail(CCT_ENOMEM, "device allocation failed"));
 
   // sorting scratch, allocated before the tree is touched
@@ -695,10 +693,6 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
   Event trie_fork, trie_mid, trie_join;
   AGG_TRY(hipMemsetAsync(cursor.p, 0, 64, s));
   if (n_new) {
-    // place the new paths in the store: exclusive scan of their padded lengths (listed
-    // by collect_new with their first frames and lengths)
-    launch_scan(nlen.as<uint64_t>(), (int64_t)n_new, 1, nblkbuf.as<uint64_t>(), nstart.as<uint64_t>(), s);
-    AGG_TRY(hipMemcpyAsync(cursor.p, nstart.as<uint64_t>() + n_new, 8, hipMemcpyDeviceToDevice, s));
     PublishArgs pa{};
     pa.off = p->offsets; pa.fr = p->frames; pa.n_frames = p->n_frames; pa.slot = t->slot.as<Slot>();
     pa.new_slots = new_slots.as<uint32_t>(); pa.n_new = (int64_t)n_new; pa.d_old = t->d;
@@ -773,7 +767,7 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
   if (keep_stats && ts.ok) g_stats_ms = ts.span(0, 1);
 
   // ---- commit -------------------------------------------------------------------------------
-  t->store_used += (int64_t)hs[0];
+  t->store_used += (int64_t)new_store;
   t->d = D;
   t->sum_len = sum_len;
   t->u = (int64_t)hs[2];

@@ -229,84 +229,124 @@ __global__ __launch_bounds__(256) void place_old_kernel(const uint32_t *A, int64
 }
 
 // ---- exact verification, lcp, sums, scan rows ------------------------------------------------
-// Sixteen lanes per pair of neighbours: a step compares 64 frames of both with one 16-byte
-// load each (256 consecutive bytes per path), and the first lane with a difference holds
-// the LCP.  With one lane per pair the longest paths of a wave set its time, eight
-// dependent 16-byte loads per 16 frames: 60,013 events with paths of up to 2,500 frames
-// and 14,444 distinct ones 186 -> 22 us, 149,201 paths of 256 to 512 frames 83 -> 55 us (their
-// frames at 8 TB/s from the caches), 154,413 paths of 72 frames on average 24 -> 23 us.
-constexpr int kLcpLanes = 16;
-__device__ inline void lcp_one(const CanonArgs &a, int64_t i, int lane) {
+// Eight lanes per pair of neighbours: a step compares 64 frames of both, two 16-byte loads
+// per lane and path, and the first lane with a difference holds the LCP.  With one lane per
+// pair the longest paths of a wave set its time, eight dependent 16-byte loads per 16
+// frames.  Now, with the scan's block sums, level 1 of the minima and the sums' fold in the
+// same pass (they were two launches more): 14,444 paths of up to 2,500 frames 191 -> 33 us,
+// 149,201 paths of 256 to 512 frames 86 -> 61 us (their frames at 8 TB/s from the caches),
+// 154,413 paths of 72 frames on average 24 -> 25 us.  Sixteen lanes with one load: 21, 66
+// and 36 us; four lanes with four: 36, 61 and 23 us.
+constexpr int kLcpLanes = 8;
+constexpr int kLcpPieces = 2;                        // 16-byte loads per lane, path and step
+constexpr int kLcpPer = 256 / kLcpLanes;             // positions per workgroup and round
+constexpr uint32_t kLcpPiece = 4 * kLcpLanes;        // frames per piece
+static_assert(kLcpPer % 16 == 0, "whole entries of level 1 of the minima per workgroup and round");
+
+// lcp of position i (every lane of the position's group gets it); u_out[1] if the two paths
+// are not strictly increasing
+__device__ inline uint32_t lcp_at(const CanonArgs &a, int64_t i, uint32_t p, uint32_t len, int lane) {
   const int g = lane % kLcpLanes;
-  const int C = 1 + a.m;
-  if (i == a.d) {
-    if (g == 0) { a.lcp[i] = 0; a.sparse[i] = 0; }
-    return;
-  }
-  // an order from a misleading hash may hold entries that are not path ids: they raise
-  // the flag and read as path 0 here and in the kernels after this one
-  uint32_t p = a.order[i], q = i > 0 ? a.order[i - 1] : 0u;
-  const bool bad = p >= (uint64_t)a.d;
-  if (bad) p = 0;
+  if (i == 0) return 0;
+  uint32_t q = a.order[i - 1];
   if (q >= (uint64_t)a.d) q = 0;
-  const uint32_t len = a.plen[p];
-  uint32_t l = 0;
-  if (i > 0) {
-    const uint32_t lq = a.plen[q], n = min(lq, len);
-    const uint32_t *pq = a.pframes + a.pstart[q], *pp = a.pframes + a.pstart[p];
-    bool less = lq < len;  // the order of the two if they agree on n frames
-    l = n;
-    for (uint32_t k0 = 0; k0 < n; k0 += 4 * kLcpLanes) {
-      // (starts are 16-frame aligned and tails are padded: a lane whose first frame is
-      // below n stays in both paths' slots)
-      const uint32_t k = k0 + 4 * g;
-      int e = 4;  // this lane's first difference
-      bool lt = false;
-      if (k < n) {
-        const u32x4 x = ld4(pq + k), y = ld4(pp + k);
+  const uint32_t lq = a.plen[q], n = min(lq, len);
+  const uint32_t *pq = a.pframes + a.pstart[q], *pp = a.pframes + a.pstart[p];
+  bool less = lq < len;  // the order of the two if they agree on n frames
+  uint32_t l = n;
+  bool done = false;
+  for (uint32_t k0 = 0; k0 < n && !done; k0 += kLcpPiece * kLcpPieces) {
+    // (starts are 16-frame aligned and tails are padded: a lane whose first frame is
+    // below n stays in both paths' slots)
+    u32x4 x[kLcpPieces], y[kLcpPieces];
 #pragma unroll
-        for (int c = 3; c >= 0; --c)
-          if (k + c < n && x[c] != y[c]) { e = c; lt = x[c] < y[c]; }
-      }
-      const uint32_t found = (uint32_t)(__ballot(e < 4) >> (lane - g)) & ((1u << kLcpLanes) - 1);
-      const uint32_t lts = (uint32_t)(__ballot(lt) >> (lane - g)) & ((1u << kLcpLanes) - 1);
-      if (found) {
+    for (int v = 0; v < kLcpPieces; ++v) {
+      const uint32_t k = k0 + v * kLcpPiece + 4 * g, at = k < n ? k : 0;
+      x[v] = ld4(pq + at);
+      y[v] = ld4(pp + at);
+    }
+#pragma unroll
+    for (int v = 0; v < kLcpPieces; ++v) {
+      const uint32_t k = k0 + v * kLcpPiece + 4 * g;
+      uint32_t e = 8;  // this lane's first difference: frame, and whether x is the smaller
+#pragma unroll
+      for (int c = 3; c >= 0; --c)
+        if (k + c < n && x[v][c] != y[v][c]) e = 2 * c + (x[v][c] < y[v][c] ? 1 : 0);
+      const uint32_t found = (uint32_t)(__ballot(e < 8) >> (lane - g)) & ((1u << kLcpLanes) - 1);
+      if (found && !done) {
         const int f = __builtin_ctz(found);
-        l = k0 + 4 * f + (uint32_t)__shfl(e, lane - g + f, 64);
-        less = (lts >> f) & 1;
-        break;
+        const uint32_t ef = __shfl(e, lane - g + f, 64);
+        l = k0 + v * kLcpPiece + 4 * f + (ef >> 1);
+        less = ef & 1;
+        done = true;
       }
     }
-    if (!less && g == 0) atomicOr(&a.u_out[1], 1ull);  // not strictly increasing
   }
-  if (g == 0) {
-    if (bad) {
-      atomicOr(&a.u_out[1], 1ull);
-      a.order[i] = 0;
-    }
-    a.lcp[i] = l;
-    a.sparse[i] = l;  // level 0 of the range-minimum table
-  }
-  uint64_t *row = a.scan_in + i * C;
-  // the path's sums after the batch: every path sits at one position of a good order, so
-  // this pass folds each path's batch sums into its old ones, into the fresh array (a bad
-  // order's leftovers are overwritten when the corrected order comes through here)
-  const uint32_t sl = a.pslot[p];
-  for (int j = g; j < C; j += kLcpLanes) {
-    uint64_t v = (uint64_t)(len - l);
-    if (j > 0) {
-      const int64_t at = (int64_t)p * a.m + j - 1;
-      v = a.delta[(uint64_t)sl * a.m + j - 1] + (p < (uint64_t)a.d_old ? a.old_sums[at] : 0);
-      a.psums[at] = v;
-    }
-    row[j] = v;
-  }
+  if (!less && g == 0) atomicOr(&a.u_out[1], 1ull);  // not strictly increasing
+  return l;
 }
 
+// A workgroup's consecutive positions lie in one block of the scan, whose sums they meet
+// in LDS first (one atomic per column), and fill whole entries of level 1 of the minima.
 __global__ __launch_bounds__(256) void lcp_kernel(CanonArgs a) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x / kLcpLanes;
-  for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kLcpLanes; i <= a.d; i += stride)
-    lcp_one(a, i, threadIdx.x & 63);
+  __shared__ uint32_t ls[kLcpPer];
+  __shared__ uint64_t rows[kLcpPer][9];
+  const int C = 1 + a.m, lane = threadIdx.x & 63, g = lane % kLcpLanes, r = threadIdx.x / kLcpLanes;
+  // levels of the minima from 3 up are met by atomics in the next kernel
+  if (blockIdx.x == 0)
+    for (int v = 3; v < a.min_levels; ++v)
+      for (int64_t k = threadIdx.x; k < a.min_n[v]; k += blockDim.x) a.mins[v][k] = kInf;
+  for (int64_t i0 = (int64_t)blockIdx.x * kLcpPer; i0 <= a.d; i0 += (int64_t)gridDim.x * kLcpPer) {
+    const int64_t i = i0 + r;
+    uint32_t l = kInf;  // (past the last position)
+    if (i == a.d) l = 0;
+    if (i < a.d) {
+      // an order from a misleading hash may hold entries that are not path ids: they raise
+      // the flag and read as path 0 here and in the kernels after this one
+      uint32_t p = a.order[i];
+      const bool bad = p >= (uint64_t)a.d;
+      if (bad) p = 0;
+      const uint32_t len = a.plen[p], sl = a.pslot[p];
+      l = lcp_at(a, i, p, len, lane);
+      if (bad && g == 0) {
+        atomicOr(&a.u_out[1], 1ull);
+        a.order[i] = 0;
+      }
+      // the path's sums after the batch: every path sits at one position of a good order,
+      // so this pass folds each path's batch sums into its old ones, into the fresh array
+      // (a bad order's leftovers are overwritten when the corrected order comes through)
+      for (int c = g; c < C; c += kLcpLanes) {
+        uint64_t v = (uint64_t)(len - l);
+        if (c > 0) {
+          const int64_t at = (int64_t)p * a.m + c - 1;
+          v = a.delta[(uint64_t)sl * a.m + c - 1] + (p < (uint64_t)a.d_old ? a.old_sums[at] : 0);
+          a.psums[at] = v;
+        }
+        a.scan_in[i * C + c] = v;
+        rows[r][c] = v;
+      }
+    } else {
+      for (int c = g; c < C; c += kLcpLanes) rows[r][c] = 0;
+    }
+    if (g == 0) {
+      ls[r] = l;
+      if (i <= a.d) a.lcp[i] = l;
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < C) {
+      uint64_t t = 0;
+#pragma unroll
+      for (int k = 0; k < kLcpPer; ++k) t += rows[k][threadIdx.x];
+      if (t) atomicAdd((unsigned long long *)&a.scan_blk[i0 / kScanRows * C + threadIdx.x], (unsigned long long)t);
+    } else if (threadIdx.x >= 64 && threadIdx.x < 64 + kLcpPer / 16) {
+      const int e = (int)threadIdx.x - 64;
+      uint32_t t = kInf;
+#pragma unroll
+      for (int k = 0; k < 16; ++k) t = min(t, ls[16 * e + k]);
+      if (i0 / 16 + e < a.min_n[1] && a.min_levels > 1) a.mins[1][i0 / 16 + e] = t;
+    }
+    __syncthreads();
+  }
 }
 
 // ---- multi-column exclusive scan (uint64, mod 2^64) -------------------------------------
@@ -409,92 +449,145 @@ __global__ __launch_bounds__(256) void scan_final_kernel(const uint64_t *in, int
   }
 }
 
-// ---- range minima of lcp over [0, D] (lcp[D] = 0 is the sentinel) --------------------
-__global__ void sparse_level_kernel(uint32_t *sp, int64_t n, int k) {
-  // level k from level k-1 (k >= 1): minimum of lcp over [x, min(n, x + 2^k))
-  const int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (x >= n) return;
-  const uint32_t *prev = sp + (int64_t)(k - 1) * n;
-  const int64_t h = (int64_t)1 << (k - 1);
-  uint32_t v = prev[x];
-  if (x + h < n) v = min(v, prev[x + h]);
-  sp[(int64_t)k * n + x] = v;
-}
-
-// Levels top + 1 .. top + count in one launch: level k at x is the minimum of the
-// level-top windows starting at x, x + 2^top, ... below x + 2^k (windows past n left
-// out), so each thread reads 2^count - 1 level-top entries instead of waiting for the
-// level below.
-constexpr int kHighLevels = 7;  // levels per launch: 127 level-top reads per position
-__global__ void sparse_high_kernel(uint32_t *sp, int64_t n, int top, int count) {
-  const int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (x >= n) return;
-  const uint32_t *lv = sp + (int64_t)top * n;
-  const int64_t w = (int64_t)1 << top;
-  uint32_t v = lv[x];
-  for (int c = 1; c <= count; ++c) {
-    // the new half of level top + c: windows x + 2^(top + c - 1) + j w, j < 2^(c - 1)
-    const int64_t lo = x + (w << (c - 1));
-    for (int64_t j = 0; j < ((int64_t)1 << (c - 1)); ++j) {
-      const int64_t y = lo + j * w;
-      if (y >= n) break;
-      v = min(v, lv[y]);
+// ---- scan of the canonical rows, upper levels of the minima -----------------------------
+// Workgroup (b, y) writes the exclusive prefix sums of columns y, y + gridDim.y, ... of
+// rows [1024 b, 1024 b + 1024).  scan_blk holds the sums of every 1024 rows (lcp_kernel):
+// each workgroup adds up those before it (direct), or they are scanned already.  The
+// workgroups with y = 0 also build level 2 of the minima and meet in the levels above.
+__global__ __launch_bounds__(256) void canon_scan_kernel(CanonArgs a, int direct) {
+  __shared__ uint64_t part[4], pre[4];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, C = 1 + a.m;
+  const int64_t b = blockIdx.x, r0 = b * kScanRows + tid * 4;
+  if (blockIdx.y == 0 && tid < 64 && a.min_levels > 2) {
+    const int64_t k = b * (kScanRows / 16) + tid;
+    uint32_t t = k < a.min_n[1] ? a.mins[1][k] : kInf;
+    for (int o = 32; o > 0; o >>= 1) t = min(t, (uint32_t)__shfl_xor(t, o, 64));
+    if (tid == 0) {
+      a.mins[2][b] = t;
+      int64_t at = b;
+      for (int v = 3; v < a.min_levels; ++v) {
+        at >>= 6;
+        atomicMin(&a.mins[v][at], t);
+      }
     }
-    sp[(int64_t)(top + c) * n + x] = v;
   }
-}
-
-// Levels 1 .. kTileLevels in one pass: a workgroup takes kTileOut positions, loads
-// their lcp values and the 2^kTileLevels - 1 after them (past n: +inf) into LDS,
-// and builds every level there from the one below.
-constexpr int kTileLevels = 11, kTileOut = 2048, kTileIn = kTileOut + (1 << kTileLevels);
-__global__ __launch_bounds__(1024) void sparse_tile_kernel(uint32_t *sp, const uint32_t *lcp, int64_t n, int top) {
-  __shared__ uint32_t buf[2][kTileIn];
-  const int64_t x0 = (int64_t)blockIdx.x * kTileOut;
-  for (int i = threadIdx.x; i < kTileIn; i += 1024) buf[0][i] = x0 + i < n ? lcp[x0 + i] : 0xFFFFFFFFu;
-  __syncthreads();
-  int cur = 0;
-  for (int k = 1; k <= top; ++k) {
-    const int h = 1 << (k - 1);
-    for (int i = threadIdx.x; i + h < kTileIn; i += 1024) buf[cur ^ 1][i] = min(buf[cur][i], buf[cur][i + h]);
+  for (int c = blockIdx.y; c < C; c += gridDim.y) {
+    uint64_t v[4], s = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      v[k] = r0 + k < a.d ? a.scan_in[(r0 + k) * C + c] : 0;
+      s += v[k];
+    }
+    uint64_t x = 0;  // this thread's share of the sums of the earlier blocks
+    if (direct)
+      for (int64_t j = tid; j < b; j += 256) x += a.scan_blk[j * C + c];
+    for (int o = 32; o > 0; o >>= 1) {
+      const uint32_t lo = __shfl_xor((uint32_t)x, o, 64), hi = __shfl_xor((uint32_t)(x >> 32), o, 64);
+      x += ((uint64_t)hi << 32) | lo;
+    }
+    uint64_t y = s;
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint64_t z = shfl_up_u64(y, o);
+      if (lane >= o) y += z;
+    }
+    if (lane == 0) pre[wave] = x;
+    if (lane == 63) part[wave] = y;
     __syncthreads();
-    cur ^= 1;
-    for (int i = threadIdx.x; i < kTileOut; i += 1024)
-      if (x0 + i < n) sp[(int64_t)k * n + x0 + i] = buf[cur][i];
+    uint64_t run = (direct ? pre[0] + pre[1] + pre[2] + pre[3] : a.scan_blk[b * C + c]) + y - s;
+    for (int w = 0; w < wave; ++w) run += part[w];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      // (row D holds the totals: every row before it is in this block or an earlier one)
+      if (r0 + k <= a.d) a.scan_out[(r0 + k) * C + c] = run;
+      run += v[k];
+    }
+    __syncthreads();
   }
 }
 
-// first j >= s with lcp[j] < t (exists: lcp[D] = 0 < t for t >= 1).  Exponential search:
-// skip blocks of 1, 2, 4, ... entries while a whole block is >= t, then descend within the
-// block that holds the answer; about 2 log2(j - s) dependent loads instead of one per
-// level, and most subtrees end a few paths on.
-__device__ inline int64_t next_smaller(const CanonArgs &a, int64_t n, int64_t s, uint32_t t) {
-  int64_t j = s;
-  int k = 0;
-  while (k < a.levels && j + ((int64_t)1 << k) <= n && a.sparse[(int64_t)k * n + j] >= t) {
-    j += (int64_t)1 << k;
-    ++k;
-  }
-  for (int q = k - 1; q >= 0; --q) {
-    const int64_t w = (int64_t)1 << q;
-    if (j + w <= n && a.sparse[(int64_t)q * n + j] >= t) j += w;
-  }
-  return j;
+// ---- range minima of lcp over [0, D] (lcp[D] = 0 is the sentinel) --------------------
+// The searches below look at sixteen entries at a time (four 16-byte loads in flight
+// together): most answers lie in the entries next to the start, one round trip away.
+// (A table of every power of two took two launches to build, 17 words per path, and a
+// search of it two dependent 4-byte loads per doubling of the distance.)
+
+// Positions fit 32 bits (a tree has fewer than 2^32 - 2 nodes, and every path but the
+// empty one a node of its own); not-found is kInf.
+
+// bit k: p[k] < t, for sixteen entries at a 64-byte aligned address
+__device__ inline uint32_t below16(const uint32_t *p, uint32_t t) {
+  u32x4 v[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) v[c] = ld4(p + 4 * c);
+  uint32_t m = 0;
+#pragma unroll
+  for (int c = 0; c < 4; ++c)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) m |= v[c][e] < t ? 1u << (4 * c + e) : 0u;
+  return m;
 }
-// largest j <= s with lcp[j] < t (exists: lcp[0] = 0 < t for t >= 1), the same search
-// towards smaller indices
-__device__ inline int64_t prev_smaller(const CanonArgs &a, int64_t n, int64_t s, uint32_t t) {
-  int64_t j = s;
-  int k = 0;
-  while (k < a.levels && j - ((int64_t)1 << k) + 1 >= 0 && a.sparse[(int64_t)k * n + (j - ((int64_t)1 << k) + 1)] >= t) {
-    j -= (int64_t)1 << k;
-    ++k;
+// first entry from k to the last one of its group of w (16 or 64; last: the level's last
+// entry) below t
+__device__ inline uint32_t first_below(const uint32_t *lv, uint32_t k, uint32_t w, uint32_t last, uint32_t t) {
+  const uint32_t end = min(k | (w - 1), last);
+  for (uint32_t c = k & ~15u;; c += 16) {
+    uint32_t m = below16(lv + c, t);
+    if (c < k) m &= ~0u << (k - c);
+    if (m) {
+      const uint32_t f = c + (uint32_t)__builtin_ctz(m);
+      return f <= end ? f : kInf;  // (past the end: padding)
+    }
+    if (end - c < 16) return kInf;
   }
-  for (int q = k - 1; q >= 0; --q) {
-    const int64_t w = (int64_t)1 << q;
-    if (j - w + 1 >= 0 && a.sparse[(int64_t)q * n + (j - w + 1)] >= t) j -= w;
+}
+// last entry from the first one of k's group of w up to k below t
+__device__ inline uint32_t last_below(const uint32_t *lv, uint32_t k, uint32_t w, uint32_t t) {
+  for (uint32_t c = k & ~15u;; c -= 16) {
+    uint32_t m = below16(lv + c, t);
+    if (k - c < 15) m &= (2u << (k - c)) - 1;
+    if (m) return c + 31 - (uint32_t)__builtin_clz(m);
+    if ((c & (w - 1)) == 0) return kInf;
   }
-  return j;
+}
+
+// first j >= s with lcp[j] < t (exists for s <= D: lcp[D] = 0 < t for t >= 1): up through
+// the levels to the first entry that holds such a position, then down to it
+__device__ inline uint32_t next_smaller(const CanonArgs &a, uint32_t s, uint32_t t) {
+  uint32_t k = s, w = 16;
+  int v = 0;
+  for (;;) {
+    const uint32_t f = first_below(a.mins[v], k, w, (uint32_t)a.min_n[v] - 1, t);
+    if (f != kInf) { k = f; break; }
+    k = k / w + 1;
+    w = 64;
+    if (++v == a.min_levels || k >= (uint64_t)a.min_n[v]) return (uint32_t)a.d;
+  }
+  while (v > 0) {
+    k *= w = --v == 0 ? 16 : 64;
+    k = first_below(a.mins[v], k, w, (uint32_t)a.min_n[v] - 1, t);
+    if (k == kInf) return (uint32_t)a.d;
+  }
+  return k;
+}
+// largest j <= s with lcp[j] < t (exists for s >= 0: lcp[0] = 0 < t for t >= 1), the same
+// search towards smaller indices
+__device__ inline uint32_t prev_smaller(const CanonArgs &a, uint32_t s, uint32_t t) {
+  uint32_t k = s, w = 16;
+  int v = 0;
+  for (;;) {
+    const uint32_t f = last_below(a.mins[v], k, w, t);
+    if (f != kInf) { k = f; break; }
+    k /= w;
+    w = 64;
+    if (k-- == 0 || ++v == a.min_levels) return 0;
+  }
+  while (v > 0) {
+    w = --v == 0 ? 16 : 64;
+    k = (uint32_t)min((uint64_t)k * w + w - 1, (uint64_t)a.min_n[v] - 1);
+    k = last_below(a.mins[v], k, w, t);
+    if (k == kInf) return 0;
+  }
+  return k;
 }
 
 __device__ inline uint64_t node_base(const CanonArgs &a, int64_t i) { return 1 + a.scan_out[i * (1 + a.m)]; }
@@ -506,11 +599,10 @@ __device__ inline uint64_t node_base(const CanonArgs &a, int64_t i) { return 1 +
 __global__ void chain_kernel(CanonArgs a) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= a.d) return;
-  const int64_t n = a.d + 1;
   const uint32_t L = a.lcp[i];
   uint32_t par = 0;
   if (L > 0) {
-    const int64_t c = prev_smaller(a, n, i - 1, L);
+    const int64_t c = prev_smaller(a, i - 1, L);
     par = (uint32_t)(node_base(a, c) + L - a.lcp[c] - 1);
   }
   a.chain_parent[i] = par;
@@ -527,7 +619,13 @@ __global__ void chain_kernel(CanonArgs a) {
   for (uint64_t w = (b + 63) / 64; w <= (b + cnt - 1) / 64; ++w) a.win_path[w] = (uint32_t)i;
 }
 
-__global__ __launch_bounds__(256) void emit_kernel(CanonArgs a) {
+// Waves: waves per SIMD the registers leave room for.  The kernel waits for chains of
+// dependent loads, so up to 4 metrics it is held to 64 VGPRs for 8 waves (4,222,948 nodes
+// of 2 metrics: 111 us at 73 VGPRs, 101 us at 64 with a few spills); from 5 metrics on
+// its LDS rows allow 4 or 5 waves anyway (4,000,380 nodes of 8 metrics: 172 us, 177 at 64
+// VGPRs).
+template <int Waves>
+__global__ __launch_bounds__(256, Waves) void emit_kernel(CanonArgs a) {
   // a wave's 64 consecutive nodes stage their excl and incl rows in LDS ([2][256][m]
   // words), then write each array's 64 m words as one contiguous stretch
   extern __shared__ uint64_t emit_stage[];
@@ -535,7 +633,6 @@ __global__ __launch_bounds__(256) void emit_kernel(CanonArgs a) {
   const int C = 1 + a.m, m = a.m;
   const int lane = threadIdx.x & 63, w0 = threadIdx.x - lane;
   uint64_t *sx = emit_stage + (int64_t)w0 * m, *si = emit_stage + (int64_t)(256 + w0) * m;
-  const int64_t n = a.d + 1;
   // (bounded by u_max, as in chain_kernel: past it the order is not a permutation)
   const int64_t U_all = (int64_t)(1 + a.scan_out[a.d * C]);
   const int64_t U = U_all < a.u_max ? U_all : a.u_max;
@@ -577,7 +674,7 @@ __global__ __launch_bounds__(256) void emit_kernel(CanonArgs a) {
       a.subend[0] = (uint32_t)U;
       const bool empty_path = a.d > 0 && a.plen[a.order[0]] == 0;
       for (int j = 0; j < m; ++j) {
-        sx[j] = empty_path ? a.psums[(int64_t)a.order[0] * m + j] : 0;
+        sx[j] = empty_path ? a.scan_out[C + 1 + j] : 0;
         si[j] = a.scan_out[a.d * C + 1 + j];
       }
     } else if (u < U) {
@@ -598,12 +695,12 @@ __global__ __launch_bounds__(256) void emit_kernel(CanonArgs a) {
       a.parent[u] = u == (int64_t)b ? a.chain_parent[i] : (uint32_t)(u - 1);
       a.frame[u] = l ? a.pframes[a.pstart[pid] + l - 1] : 0u;
       a.depth[u] = l;
-      const int64_t e = (i + 1 == a.d || l > a.lcp[i + 1]) ? i + 1 : next_smaller(a, n, i + 2, l);
+      const int64_t e = (i + 1 == a.d || l > a.lcp[i + 1]) ? i + 1 : next_smaller(a, i + 2, l);
       // the subtree is the paths i .. e-1 below depth l: ids up to the first node of path e
       a.subend[u] = (uint32_t)node_base(a, e);
       const uint64_t *pi = a.scan_out + i * C, *pe = a.scan_out + e * C;
       for (int j = 0; j < m; ++j) {
-        sx[lane * m + j] = l == len ? a.psums[(int64_t)pid * m + j] : 0;
+        sx[lane * m + j] = l == len ? pi[C + 1 + j] - pi[1 + j] : 0;  // the path's own sums
         si[lane * m + j] = pe[1 + j] - pi[1 + j];
       }
     }
@@ -675,25 +772,40 @@ void launch_scan(const uint64_t *in, int64_t rows, int C, uint64_t *blk, uint64_
   }
 }
 
+int64_t min_level_words(int64_t n, CanonArgs &a) {
+  int64_t words = 0, k = n;
+  a.min_levels = 1;
+  a.min_n[0] = n;
+  while (k > (a.min_levels == 1 ? 16 : 64) && a.min_levels < 6) {  // until one group is left
+    k = a.min_levels == 1 ? (k + 15) / 16 : (k + 63) / 64;
+    a.min_n[a.min_levels++] = k;
+    words += (k + 15) / 16 * 16;
+  }
+  return words;
+}
+void set_min_levels(CanonArgs &a, uint32_t *words) {
+  a.mins[0] = a.lcp;
+  for (int v = 1; v < a.min_levels; ++v) {
+    a.mins[v] = words;
+    words += (a.min_n[v] + 15) / 16 * 16;
+  }
+}
+
 void launch_canon(const CanonArgs &a, hipStream_t s) {
   const int C = 1 + a.m;
   const int64_t n = a.d + 1;
-  // (a launch holds fewer than 2^32 work items: more pairs loop)
-  hipLaunchKernelGGL(lcp_kernel, dim3(std::min(blocks_for(n, 256 / kLcpLanes), 1u << 22)), dim3(256), 0, s, a);
-  launch_scan(a.scan_in, a.d, C, a.scan_blk, a.scan_out, s);
-  // range-minimum table: level 0 (lcp itself) written by lcp_kernel, levels up to
-  // kTileLevels in LDS tiles, the rest one level per launch
-  const int top = std::min(a.levels - 1, kTileLevels);
-  if (top >= 1)
-    hipLaunchKernelGGL(sparse_tile_kernel, dim3(blocks_for(n, kTileOut)), dim3(1024), 0, s, a.sparse, a.lcp, n, top);
-  if (top >= 1 && top < a.levels - 1) {
-    const int count = std::min(a.levels - 1 - top, kHighLevels);
-    hipLaunchKernelGGL(sparse_high_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, a.sparse, n, top, count);
-    for (int k = top + count + 1; k < a.levels; ++k)
-      hipLaunchKernelGGL(sparse_level_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, a.sparse, n, k);
-  }
+  // (a launch holds fewer than 2^32 work items: more positions loop)
+  hipLaunchKernelGGL(lcp_kernel, dim3(std::min(blocks_for(n, kLcpPer), 1u << 22)), dim3(256), 0, s, a);
+  const int64_t nblk = (n + kScanRows - 1) / kScanRows;
+  const int direct = nblk <= kScanDirectBlocks ? 1 : 0;
+  if (!direct)
+    hipLaunchKernelGGL(scan_blocks_kernel, dim3(1), dim3(256), 0, s, a.scan_blk, nblk, C, a.scan_out, a.d);
+  // few blocks: the columns side by side as well (each then reads the rows for itself)
+  hipLaunchKernelGGL(canon_scan_kernel, dim3((unsigned)nblk, nblk <= 256 ? C : 1), dim3(256), 0, s, a, direct);
   if (a.d > 0) hipLaunchKernelGGL(chain_kernel, dim3(blocks_for(a.d, 256)), dim3(256), 0, s, a);
-  hipLaunchKernelGGL(emit_kernel, dim3(a.grid_nodes), dim3(256), (size_t)2 * 256 * a.m * 8, s, a);
+  const size_t stage = (size_t)2 * 256 * a.m * 8;
+  if (a.m <= 4) hipLaunchKernelGGL(emit_kernel<8>, dim3(a.grid_nodes), dim3(256), stage, s, a);
+  else hipLaunchKernelGGL(emit_kernel<4>, dim3(a.grid_nodes), dim3(256), stage, s, a);
 }
 
 }  // namespace cct

@@ -207,13 +207,16 @@ struct CanonArgs {
   // outputs / scratch
   uint32_t *order;       // [D] path ids in lexicographic order
   uint32_t *order_tmp;   // [D]
-  uint32_t *lcp;         // [D+1] lcp with the previous path in order; lcp[D] = 0
+  uint32_t *lcp;         // [D+1] lcp with the previous path in order; lcp[D] = 0 (room for a multiple of 16)
   uint64_t *scan_in;     // [D][1+m] new-node counts and sums in order
   uint64_t *scan_out;    // [D+1][1+m] exclusive prefix sums (+ totals at row D)
-  uint64_t *scan_blk;    // block partials
-  int64_t scan_blocks;
-  uint32_t *sparse;      // [levels][D] range minima of lcp
-  int32_t levels;
+  uint64_t *scan_blk;    // [ceil(D / 1024)][1+m] sums of 1024 rows, zeroed before launch_canon
+  // minima of lcp: level 0 is lcp itself, an entry of level 1 covers 16 positions, an entry
+  // of every further level 64 of the one below (min_levels of them, until one group is
+  // left); every level padded to a multiple of 16 entries
+  uint32_t *mins[6];
+  int64_t min_n[6];
+  int32_t min_levels;
   uint32_t *chain_parent; // [D]
   uint32_t *win_path;    // [U_max / 64 + 1] path index (in order) holding each 64-node window's first node
   int64_t u_max;
@@ -279,7 +282,11 @@ constexpr int kTrieCtrFail = 4;
 // with `join` (two events of the caller's, unused when s2 is s).
 void launch_trie_sort(const TrieArgs &a, hipStream_t s, hipStream_t s2, hipEvent_t fork, hipEvent_t mid,
                       hipEvent_t join);
-void launch_canon(const CanonArgs &a, hipStream_t s);  // lcp, scans, sparse table, emission
+// Levels of the minima of n = D + 1 positions: their entries in min_n, the words of levels
+// 1 and up as the result, and set_min_levels points mins at them (level 0 at lcp).
+int64_t min_level_words(int64_t n, CanonArgs &a);
+void set_min_levels(CanonArgs &a, uint32_t *words);
+void launch_canon(const CanonArgs &a, hipStream_t s);  // lcp, sums, minima, emission
 
 struct alignas(32) PathRec {  // the path at a canonical position
   int64_t start;             // first frame in the store

@@ -630,14 +630,16 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
   }
   const int C = 1 + m;
   const int64_t n1 = D + 1;
-  const int levels = floor_log2((uint64_t)n1) + 1;
-  const int64_t nblk = (D + 1023) / 1024 + 1;
+  const int64_t nblk = (n1 + 1023) / 1024;
+  CanonArgs ca{};
+  const int64_t min_words = min_level_words(n1, ca);
   const int64_t u_max = sum_len + 1;
-  Buf order, order_tmp, lcp, scan_in, scan_out, scan_blk, sparse, chain, win_path, cursor;
+  const size_t ctl_bytes = 64 + nblk * C * 8;  // control words, then the sums of the scan's blocks
+  Buf order, order_tmp, lcp, scan_in, scan_out, mins, chain, win_path, cursor;
   Buf n_parent, n_frame, n_depth, n_subend, n_excl, n_incl;  // canonical arrays of the new tree
-  if (!order.alloc(dneed * 4) || !order_tmp.alloc(dneed * 4) || !lcp.alloc(n1 * 4) || !scan_in.alloc(dneed * C * 8) ||
-      !scan_out.alloc(n1 * C * 8) || !scan_blk.alloc(nblk * C * 8) || !sparse.alloc((int64_t)levels * n1 * 4) ||
-      !chain.alloc(dneed * 4) || !win_path.alloc((u_max / 64 + 2) * 4) || !cursor.alloc(64) || !n_parent.alloc(u_max * 4) || !n_subend.alloc(u_max * 4) ||
+  if (!order.alloc(dneed * 4) || !order_tmp.alloc(dneed * 4) || !lcp.alloc((n1 + 15) / 16 * 64) || !scan_in.alloc(dneed * C * 8) ||
+      !scan_out.alloc(n1 * C * 8) || !mins.alloc(min_words * 4) ||
+      !chain.alloc(dneed * 4) || !win_path.alloc((u_max / 64 + 2) * 4) || !cursor.alloc(ctl_bytes) || !n_parent.alloc(u_max * 4) || !n_subend.alloc(u_max * 4) ||
       !n_frame.alloc(u_max * 4) || !n_depth.alloc(u_max * 4) || !n_excl.alloc(u_max * m * 8) ||
       !n_incl.alloc(u_max * m * 8))
     return undo(fail(CCT_ENOMEM, "device allocation failed"));
@@ -691,7 +693,7 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
 
   // ---- publish new paths ----------------------------------------------------------------
   Event trie_fork, trie_mid, trie_join;
-  AGG_TRY(hipMemsetAsync(cursor.p, 0, 64, s));
+  AGG_TRY(hipMemsetAsync(cursor.p, 0, ctl_bytes, s));
   if (n_new) {
     PublishArgs pa{};
     pa.off = p->offsets; pa.fr = p->frames; pa.n_frames = p->n_frames; pa.slot = t->slot.as<Slot>();
@@ -722,15 +724,14 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
   if (env_int("CCT_TEST_FAIL_AFTER_PUBLISH", 0)) return undo(fail(CCT_EDEVICE, "test failure after publish"));
 
   // ---- A5-A9: canonical order and node arrays ------------------------------------------
-  CanonArgs ca{};
   ca.d = D; ca.m = m; ca.exact = exact_sort ? 1 : 0;
   ca.pframes = t->pframes.as<uint32_t>(); ca.pcp = t->pcp.as<uint64_t>(); ca.pstart = t->pstart.as<int64_t>();
   ca.plen = t->plen.as<uint32_t>(); ca.psums = nsums.as<uint64_t>();
   ca.d_old = t->d; ca.pslot = t->pslot.as<uint32_t>(); ca.delta = delta.as<uint64_t>();
   ca.old_sums = t->psums.as<uint64_t>();
   ca.order = order.as<uint32_t>(); ca.order_tmp = order_tmp.as<uint32_t>(); ca.lcp = lcp.as<uint32_t>();
-  ca.scan_in = scan_in.as<uint64_t>(); ca.scan_out = scan_out.as<uint64_t>(); ca.scan_blk = scan_blk.as<uint64_t>();
-  ca.scan_blocks = nblk; ca.sparse = sparse.as<uint32_t>(); ca.levels = levels;
+  ca.scan_in = scan_in.as<uint64_t>(); ca.scan_out = scan_out.as<uint64_t>(); ca.scan_blk = cursor.as<uint64_t>() + 8;
+  set_min_levels(ca, mins.as<uint32_t>());
   ca.chain_parent = chain.as<uint32_t>(); ca.win_path = win_path.as<uint32_t>(); ca.u_max = u_max;
   ca.parent = n_parent.as<uint32_t>(); ca.frame = n_frame.as<uint32_t>(); ca.depth = n_depth.as<uint32_t>();
   ca.subend = n_subend.as<uint32_t>();
@@ -761,7 +762,7 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
     if (mode == 2) return undo(fail(CCT_EDEVICE, "canonical order failed exact verification"));
     if (mode == 0 && env_int("CCT_TEST_REQUIRE_TRIE", 0)) return undo(fail(CCT_EDEVICE, "block-trie order not usable"));
     mode = 2;  // a hash collision misled the fast order: sort again with exact compares
-    AGG_TRY(hipMemsetAsync(cursor.as<unsigned long long>() + 2, 0, 16, s));
+    AGG_TRY(hipMemsetAsync(cursor.p, 0, ctl_bytes, s));
   }
   tm.collect(N > 0);
   if (keep_stats && ts.ok) g_stats_ms = ts.span(0, 1);

@@ -245,13 +245,13 @@ static_assert(kLcpPer % 16 == 0, "whole entries of level 1 of the minima per wor
 
 // lcp of position i (every lane of the position's group gets it); u_out[1] if the two paths
 // are not strictly increasing
-__device__ inline uint32_t lcp_at(const CanonArgs &a, int64_t i, uint32_t p, uint32_t len, int lane) {
+__device__ inline uint32_t lcp_at(const CanonArgs &a, int64_t i, uint32_t p, uint32_t len, int64_t start, int lane) {
   const int g = lane % kLcpLanes;
   if (i == 0) return 0;
   uint32_t q = a.order[i - 1];
   if (q >= (uint64_t)a.d) q = 0;
   const uint32_t lq = a.plen[q], n = min(lq, len);
-  const uint32_t *pq = a.pframes + a.pstart[q], *pp = a.pframes + a.pstart[p];
+  const uint32_t *pq = a.pframes + a.pstart[q], *pp = a.pframes + start;
   bool less = lq < len;  // the order of the two if they agree on n frames
   uint32_t l = n;
   bool done = false;
@@ -299,6 +299,7 @@ __global__ __launch_bounds__(256) void lcp_kernel(CanonArgs a) {
   for (int64_t i0 = (int64_t)blockIdx.x * kLcpPer; i0 <= a.d; i0 += (int64_t)gridDim.x * kLcpPer) {
     const int64_t i = i0 + r;
     uint32_t l = kInf;  // (past the last position)
+    CanonRec rc{};
     if (i == a.d) l = 0;
     if (i < a.d) {
       // an order from a misleading hash may hold entries that are not path ids: they raise
@@ -307,7 +308,10 @@ __global__ __launch_bounds__(256) void lcp_kernel(CanonArgs a) {
       const bool bad = p >= (uint64_t)a.d;
       if (bad) p = 0;
       const uint32_t len = a.plen[p], sl = a.pslot[p];
-      l = lcp_at(a, i, p, len, lane);
+      rc.start = a.pstart[p];
+      l = lcp_at(a, i, p, len, rc.start, lane);
+      rc.len = len;
+      rc.lcp = l;
       if (bad && g == 0) {
         atomicOr(&a.u_out[1], 1ull);
         a.order[i] = 0;
@@ -331,6 +335,7 @@ __global__ __launch_bounds__(256) void lcp_kernel(CanonArgs a) {
     if (g == 0) {
       ls[r] = l;
       if (i <= a.d) a.lcp[i] = l;
+      if (i < a.d) a.rec[i] = rc;
     }
     __syncthreads();
     if ((int)threadIdx.x < C) {
@@ -607,7 +612,7 @@ __global__ void chain_kernel(CanonArgs a) {
   }
   a.chain_parent[i] = par;
   const uint64_t b = node_base(a, i);
-  const uint32_t cnt = a.plen[a.order[i]] - L;
+  const uint32_t cnt = a.rec[i].len - L;
   if (b + cnt > (uint64_t)a.u_max) {
     atomicOr(&a.u_out[1], 1ull);
     return;
@@ -619,20 +624,25 @@ __global__ void chain_kernel(CanonArgs a) {
   for (uint64_t w = (b + 63) / 64; w <= (b + cnt - 1) / 64; ++w) a.win_path[w] = (uint32_t)i;
 }
 
-// Waves: waves per SIMD the registers leave room for.  The kernel waits for chains of
-// dependent loads, so up to 4 metrics it is held to 64 VGPRs for 8 waves (4,222,948 nodes
-// of 2 metrics: 111 us at 73 VGPRs, 101 us at 64 with a few spills); from 5 metrics on
-// its LDS rows allow 4 or 5 waves anyway (4,000,380 nodes of 8 metrics: 172 us, 177 at 64
-// VGPRs).
-template <int Waves>
-__global__ __launch_bounds__(256, Waves) void emit_kernel(CanonArgs a) {
-  // a wave's 64 consecutive nodes stage their excl and incl rows in LDS ([2][256][m]
-  // words), then write each array's 64 m words as one contiguous stretch
-  extern __shared__ uint64_t emit_stage[];
+// One wave per window of 64 consecutive nodes.  The kernel is a chain of dependent loads
+// (window's first path, bases of its 64 paths, a path's record, frame, end of the subtree,
+// sums at the end), so the next window's first two are requested a window ahead, a path's
+// fields come from one 16-byte record, and the M sums of a row are requested together (M is
+// a template parameter).  7 waves per SIMD (72 VGPRs; 64 for 8 waves spill, 1 to 9 us
+// slower); from 5 metrics on the LDS rows allow 5.  The node arrays are written with
+// non-temporal stores: nothing here reads them, and what they would evict from the caches
+// is read (this kernel's rows, the next call's frames).  4,222,948 nodes of 2 metrics 114
+// -> 81 us (2.5 TB/s of arrays written), 4.57 million of 4 metrics 149 -> 107 us (3.4), 4.0
+// million of 8 metrics 166 -> 95 us (6.1).
+template <int M>
+__global__ __launch_bounds__(256, M <= 4 ? 7 : 5) void emit_kernel(CanonArgs a) {
+  // a wave's 64 consecutive nodes stage their excl and incl rows in LDS, then write each
+  // array's 64 M words as one contiguous stretch
+  constexpr int C = 1 + M;
+  __shared__ uint64_t stage[2][256 * M];
   __shared__ uint32_t emit_mark[256];  // per wave: window position -> path offset
-  const int C = 1 + a.m, m = a.m;
-  const int lane = threadIdx.x & 63, w0 = threadIdx.x - lane;
-  uint64_t *sx = emit_stage + (int64_t)w0 * m, *si = emit_stage + (int64_t)(256 + w0) * m;
+  const int lane = threadIdx.x & 63, w0 = __builtin_amdgcn_readfirstlane(threadIdx.x - lane);
+  uint64_t *sx = stage[0] + w0 * M, *si = stage[1] + w0 * M;
   // (bounded by u_max, as in chain_kernel: past it the order is not a permutation)
   const int64_t U_all = (int64_t)(1 + a.scan_out[a.d * C]);
   const int64_t U = U_all < a.u_max ? U_all : a.u_max;
@@ -640,24 +650,36 @@ __global__ __launch_bounds__(256, Waves) void emit_kernel(CanonArgs a) {
     a.u_out[0] = (unsigned long long)U;
     if (U_all > a.u_max) atomicOr(&a.u_out[1], 1ull);
   }
-  uint32_t *mark = emit_mark + (w0 >> 6) * 64;
+  uint32_t *mark = emit_mark + w0;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t base = (int64_t)blockIdx.x * blockDim.x + w0; base < U; base += stride) {
-    const int64_t u = base + lane;
+  const uint32_t d = (uint32_t)a.d;
+  // (positions and node ids fit 32 bits; a wave's window and its first path are uniform)
+  // first path of the window at `base` (window 0 holds only the root when there is no other
+  // node: no path to look up), and the first node of path i
+  auto window_path = [&](int64_t base) -> uint32_t {
+    return __builtin_amdgcn_readfirstlane(base < U && (base > 0 || U > 1) ? a.win_path[base >> 6] : 0u);
+  };
+  auto first_node = [&](uint32_t i) -> uint32_t {
+    return i < d ? 1 + (uint32_t)a.scan_out[(uint64_t)i * C] : kInf;
+  };
+  int64_t base = (int64_t)blockIdx.x * blockDim.x + w0;
+  uint32_t i0 = window_path(base);
+  uint32_t nb = first_node(i0 + lane);
+  for (; base < U; base += stride) {
+    const uint32_t b0 = (uint32_t)base, u = b0 + lane;
+    const uint32_t i0_next = window_path(base + stride);
     // this window's paths: the one holding its first node and the 63 after it (every
     // path past the first has at least one node, so they cover the window); a node's
     // path is the last of them whose first node is at or before it
-    // (window 0 holds only the root when there is no other node: no path to look up)
-    int64_t i0 = (base > 0 || U > 1) ? (int64_t)a.win_path[base >> 6] : 0;
-    if (i0 >= a.d && (base > 0 || U > 1)) {  // a window chain_kernel did not write (the order is not a permutation)
+    if (i0 >= d && (base > 0 || U > 1)) {  // a window chain_kernel did not write (the order is not a permutation)
       if (lane == 0) atomicOr(&a.u_out[1], 1ull);
       i0 = 0;
+      nb = first_node(lane);
     }
-    const uint64_t nb = i0 + lane < a.d ? node_base(a, i0 + lane) : ~0ull;
     mark[lane] = 0;
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_wave_barrier();
-    if (lane > 0 && nb >= (uint64_t)base && nb < (uint64_t)base + 64) mark[nb - base] = (uint32_t)lane;
+    if (lane > 0 && nb >= b0 && nb - b0 < 64) mark[nb - b0] = (uint32_t)lane;
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_wave_barrier();
     uint32_t off = mark[lane];
@@ -666,55 +688,74 @@ __global__ __launch_bounds__(256, Waves) void emit_kernel(CanonArgs a) {
       const uint32_t y = __shfl_up(off, o, 64);
       if (lane >= o) off = max(off, y);
     }
-    const uint64_t bnode = ((uint64_t)__shfl((uint32_t)(nb >> 32), (int)off, 64) << 32) | __shfl((uint32_t)nb, (int)off, 64);
+    uint32_t b = __shfl(nb, (int)off, 64);
+    const uint32_t nb_next = first_node(i0_next + lane);
     if (u == 0) {
       a.parent[0] = kInf;
       a.frame[0] = 0;
       a.depth[0] = 0;
       a.subend[0] = (uint32_t)U;
-      const bool empty_path = a.d > 0 && a.plen[a.order[0]] == 0;
-      for (int j = 0; j < m; ++j) {
+      const bool empty_path = d > 0 && a.rec[0].len == 0;
+      for (int j = 0; j < M; ++j) {
         sx[j] = empty_path ? a.scan_out[C + 1 + j] : 0;
         si[j] = a.scan_out[a.d * C + 1 + j];
       }
-    } else if (u < U) {
-      int64_t i = i0 + (int64_t)off;
-      uint64_t b = bnode;
-      if (i >= a.d || b > (uint64_t)u) {  // (only when the order is not a permutation)
+    } else if (base + lane < U) {
+      uint32_t i = i0 + off;
+      if (i >= d || b > u) {  // (only when the order is not a permutation)
         atomicOr(&a.u_out[1], 1ull);
         i = 0;
-        b = node_base(a, 0);
+        b = first_node(0);
       }
-      const uint32_t pid = a.order[i];
-      const uint32_t L = a.lcp[i], len = a.plen[pid];
-      uint32_t l = L + 1 + (uint32_t)(u - b);
-      if (l > len || (uint64_t)u - b >= (uint64_t)len) {  // (only when the order is not a permutation)
+      const CanonRec rc = a.rec[i];
+      const uint32_t after = a.lcp[i + 1];
+      uint32_t l = rc.lcp + 1 + (u - b);
+      if (l > rc.len || u - b >= rc.len) {  // (only when the order is not a permutation)
         atomicOr(&a.u_out[1], 1ull);
-        l = len;
+        l = rc.len;
       }
-      a.parent[u] = u == (int64_t)b ? a.chain_parent[i] : (uint32_t)(u - 1);
-      a.frame[u] = l ? a.pframes[a.pstart[pid] + l - 1] : 0u;
-      a.depth[u] = l;
-      const int64_t e = (i + 1 == a.d || l > a.lcp[i + 1]) ? i + 1 : next_smaller(a, i + 2, l);
+      const uint32_t fr = l ? a.pframes[rc.start + l - 1] : 0u;
+      __builtin_nontemporal_store(u == b ? a.chain_parent[i] : u - 1, &a.parent[u]);
+      __builtin_nontemporal_store(l, &a.depth[u]);
+      const uint32_t e = i + 1 == d || l > after ? i + 1 : next_smaller(a, i + 2, l);
+      __builtin_nontemporal_store(fr, &a.frame[u]);
       // the subtree is the paths i .. e-1 below depth l: ids up to the first node of path e
-      a.subend[u] = (uint32_t)node_base(a, e);
-      const uint64_t *pi = a.scan_out + i * C, *pe = a.scan_out + e * C;
-      for (int j = 0; j < m; ++j) {
-        sx[lane * m + j] = l == len ? pi[C + 1 + j] - pi[1 + j] : 0;  // the path's own sums
-        si[lane * m + j] = pe[1 + j] - pi[1 + j];
+      const uint64_t *pi = a.scan_out + (uint64_t)i * C, *pe = a.scan_out + (uint64_t)e * C;
+      __builtin_nontemporal_store((uint32_t)(1 + (uint32_t)pe[0]), &a.subend[u]);
+      uint64_t from[M], to[M];  // the sums of the paths before i, before e
+#pragma unroll
+      for (int j = 0; j < M; ++j) {
+        from[j] = pi[1 + j];
+        to[j] = pe[1 + j];
       }
+#pragma unroll
+      for (int j = 0; j < M; ++j) si[lane * M + j] = to[j] - from[j];
+      // the path's own sums at its last node (mostly the row just read: a path's last node
+      // is most often a leaf)
+      if (l == rc.len && e != i + 1) {
+#pragma unroll
+        for (int j = 0; j < M; ++j) to[j] = pi[C + 1 + j];
+      }
+#pragma unroll
+      for (int j = 0; j < M; ++j) sx[lane * M + j] = l == rc.len ? to[j] - from[j] : 0;
     }
     // every lane's LDS writes before any lane's reads
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_wave_barrier();
-    const int64_t words = (U - base < 64 ? U - base : 64) * m;
-    for (int64_t k = lane; k < words; k += 64) {
-      a.excl[base * m + k] = sx[k];
-      a.incl[base * m + k] = si[k];
+    const int words = (int)(U - base < 64 ? U - base : 64) * M;
+#pragma unroll
+    for (int q = 0; q < M; ++q) {
+      const int k = 64 * q + lane;
+      if (k < words) {
+        __builtin_nontemporal_store(sx[k], &a.excl[base * M + k]);
+        __builtin_nontemporal_store(si[k], &a.incl[base * M + k]);
+      }
     }
     // every lane's reads before the next nodes' writes
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_wave_barrier();
+    i0 = i0_next;
+    nb = nb_next;
   }
 }
 
@@ -803,9 +844,16 @@ void launch_canon(const CanonArgs &a, hipStream_t s) {
   // few blocks: the columns side by side as well (each then reads the rows for itself)
   hipLaunchKernelGGL(canon_scan_kernel, dim3((unsigned)nblk, nblk <= 256 ? C : 1), dim3(256), 0, s, a, direct);
   if (a.d > 0) hipLaunchKernelGGL(chain_kernel, dim3(blocks_for(a.d, 256)), dim3(256), 0, s, a);
-  const size_t stage = (size_t)2 * 256 * a.m * 8;
-  if (a.m <= 4) hipLaunchKernelGGL(emit_kernel<8>, dim3(a.grid_nodes), dim3(256), stage, s, a);
-  else hipLaunchKernelGGL(emit_kernel<4>, dim3(a.grid_nodes), dim3(256), stage, s, a);
+  switch (a.m) {
+#define CCT_EMIT_CASE(M)                                                                      \
+  case M:                                                                                     \
+    hipLaunchKernelGGL(emit_kernel<M>, dim3(a.grid_nodes), dim3(256), 0, s, a);               \
+    break;
+    CCT_EMIT_CASE(1) CCT_EMIT_CASE(2) CCT_EMIT_CASE(3) CCT_EMIT_CASE(4)
+    CCT_EMIT_CASE(5) CCT_EMIT_CASE(6) CCT_EMIT_CASE(7) CCT_EMIT_CASE(8)
+#undef CCT_EMIT_CASE
+    default: break;
+  }
 }
 
 }  // namespace cct

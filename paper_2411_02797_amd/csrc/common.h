@@ -187,6 +187,10 @@ void launch_unclaim(Slot *slot, uint64_t cap, hipStream_t s);
 void launch_rehash(const uint32_t *pframes, const int64_t *pstart, const uint32_t *plen, int64_t d,
                    Slot *slot, uint64_t cap_mask, uint64_t hash_mask, uint32_t *pslot, hipStream_t s);
 
+struct alignas(16) CanonRec {  // the path at a canonical position
+  int64_t start;         // first frame in the store
+  uint32_t len, lcp;     // length, LCP with the path before it
+};
 struct CanonArgs {
   int64_t d;             // number of distinct full paths
   int64_t id0;           // launch_sort: sorts path ids id0 .. id0 + d - 1 (0 for a full sort)
@@ -208,6 +212,7 @@ struct CanonArgs {
   uint32_t *order;       // [D] path ids in lexicographic order
   uint32_t *order_tmp;   // [D]
   uint32_t *lcp;         // [D+1] lcp with the previous path in order; lcp[D] = 0 (room for a multiple of 16)
+  CanonRec *rec;         // [D]
   uint64_t *scan_in;     // [D][1+m] new-node counts and sums in order
   uint64_t *scan_out;    // [D+1][1+m] exclusive prefix sums (+ totals at row D)
   uint64_t *scan_blk;    // [ceil(D / 1024)][1+m] sums of 1024 rows, zeroed before launch_canon

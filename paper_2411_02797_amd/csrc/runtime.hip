@@ -635,10 +635,10 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
   const int64_t min_words = min_level_words(n1, ca);
   const int64_t u_max = sum_len + 1;
   const size_t ctl_bytes = 64 + nblk * C * 8;  // control words, then the sums of the scan's blocks
-  Buf order, order_tmp, lcp, scan_in, scan_out, mins, chain, win_path, cursor;
+  Buf order, order_tmp, lcp, scan_in, scan_out, mins, recs, chain, win_path, cursor;
   Buf n_parent, n_frame, n_depth, n_subend, n_excl, n_incl;  // canonical arrays of the new tree
   if (!order.alloc(dneed * 4) || !order_tmp.alloc(dneed * 4) || !lcp.alloc((n1 + 15) / 16 * 64) || !scan_in.alloc(dneed * C * 8) ||
-      !scan_out.alloc(n1 * C * 8) || !mins.alloc(min_words * 4) ||
+      !scan_out.alloc(n1 * C * 8) || !mins.alloc(min_words * 4) || !recs.alloc(dneed * sizeof(CanonRec)) ||
       !chain.alloc(dneed * 4) || !win_path.alloc((u_max / 64 + 2) * 4) || !cursor.alloc(ctl_bytes) || !n_parent.alloc(u_max * 4) || !n_subend.alloc(u_max * 4) ||
       !n_frame.alloc(u_max * 4) || !n_depth.alloc(u_max * 4) || !n_excl.alloc(u_max * m * 8) ||
       !n_incl.alloc(u_max * m * 8))
@@ -732,12 +732,13 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
   ca.order = order.as<uint32_t>(); ca.order_tmp = order_tmp.as<uint32_t>(); ca.lcp = lcp.as<uint32_t>();
   ca.scan_in = scan_in.as<uint64_t>(); ca.scan_out = scan_out.as<uint64_t>(); ca.scan_blk = cursor.as<uint64_t>() + 8;
   set_min_levels(ca, mins.as<uint32_t>());
+  ca.rec = recs.as<CanonRec>();
   ca.chain_parent = chain.as<uint32_t>(); ca.win_path = win_path.as<uint32_t>(); ca.u_max = u_max;
   ca.parent = n_parent.as<uint32_t>(); ca.frame = n_frame.as<uint32_t>(); ca.depth = n_depth.as<uint32_t>();
   ca.subend = n_subend.as<uint32_t>();
   ca.excl = n_excl.as<uint64_t>(); ca.incl = n_incl.as<uint64_t>();
   ca.u_out = cursor.as<unsigned long long>() + 2;
-  ca.grid_nodes = (int)std::max<int64_t>(1, std::min<int64_t>((u_max + 255) / 256, (int64_t)cu_count() * 16));
+  ca.grid_nodes = (int)std::max<int64_t>(1, std::min<int64_t>((u_max + 255) / 256, (int64_t)cu_count() * 64));
   // 0: block trie, 1: comparison sort with checkpoint hashes, 2: exact comparisons only,
   // 3: the previous order with this call's new paths merged in
   for (int mode = incremental ? 3 : (use_trie ? 0 : (ca.exact ? 2 : 1));;) {

@@ -30,7 +30,6 @@ namespace cct {
 namespace {
 
 constexpr uint32_t kInf = 0xFFFFFFFFu;
-constexpr int kSortBlock = 1024;   // keys per block-local bitonic sort
 constexpr int kMergeItems = 8;     // outputs per thread per merge pass
 constexpr int kScanRows = 1024;    // rows per scan block
 
@@ -110,35 +109,113 @@ __device__ inline bool key_less(const CanonArgs &a, uint32_t x, uint32_t y) {
 }
 
 // ---- sort -------------------------------------------------------------------------
-// Block-local bitonic sort.  A merge's new paths carry their gap beside the key in LDS,
-// so pairs in different gaps are ordered without a global load; only pairs in one gap
-// compare paths.
+// Block-local bitonic sort by path.
 __global__ __launch_bounds__(512) void sort_block_kernel(CanonArgs a, uint32_t *out) {
   __shared__ uint32_t key[kSortBlock];
-  __shared__ uint32_t kgap[kSortBlock];
   const int tid = threadIdx.x;
   const int64_t base = (int64_t)blockIdx.x * kSortBlock;
-  for (int i = tid; i < kSortBlock; i += 512) {
-    const bool in = base + i < a.d;
-    key[i] = in ? (uint32_t)(a.id0 + base + i) : kInf;
-    kgap[i] = in && a.gap ? a.gap[base + i] : 0u;
-  }
+  for (int i = tid; i < kSortBlock; i += 512) key[i] = base + i < a.d ? (uint32_t)(a.id0 + base + i) : kInf;
   __syncthreads();
   for (int k = 2; k <= kSortBlock; k <<= 1) {
     for (int j = k >> 1; j > 0; j >>= 1) {
       const int i = 2 * j * (tid / j) + (tid % j), l = i + j;
-      const uint32_t x = key[i], y = key[l], gx = kgap[i], gy = kgap[l];
+      const uint32_t x = key[i], y = key[l];
       // ascending where (i & k) == 0: swap if y < x; else swap if x < y
       const bool up = (i & k) == 0;
-      const uint32_t p = up ? y : x, q = up ? x : y, gp = up ? gy : gx, gq = up ? gx : gy;
-      const bool swap = p != kInf && (q == kInf || (gp != gq ? gp < gq : path_less(a, p, q)));
+      const bool swap = path_less(a, up ? y : x, up ? x : y);
       __syncthreads();
-      if (swap) { key[i] = y; key[l] = x; kgap[i] = gy; kgap[l] = gx; }
+      if (swap) { key[i] = y; key[l] = x; }
       __syncthreads();
     }
   }
   for (int i = tid; i < kSortBlock; i += 512)
     if (base + i < a.d) out[base + i] = key[i];
+}
+
+// Block-local order of a merge's new paths by (gap, path): sixteen lanes share a path and
+// count the block's paths before it, four gaps per load; the paths themselves are compared
+// only within a gap.  The counts need no barrier and no second pass, so a block of 1024
+// takes a few round trips: 10 us, where a bitonic sort took 40 us comparing paths in every
+// step, and 26 us ordering the gaps first (55 steps on one CU).  With one block (place), the
+// paths go straight to their place in the new order.
+constexpr int kNewLanes = 16;
+__global__ __launch_bounds__(256) void sort_new_kernel(CanonArgs a, uint32_t *out, uint32_t *gsorted,
+                                                       uint32_t *place) {
+  const int g = threadIdx.x % kNewLanes;
+  const int64_t j = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kNewLanes;
+  if (j >= a.d) return;
+  const int64_t base = j / kSortBlock * kSortBlock;
+  const int n = (int)(a.d - base < kSortBlock ? a.d - base : kSortBlock), own = (int)(j - base);
+  const uint32_t x = (uint32_t)(a.id0 + j), gx = a.gap[j];
+  uint32_t before = 0;
+  for (int k0 = 4 * g; k0 < n; k0 += 4 * kNewLanes) {
+    const u32x4 v = ld4(a.gap + base + k0);  // (the array is padded to whole blocks)
+    uint32_t tie = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const bool in = k0 + e < n && k0 + e != own;
+      before += in && v[e] < gx;
+      tie |= in && v[e] == gx ? 1u << e : 0u;
+    }
+    for (; tie; tie &= tie - 1)
+      before += path_less(a, (uint32_t)(a.id0 + base + k0 + __builtin_ctz(tie)), x);
+  }
+#pragma unroll
+  for (int o = kNewLanes / 2; o > 0; o >>= 1) before += __shfl_xor(before, o, 64);
+  if (g != 0) return;
+  gsorted[base + before] = gx;
+  if (place) {
+    place[gx + before] = x;
+    a.lcp[gx + before] = kInf;  // not known yet
+  } else {
+    out[base + before] = x;
+  }
+}
+
+// The sorted blocks of a merge's new paths (ids, gaps bgap) into one order: a path's rank is
+// its position in its block plus, for every other block, the paths there before it, found by
+// binary search.  Sixteen lanes share a path, a block each: the search by gap needs 4-byte
+// loads only; where the block holds paths in the same gap, a second one compares paths.
+// Every block costs each path the same searches, so past kRankBlocks the merge passes, which
+// grow with the logarithm of the number of blocks, are used instead.
+constexpr int64_t kRankBlocks = 64;
+__global__ __launch_bounds__(256) void rank_new_kernel(CanonArgs a, const uint32_t *ids, const uint32_t *bgap,
+                                                       uint32_t *gsorted, uint32_t *place) {
+  const int g = threadIdx.x % kNewLanes;
+  const int64_t j = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kNewLanes;
+  if (j >= a.d) return;
+  const uint32_t x = ids[j], gx = bgap[j];
+  const int64_t own = j / kSortBlock, nb = (a.d + kSortBlock - 1) / kSortBlock;
+  uint32_t before = g == 0 ? (uint32_t)(j - own * kSortBlock) : 0u;
+  for (int64_t b = g; b < nb; b += kNewLanes) {
+    if (b == own) continue;
+    const uint32_t *gb = bgap + b * kSortBlock, *ib = ids + b * kSortBlock;
+    const int n = (int)(a.d - b * kSortBlock < kSortBlock ? a.d - b * kSortBlock : kSortBlock);
+    int lo = 0, hi = n;  // first path of the block with a gap >= gx
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (gb[mid] < gx) lo = mid + 1; else hi = mid;
+    }
+    if (lo < n && gb[lo] == gx) {
+      int end = n, from = lo;  // its paths in gap gx: [lo, end)
+      while (from < end) {
+        const int mid = (from + end) >> 1;
+        if (gb[mid] <= gx) from = mid + 1; else end = mid;
+      }
+      while (lo < end) {
+        const int mid = (lo + end) >> 1;
+        if (path_less(a, ib[mid], x)) lo = mid + 1; else end = mid;
+      }
+    }
+    before += (uint32_t)lo;
+  }
+#pragma unroll
+  for (int o = kNewLanes / 2; o > 0; o >>= 1) before += __shfl_xor(before, o, 64);
+  if (g == 0) {
+    gsorted[before] = gx;
+    place[gx + before] = x;
+    a.lcp[gx + before] = kInf;  // not known yet
+  }
 }
 
 __global__ __launch_bounds__(256) void merge_pass_kernel(CanonArgs a, const uint32_t *src, uint32_t *dst,
@@ -172,7 +249,8 @@ __global__ __launch_bounds__(256) void merge_pass_kernel(CanonArgs a, const uint
 // answer takes about log_17(d_old) rounds of path comparisons instead of log_2(d_old)
 // (each comparison is a chain of dependent loads).
 constexpr int kGapLanes = 16;
-__global__ __launch_bounds__(256) void gap_kernel(CanonArgs a, const uint32_t *old_order, int64_t d_old, uint32_t *gap) {
+__global__ __launch_bounds__(256) void gap_kernel(CanonArgs a, const uint32_t *old_order, int64_t d_old, uint32_t *gap,
+                                                  uint32_t *ids, uint32_t *bgap, uint32_t *gsorted) {
   const int lane = threadIdx.x & 63, g = lane % kGapLanes, g0 = lane - g;
   const int64_t j = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kGapLanes;
   const bool active = j < a.d - d_old;
@@ -201,24 +279,38 @@ __global__ __launch_bounds__(256) void gap_kernel(CanonArgs a, const uint32_t *o
       }
     }
   }
-  if (active && g == 0) gap[j] = (uint32_t)lo;
+  if (active && g == 0) {
+    gap[j] = (uint32_t)lo;
+    // a hash collision can make two paths claim one place of an order below: the place no
+    // path claims then still holds a path and its gap in a block's order, and is found
+    // unclaimed in the whole one (place_old_kernel)
+    ids[j] = x;
+    bgap[j] = (uint32_t)lo;
+    gsorted[j] = kInf;
+  }
 }
 
 // Placement: the r-th new path (sorted by gap, then path) goes after its gap's old
 // paths and the r new paths before it; old path i goes after the new paths whose
-// gap is <= i.
+// gap is <= i.  Where no new path comes between old paths i - 1 and i, their LCP is the one
+// the tree keeps (lcp: kInf elsewhere): only pairs with a new path are compared again.
 __global__ __launch_bounds__(256) void place_new_kernel(const uint32_t *B, int64_t n_new, int64_t d_old,
-                                                        const uint32_t *gap, uint32_t *gsorted, uint32_t *dst) {
+                                                        const uint32_t *gap, uint32_t *gsorted, uint32_t *dst, uint32_t *lcp) {
   const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (r >= n_new) return;
   const uint32_t x = B[r];
   const uint32_t g = gap[x - d_old];
   gsorted[r] = g;
   dst[g + r] = x;
+  lcp[g + r] = kInf;  // not known yet
 }
 __global__ __launch_bounds__(256) void place_old_kernel(const uint32_t *A, int64_t d_old, const uint32_t *gsorted,
-                                                        int64_t n_new, uint32_t *dst) {
+                                                        int64_t n_new, const uint32_t *old_lcp, uint32_t *dst,
+                                                        uint32_t *lcp, unsigned long long *u_out) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  // a rank no path took (two took another one, after a hash collision): the order has a
+  // hole there, and the host sorts again by exact comparisons
+  if (i < n_new && gsorted[i] == kInf) atomicOr(&u_out[1], 1ull);
   if (i >= d_old) return;
   int64_t lo = 0, hi = n_new;  // new paths with gap <= i
   while (lo < hi) {
@@ -226,8 +318,8 @@ __global__ __launch_bounds__(256) void place_old_kernel(const uint32_t *A, int64
     if ((int64_t)gsorted[mid] <= i) lo = mid + 1; else hi = mid;
   }
   dst[i + lo] = A[i];
+  lcp[i + lo] = i > 0 && !(lo > 0 && (int64_t)gsorted[lo - 1] == i) ? old_lcp[i] : kInf;
 }
-
 // ---- exact verification, lcp, sums, scan rows ------------------------------------------------
 // Eight lanes per pair of neighbours: a step compares 64 frames of both, two 16-byte loads
 // per lane and path, and the first lane with a difference holds the LCP.  With one lane per
@@ -309,7 +401,8 @@ __global__ __launch_bounds__(256) void lcp_kernel(CanonArgs a) {
       if (bad) p = 0;
       const uint32_t len = a.plen[p], sl = a.pslot[p];
       rc.start = a.pstart[p];
-      l = lcp_at(a, i, p, len, rc.start, lane);
+      l = a.lcp_known ? a.lcp[i] : kInf;
+      if (l > len) l = lcp_at(a, i, p, len, rc.start, lane);
       rc.len = len;
       rc.lcp = l;
       if (bad && g == 0) {
@@ -763,40 +856,62 @@ inline unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1)
 
 }  // namespace
 
-void launch_sort(CanonArgs &a, hipStream_t s) {
-  if (a.d <= 0) return;
-  uint32_t *src = a.order, *dst = a.order_tmp;
-  hipLaunchKernelGGL(sort_block_kernel, dim3(blocks_for(a.d, kSortBlock)), dim3(512), 0, s, a, src);
+namespace {
+// merge passes over blocks of kSortBlock sorted ids: the sorted list, in one of the buffers
+uint32_t *merge_blocks(const CanonArgs &a, uint32_t *src, uint32_t *dst, hipStream_t s) {
   for (int64_t run = kSortBlock; run < a.d; run *= 2) {
     hipLaunchKernelGGL(merge_pass_kernel, dim3(blocks_for((a.d + kMergeItems - 1) / kMergeItems, 256)), dim3(256),
                        0, s, a, src, dst, run);
     uint32_t *t = src; src = dst; dst = t;
   }
-  a.order = src;
-  a.order_tmp = dst;
+  return src;
+}
+}  // namespace
+
+void launch_sort(CanonArgs &a, hipStream_t s) {
+  if (a.d <= 0) return;
+  hipLaunchKernelGGL(sort_block_kernel, dim3(blocks_for(a.d, kSortBlock)), dim3(512), 0, s, a, a.order);
+  uint32_t *sorted = merge_blocks(a, a.order, a.order_tmp, s);
+  if (sorted != a.order) {
+    a.order_tmp = a.order;
+    a.order = sorted;
+  }
 }
 
-void launch_merge_order(CanonArgs &a, const uint32_t *old_order, int64_t d_old, uint32_t *scratch,
-                        hipStream_t s) {
+void launch_merge_order(CanonArgs &a, const uint32_t *old_order, const uint32_t *old_lcp, int64_t d_old,
+                        uint32_t *scratch, hipStream_t s) {
   const int64_t n_new = a.d - d_old;
-  uint32_t *gap = scratch, *gsorted = scratch + n_new;
-  const uint32_t *B = nullptr;
+  const int64_t room = (n_new + kSortBlock - 1) / kSortBlock * kSortBlock;
+  uint32_t *gap = scratch, *gsorted = scratch + room;
   uint32_t *dst = a.order;
+  a.lcp_known = 1;
   if (n_new > 0) {
-    hipLaunchKernelGGL(gap_kernel, dim3(blocks_for(n_new * kGapLanes, 256)), dim3(256), 0, s, a, old_order, d_old, gap);
-    CanonArgs r = a;
+    const int64_t nb = room / kSortBlock;
+    uint32_t *src = a.order, *tmp = a.order_tmp, *bgap = scratch + 2 * room;
+    hipLaunchKernelGGL(gap_kernel, dim3(blocks_for(n_new * kGapLanes, 256)), dim3(256), 0, s, a, old_order, d_old, gap,
+                       nb > 1 ? src : tmp, bgap, gsorted);
+    CanonArgs r = a;  // the new ids by (gap, path)
     r.d = n_new;
     r.id0 = d_old;
     r.gap = gap;
-    launch_sort(r, s);  // new ids by (gap, path), in r.order (one of the two buffers)
-    B = r.order;
-    dst = r.order_tmp;
-    hipLaunchKernelGGL(place_new_kernel, dim3(blocks_for(n_new, 256)), dim3(256), 0, s, B, n_new, d_old, gap,
-                       gsorted, dst);
+    hipLaunchKernelGGL(sort_new_kernel, dim3(blocks_for(n_new * kNewLanes, 256)), dim3(256), 0, s, r, src,
+                       nb > 1 ? bgap : gsorted, nb > 1 ? (uint32_t *)nullptr : dst);
+    if (nb > 1 && nb <= kRankBlocks) {
+      dst = tmp;
+      hipLaunchKernelGGL(rank_new_kernel, dim3(blocks_for(n_new * kNewLanes, 256)), dim3(256), 0, s, r, src, bgap,
+                         gsorted, dst);
+    } else if (nb > 1) {
+      // (a misleading hash can make these passes lose or repeat a path: every pair is
+      // compared again, nothing is taken as known)
+      a.lcp_known = 0;
+      uint32_t *sorted = merge_blocks(r, src, tmp, s);
+      dst = sorted == src ? tmp : src;
+      hipLaunchKernelGGL(place_new_kernel, dim3(blocks_for(n_new, 256)), dim3(256), 0, s, sorted, n_new, d_old, gap,
+                         gsorted, dst, a.lcp);
+    }
   }
-  if (d_old > 0)
-    hipLaunchKernelGGL(place_old_kernel, dim3(blocks_for(d_old, 256)), dim3(256), 0, s, old_order, d_old, gsorted,
-                       n_new, dst);
+  hipLaunchKernelGGL(place_old_kernel, dim3(blocks_for(std::max(d_old, n_new), 256)), dim3(256), 0, s, old_order,
+                     d_old, gsorted, n_new, old_lcp, dst, a.lcp, a.u_out);
   a.order_tmp = dst == a.order ? a.order_tmp : a.order;
   a.order = dst;
 }

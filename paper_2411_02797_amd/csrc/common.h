@@ -187,14 +187,18 @@ void launch_unclaim(Slot *slot, uint64_t cap, hipStream_t s);
 void launch_rehash(const uint32_t *pframes, const int64_t *pstart, const uint32_t *plen, int64_t d,
                    Slot *slot, uint64_t cap_mask, uint64_t hash_mask, uint32_t *pslot, hipStream_t s);
 
+constexpr int kSortBlock = 1024;   // paths per block-local sort
 struct alignas(16) CanonRec {  // the path at a canonical position
   int64_t start;         // first frame in the store
   uint32_t len, lcp;     // length, LCP with the path before it
 };
 struct CanonArgs {
   int64_t d;             // number of distinct full paths
-  int64_t id0;           // launch_sort: sorts path ids id0 .. id0 + d - 1 (0 for a full sort)
-  const uint32_t *gap;   // launch_sort with gap: orders by (gap[id - id0], path); else nullptr
+  // the sort kernels order path ids id0 .. id0 + d - 1 by path (0 for a full sort), or a
+  // merge's new ones by (gap[id - id0], path)
+  int64_t id0;
+  const uint32_t *gap;
+  int32_t lcp_known;     // launch_canon: lcp holds what launch_merge_order knows already, kInf elsewhere
   int32_t m;
   int32_t exact;         // 1: compare frames only (no checkpoint-hash shortcut)
   const uint32_t *pframes;
@@ -236,10 +240,11 @@ void launch_sort(CanonArgs &a, hipStream_t s);        // leaves the result in a.
 // Order after a merge: every path new in this call (ids d_old .. a.d - 1) finds its
 // gap in the previous order (d_old ids, sorted; the old paths keep their relative
 // order) by binary search, the new paths are sorted by (gap, path), and both lists
-// are placed by integer arithmetic.  scratch: 2 (a.d - d_old) words.  Leaves the
-// result in a.order.
-void launch_merge_order(CanonArgs &a, const uint32_t *old_order, int64_t d_old, uint32_t *scratch,
-                        hipStream_t s);
+// are placed by integer arithmetic; the LCPs of old neighbours that stay neighbours are
+// taken from old_lcp.  scratch: 3 words for every new path,
+// rounded up to a multiple of kSortBlock.  Leaves the result in a.order.
+void launch_merge_order(CanonArgs &a, const uint32_t *old_order, const uint32_t *old_lcp, int64_t d_old,
+                        uint32_t *scratch, hipStream_t s);
 
 // Lexicographic order of the D distinct paths through a trie of 16-frame blocks (see
 // trie.hip).  Scratch sizes: nblocks = store blocks in use (sum of ceil(len / 16)),

@@ -655,7 +655,7 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
   const bool incremental = t->d > 0 && t->order.p && !exact_sort && !env_int("CCT_TEST_FULL_SORT", 0);
   const bool use_trie = !incremental && !exact_sort && !env_int("CCT_TEST_MERGE_SORT", 0) && D > 0;
   Buf merge_scratch;
-  if (incremental && !merge_scratch.alloc(std::max<int64_t>(2 * (int64_t)n_new, 1) * 4))
+  if (incremental && !merge_scratch.alloc(3 * (((int64_t)n_new + kSortBlock - 1) / kSortBlock * kSortBlock) * 4))
     return undo(fail(CCT_ENOMEM, "device allocation failed"));
   Buf tr_key, tr_info, tr_bpos, tr_occ, tr_par, tr_cnt, tr_end, tr_hist, tr_gstart, tr_cidx, tr_rb, tr_lg, tr_spl, tr_bc, tr_grp, tr_grp2, tr_pos,
       tr_c, tr_cs, tr_blk, tr_lists, tr_ctr;
@@ -745,7 +745,7 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
     CanonArgs run = ca;
     run.exact = mode == 2 ? 1 : 0;
     if (mode == 0) launch_trie_sort(ta, s, side, trie_fork.ev, trie_mid.ev, trie_join.ev);
-    else if (mode == 3) launch_merge_order(run, t->order.as<uint32_t>(), t->d, merge_scratch.as<uint32_t>(), s);
+    else if (mode == 3) launch_merge_order(run, t->order.as<uint32_t>(), t->lcp.as<uint32_t>(), t->d, merge_scratch.as<uint32_t>(), s);
     else launch_sort(run, s);
     tm.mark(4, s);
     if (N > 0 && side != s) AGG_TRY(hipStreamWaitEvent(s, summed.ev, 0));  // launch_canon folds the sums

@@ -175,6 +175,8 @@ struct PublishArgs {
   int64_t store_used;        // frames already used in the store
   const uint64_t *starts;    // [n_new] place of each new path past store_used
   const int64_t *src_len;    // [n_new][2] first frame in the batch and length of each new path
+  uint64_t *bpos;            // block positions for the trie (see TrieArgs), or null
+  unsigned long long *empty; // set to 1 if the empty path is new (with bpos)
   uint64_t cp_mask;          // all ones, except under a test setting that forces collisions
 };
 void launch_publish(const PublishArgs &a, hipStream_t s);
@@ -258,40 +260,43 @@ struct TrieArgs {
   const int64_t *pstart;
   const uint32_t *plen;
   uint64_t *tkey;              // [cap] node keys (0: empty)
-  uint64_t *tinfo;             // [cap] (representative block << 32) | depth
+  uint32_t *tval;              // [cap] node id of each key: the store block that claimed it
+  uint32_t *count;             // [cap] distinct paths through each key's node
+  uint32_t *hist;              // [cap + 1] its children (entry cap: the root's)
   uint64_t *bpos;              // [nblocks] (path length << 32) | index of the block in its path
-  uint32_t *occ;               // [nblocks] node of each store block
-  uint32_t *nparent;           // [cap] parent node (cap: the root)
-  uint32_t *ncount;            // [cap] distinct paths through the node
-  uint32_t *nend;              // [cap + 1] a path ends at the node (cap: the root)
-  uint64_t *hist;              // [cap + 1] children per node
-  uint64_t *gstart;            // [cap + 2] exclusive prefix sums of hist
-  uint32_t *cidx;              // [cap] index of each node among its siblings (root's children:
-                               //        (link workgroup << 22) | index within the workgroup)
+  uint32_t *oslot, *occ;       // [nblocks] table slot and node of each store block
+  // per node (its id is a store block, its representative; id nblocks is the root, where an
+  // array has nblocks + 1 entries)
+  uint32_t *nparent;           // [nblocks] parent node
+  uint32_t *ncount;            // [nblocks] distinct paths through the node
+  uint32_t *nend;              // [nblocks] a path ends at the node
+  uint32_t *nchild;            // [nblocks + 1] children, where there are any
+  uint32_t *gstart;            // [nblocks + 1] position of a node's first child
+  uint32_t *cidx;              // [nblocks] index of each node among its siblings (root's children:
+                               //           (link workgroup << 22) | index within the workgroup)
+  uint32_t *weight;            // [nblocks] what the node adds to the ranks of the paths through it
+  uint32_t *place;             // [nblocks] (bucket << 24) | index there, for members of large groups
   uint32_t *rootbase;          // [1024] first index of each link workgroup's root children
-  uint32_t *grouped;           // [nblocks] nodes grouped by parent, siblings in order
-  uint32_t *grouped2;          // [nblocks] scratch
-  uint32_t *posof;             // [cap] position of each node in grouped
-  uint64_t *cnt;               // [nblocks] path counts in grouped order
-  uint64_t *cnt_scan;          // [nblocks + 1] their exclusive prefix sums
-  uint64_t *scan_blk;          // scan scratch: (nblocks / 1024 + 2) words
-  uint64_t *lists;             // [4][list_cap] (start << 32 | size): buckets of up to 64, groups of
-                               // 65 .. 512 siblings, groups of more than 512, buckets of 65 .. 2048
-  int64_t list_cap;
-  int64_t large_cap;           // groups of more than 1024 siblings that can be listed
-  uint32_t *lgroup;            // [cap + 1] list index of a large group, by parent node
+  int32_t large;               // groups of more siblings are split into buckets (set by launch_trie_sort)
+  uint32_t *grouped;           // [nblocks] nodes grouped by parent
+  uint32_t *grouped2;          // [nblocks] the same with the large groups' nodes in their buckets
+  uint64_t *unit, *unit2;      // [nblocks] (start << 32 | size) of each position's group, or bucket
+  uint32_t *base2;             // [nblocks] paths in the buckets before it
+  uint64_t *lists;             // [large_cap] (start << 32 | size) of the large groups
+  int64_t large_cap;           // large groups that can be listed
+  uint32_t *lgroup;            // [nblocks + 1] list index of a large group, by parent node
   uint32_t *spl;               // [large_cap][256] splitters (node ids)
-  uint32_t *bcnt;              // [large_cap][256] bucket sizes
-  unsigned long long *ctr;     // [8]: [0..3] list counts, [kTrieCtrFail] failure
+  uint32_t *bcnt, *bsum;       // [large_cap][256] bucket sizes, path counts
+  unsigned long long *ctr;     // [8], zeroed before
   uint32_t *order;             // [D] out: path ids in lexicographic order
 };
-constexpr int kTrieCtrFail = 4;
+// large groups listed, an empty path seen, nodes, failure
+constexpr int kTrieCtrLarge = 0, kTrieCtrEmpty = 1, kTrieCtrNodes = 2, kTrieCtrFail = 4;
+// bpos of block k of a path of len frames
+__host__ __device__ inline uint64_t make_bpos(uint64_t len, uint64_t k) { return (len << 32) | k; }
 // ctr[kTrieCtrFail] != 0 after the call: the trie could not be used (the caller sorts
-// another way).  s2 (may be s): a second stream for the part of the sibling ordering that
-// is independent of the large groups, forked from s with `fork` and joined back into s
-// with `join` (two events of the caller's, unused when s2 is s).
-void launch_trie_sort(const TrieArgs &a, hipStream_t s, hipStream_t s2, hipEvent_t fork, hipEvent_t mid,
-                      hipEvent_t join);
+// another way).  bpos holds the blocks of the paths from d_old on (launch_publish).
+void launch_trie_sort(const TrieArgs &a, int64_t d_old, hipStream_t s);
 // Levels of the minima of n = D + 1 positions: their entries in min_n, the words of levels
 // 1 and up as the result, and set_min_levels points mins at them (level 0 at lcp).
 int64_t min_level_words(int64_t n, CanonArgs &a);

@@ -941,8 +941,10 @@ __global__ __launch_bounds__(256) void publish_kernel(PublishArgs a) {
     const int64_t b = k0 / kStoreAlign + blk;  // the block within the path
     if ((g & 3) == 3 && (b + 1) * kStoreAlign <= full)
       a.pcp[start / kStoreAlign + b] = finish_hash(pre, (uint64_t)(b + 1) * kStoreAlign) & a.cp_mask;
+    if (a.bpos && (g & 3) == 0 && k0 + 16 * blk < rl) a.bpos[start / kStoreAlign + b] = make_bpos(len, (uint64_t)b);
     carry += bs[0] + bs[1] + bs[2] + bs[3];
   }
+  if (a.bpos && active && g == 0 && len == 0) *a.empty = 1;
   if (active && g == 0) {
     const uint32_t s = a.new_slots[i];
     const int64_t id = a.d_old + i;

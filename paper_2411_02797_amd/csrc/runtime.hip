@@ -634,7 +634,8 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
   CanonArgs ca{};
   const int64_t min_words = min_level_words(n1, ca);
   const int64_t u_max = sum_len + 1;
-  const size_t ctl_bytes = 64 + nblk * C * 8;  // control words, then the sums of the scan's blocks
+  // control words: 8 of the emission, 8 of the trie; then the sums of the scan's blocks
+  const size_t ctl_bytes = 128 + nblk * C * 8;
   Buf order, order_tmp, lcp, scan_in, scan_out, mins, recs, chain, win_path, cursor;
   Buf n_parent, n_frame, n_depth, n_subend, n_excl, n_incl;  // canonical arrays of the new tree
   if (!order.alloc(dneed * 4) || !order_tmp.alloc(dneed * 4) || !lcp.alloc((n1 + 15) / 16 * 64) || !scan_in.alloc(dneed * C * 8) ||
@@ -657,42 +658,40 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
   Buf merge_scratch;
   if (incremental && !merge_scratch.alloc(3 * (((int64_t)n_new + kSortBlock - 1) / kSortBlock * kSortBlock) * 4))
     return undo(fail(CCT_ENOMEM, "device allocation failed"));
-  Buf tr_key, tr_info, tr_bpos, tr_occ, tr_par, tr_cnt, tr_end, tr_hist, tr_gstart, tr_cidx, tr_rb, tr_lg, tr_spl, tr_bc, tr_grp, tr_grp2, tr_pos,
-      tr_c, tr_cs, tr_blk, tr_lists, tr_ctr;
+  Buf tr_key, tr_node, tr_block, tr_lg, tr_bc, tr_rb;
   TrieArgs ta{};
   if (use_trie) {
     const uint64_t tcap = pow2_at_least(std::max<uint64_t>(2 * (uint64_t)nblocks, 1024));
     const int64_t nbk = std::max<int64_t>(nblocks, 1);
-    const int64_t list_cap = nbk + 1024;
     const int64_t large_cap = nbk / 512 + 1;  // groups of more than 512 siblings (split into buckets)
-    const int64_t scan_rows = std::max<int64_t>((int64_t)tcap + 1, nbk);
-    if (!tr_key.alloc(tcap * 8) || !tr_info.alloc(tcap * 8) || !tr_bpos.alloc(nbk * 8) || !tr_occ.alloc(nbk * 4) ||
-        !tr_par.alloc(tcap * 4) || !tr_cnt.alloc(tcap * 4) || !tr_end.alloc((tcap + 1) * 4) ||
-        !tr_hist.alloc((tcap + 1) * 8) || !tr_gstart.alloc((tcap + 2) * 8) || !tr_cidx.alloc(tcap * 4) ||
-        !tr_rb.alloc(1024 * 4) || !tr_lg.alloc((tcap + 1) * 4) || !tr_spl.alloc(large_cap * 256 * 4) ||
-        !tr_bc.alloc(large_cap * 256 * 4) ||
-        !tr_grp.alloc(nbk * 4) || !tr_grp2.alloc(nbk * 4) || !tr_pos.alloc(tcap * 4) || !tr_c.alloc(nbk * 8) ||
-        !tr_cs.alloc((nbk + 1) * 8) || !tr_blk.alloc((scan_rows / 1024 + 2) * 8) || !tr_lists.alloc(4 * list_cap * 8) ||
-        !tr_ctr.alloc(64))
+    // per table slot: one 8-byte and three 4-byte arrays (one with an entry for the root);
+    // per node: nine of 4 bytes (three with an entry for the root); per position or block:
+    // five of 4 bytes and three of 8; per large group: its list entry, splitters, bucket
+    // sizes and path counts
+    if (!tr_key.alloc(tcap * 20 + 4) || !tr_node.alloc((9 * nbk + 3) * 4) || !tr_block.alloc(nbk * (3 * 8 + 5 * 4)) ||
+        !tr_lg.alloc(large_cap * 8) || !tr_bc.alloc(large_cap * 3 * 256 * 4) || !tr_rb.alloc(1024 * 4))
       return undo(fail(CCT_ENOMEM, "device allocation failed"));
     ta.d = D; ta.nblocks = nblocks; ta.cap = tcap;
     ta.pframes = t->pframes.as<uint32_t>(); ta.pcp = t->pcp.as<uint64_t>(); ta.pstart = t->pstart.as<int64_t>();
     ta.plen = t->plen.as<uint32_t>();
-    ta.tkey = tr_key.as<uint64_t>(); ta.tinfo = tr_info.as<uint64_t>(); ta.bpos = tr_bpos.as<uint64_t>();
-    ta.occ = tr_occ.as<uint32_t>(); ta.nparent = tr_par.as<uint32_t>(); ta.ncount = tr_cnt.as<uint32_t>();
-    ta.nend = tr_end.as<uint32_t>(); ta.hist = tr_hist.as<uint64_t>(); ta.gstart = tr_gstart.as<uint64_t>();
-    ta.cidx = tr_cidx.as<uint32_t>(); ta.rootbase = tr_rb.as<uint32_t>(); ta.grouped = tr_grp.as<uint32_t>(); ta.grouped2 = tr_grp2.as<uint32_t>();
-    ta.posof = tr_pos.as<uint32_t>(); ta.cnt = tr_c.as<uint64_t>(); ta.cnt_scan = tr_cs.as<uint64_t>();
-    ta.scan_blk = tr_blk.as<uint64_t>(); ta.lists = tr_lists.as<uint64_t>(); ta.list_cap = list_cap; ta.large_cap = large_cap;
-    ta.lgroup = tr_lg.as<uint32_t>(); ta.spl = tr_spl.as<uint32_t>(); ta.bcnt = tr_bc.as<uint32_t>();
-    ta.ctr = tr_ctr.as<unsigned long long>(); ta.order = order.as<uint32_t>();
+    ta.tkey = tr_key.as<uint64_t>(); ta.tval = (uint32_t *)(ta.tkey + tcap);
+    ta.count = ta.tval + tcap; ta.hist = ta.count + tcap;
+    uint32_t *pn = tr_node.as<uint32_t>();
+    for (uint32_t **f : {&ta.nparent, &ta.ncount, &ta.nend, &ta.cidx, &ta.weight, &ta.place}) { *f = pn; pn += nbk; }
+    for (uint32_t **f : {&ta.nchild, &ta.gstart, &ta.lgroup}) { *f = pn; pn += nbk + 1; }
+    ta.bpos = tr_block.as<uint64_t>(); ta.unit = ta.bpos + nbk; ta.unit2 = ta.unit + nbk;
+    uint32_t *pb = (uint32_t *)(ta.unit2 + nbk);
+    for (uint32_t **f : {&ta.oslot, &ta.occ, &ta.grouped, &ta.grouped2, &ta.base2}) { *f = pb; pb += nbk; }
+    ta.rootbase = tr_rb.as<uint32_t>();
+    ta.lists = tr_lg.as<uint64_t>(); ta.large_cap = large_cap;
+    ta.spl = tr_bc.as<uint32_t>(); ta.bcnt = ta.spl + large_cap * 256; ta.bsum = ta.bcnt + large_cap * 256;
+    ta.ctr = cursor.as<unsigned long long>() + 8; ta.order = order.as<uint32_t>();
   }
 
   Timer ts;
   g_stats_ms = 0;
 
   // ---- publish new paths ----------------------------------------------------------------
-  Event trie_fork, trie_mid, trie_join;
   AGG_TRY(hipMemsetAsync(cursor.p, 0, ctl_bytes, s));
   if (n_new) {
     PublishArgs pa{};
@@ -702,6 +701,7 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
     pa.pstart = t->pstart.as<int64_t>(); pa.plen = t->plen.as<uint32_t>(); pa.pslot = t->pslot.as<uint32_t>();
     pa.store_used = t->store_used; pa.starts = nstart.as<uint64_t>();
     pa.src_len = nsrc.as<int64_t>();
+    if (use_trie) { pa.bpos = ta.bpos; pa.empty = ta.ctr + kTrieCtrEmpty; }
     // a test setting keeps fewer bits of the checkpoint hashes, so that the fast orders
     // meet colliding prefixes and the exact comparison sort has to take over
     const int cp_bits = (int)env_int("CCT_TEST_CP_HASH_BITS", 64);
@@ -730,7 +730,7 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
   ca.d_old = t->d; ca.pslot = t->pslot.as<uint32_t>(); ca.delta = delta.as<uint64_t>();
   ca.old_sums = t->psums.as<uint64_t>();
   ca.order = order.as<uint32_t>(); ca.order_tmp = order_tmp.as<uint32_t>(); ca.lcp = lcp.as<uint32_t>();
-  ca.scan_in = scan_in.as<uint64_t>(); ca.scan_out = scan_out.as<uint64_t>(); ca.scan_blk = cursor.as<uint64_t>() + 8;
+  ca.scan_in = scan_in.as<uint64_t>(); ca.scan_out = scan_out.as<uint64_t>(); ca.scan_blk = cursor.as<uint64_t>() + 16;
   set_min_levels(ca, mins.as<uint32_t>());
   ca.rec = recs.as<CanonRec>();
   ca.chain_parent = chain.as<uint32_t>(); ca.win_path = win_path.as<uint32_t>(); ca.u_max = u_max;
@@ -744,7 +744,7 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
   for (int mode = incremental ? 3 : (use_trie ? 0 : (ca.exact ? 2 : 1));;) {
     CanonArgs run = ca;
     run.exact = mode == 2 ? 1 : 0;
-    if (mode == 0) launch_trie_sort(ta, s, side, trie_fork.ev, trie_mid.ev, trie_join.ev);
+    if (mode == 0) launch_trie_sort(ta, t->d, s);
     else if (mode == 3) launch_merge_order(run, t->order.as<uint32_t>(), t->lcp.as<uint32_t>(), t->d, merge_scratch.as<uint32_t>(), s);
     else launch_sort(run, s);
     tm.mark(4, s);
@@ -752,8 +752,7 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
     launch_canon(run, s);
     AGG_TRY(hipGetLastError());
     tm.mark(5, s);
-    AGG_TRY(hipMemcpyAsync(hs, cursor.p, 64, hipMemcpyDeviceToHost, s));
-    if (mode == 0) AGG_TRY(hipMemcpyAsync(hs + 8, ta.ctr, 64, hipMemcpyDeviceToHost, s));
+    AGG_TRY(hipMemcpyAsync(hs, cursor.p, 128, hipMemcpyDeviceToHost, s));
     AGG_TRY(spin_sync(s));
     const bool trie_failed = mode == 0 && hs[8 + kTrieCtrFail] != 0;
     if (!hs[3] && !trie_failed) {  // order verified strictly increasing

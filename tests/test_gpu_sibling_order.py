@@ -1,0 +1,35 @@
+"""Sibling order in the block trie at the edges of its rules: groups counted whole (up to 512,
+or up to 2,048 in a small trie), groups split into buckets, blocks that share long prefixes,
+and blocks that end early or hold zero frames."""
+import numpy as np
+import pytest
+
+import oracle
+from gpu_util import assert_same, csr, gpu_tree, torch_or_skip
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("shared", [0, 13, 15])  # frames all siblings' blocks share
+@pytest.mark.parametrize("sizes", [(1,), (2,), (64, 65), (511, 512, 513), (1023, 1025), (2048,), (2049,), (513, 2, 700, 1, 9000),
+                                   (40000,)])
+def test_groups_of_siblings(sizes, shared, monkeypatch):
+    torch_or_skip()
+    monkeypatch.setenv("CCT_TEST_REQUIRE_TRIE", "1")
+    rng = np.random.default_rng(sum(sizes) + shared)
+    paths = []
+    for g, n in enumerate(sizes):  # group g: n blocks below a first block of their own
+        head = [7] * 15 + [g] if len(sizes) > 1 else []
+        stem = [3] * shared
+        kids = set()
+        while len(kids) < n:
+            room = 16 - shared
+            k = int(rng.integers(1, room + 1))
+            kids.add(tuple(int(x) for x in rng.integers(0, 60000 if room == 1 else 250, k)) if rng.random() < 0.8
+                     else (0,) * k if rng.random() < 0.1 else tuple([0] * (k - 1) + [int(rng.integers(0, 1 << 32))]))
+        paths += [head + stem + list(k) for k in kids]
+    paths += [[], [3] * shared] if shared else [[]]
+    paths = [paths[i] for i in rng.permutation(len(paths))]
+    o, f = csr(paths)
+    w = rng.integers(0, 1 << 62, (len(paths), 1), dtype=np.uint64)
+    assert_same(gpu_tree(o, f, w), oracle.build_tree(o, f, w))

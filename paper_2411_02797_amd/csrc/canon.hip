@@ -112,6 +112,7 @@ __device__ inline bool key_less(const CanonArgs &a, uint32_t x, uint32_t y) {
 // Block-local bitonic sort by path.
 __global__ __launch_bounds__(512) void sort_block_kernel(CanonArgs a, uint32_t *out) {
   __shared__ uint32_t key[kSortBlock];
+  stamp(a.stamps + kStampOrder);
   const int tid = threadIdx.x;
   const int64_t base = (int64_t)blockIdx.x * kSortBlock;
   for (int i = tid; i < kSortBlock; i += 512) key[i] = base + i < a.d ? (uint32_t)(a.id0 + base + i) : kInf;
@@ -251,6 +252,7 @@ __global__ __launch_bounds__(256) void merge_pass_kernel(CanonArgs a, const uint
 constexpr int kGapLanes = 16;
 __global__ __launch_bounds__(256) void gap_kernel(CanonArgs a, const uint32_t *old_order, int64_t d_old, uint32_t *gap,
                                                   uint32_t *ids, uint32_t *bgap, uint32_t *gsorted) {
+  stamp(a.stamps + kStampOrder);
   const int lane = threadIdx.x & 63, g = lane % kGapLanes, g0 = lane - g;
   const int64_t j = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kGapLanes;
   const bool active = j < a.d - d_old;
@@ -306,7 +308,9 @@ __global__ __launch_bounds__(256) void place_new_kernel(const uint32_t *B, int64
 }
 __global__ __launch_bounds__(256) void place_old_kernel(const uint32_t *A, int64_t d_old, const uint32_t *gsorted,
                                                         int64_t n_new, const uint32_t *old_lcp, uint32_t *dst,
-                                                        uint32_t *lcp, unsigned long long *u_out) {
+                                                        uint32_t *lcp, unsigned long long *u_out,
+                                                        unsigned long long *stamps) {
+  if (n_new == 0) stamp(stamps + kStampOrder);
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   // a rank no path took (two took another one, after a hash collision): the order has a
   // hole there, and the host sorts again by exact comparisons
@@ -384,6 +388,7 @@ __global__ __launch_bounds__(256) void lcp_kernel(CanonArgs a) {
   __shared__ uint32_t ls[kLcpPer];
   __shared__ uint64_t rows[kLcpPer][9];
   const int C = 1 + a.m, lane = threadIdx.x & 63, g = lane % kLcpLanes, r = threadIdx.x / kLcpLanes;
+  stamp(a.stamps + kStampNodes);
   // levels of the minima from 3 up are met by atomics in the next kernel
   if (blockIdx.x == 0)
     for (int v = 3; v < a.min_levels; ++v)
@@ -911,7 +916,7 @@ void launch_merge_order(CanonArgs &a, const uint32_t *old_order, const uint32_t 
     }
   }
   hipLaunchKernelGGL(place_old_kernel, dim3(blocks_for(std::max(d_old, n_new), 256)), dim3(256), 0, s, old_order,
-                     d_old, gsorted, n_new, old_lcp, dst, a.lcp, a.u_out);
+                     d_old, gsorted, n_new, old_lcp, dst, a.lcp, a.u_out, a.stamps);
   a.order_tmp = dst == a.order ? a.order_tmp : a.order;
   a.order = dst;
 }

@@ -40,6 +40,17 @@ enum Counter { kCtrNew = 0, kCtrError = 2, kCtrOverflow = 3, kCtrNewLen = 4,
 enum ErrorBits { kErrOffsets = 1 };
 constexpr uint32_t kNoSlot = 0xFFFFFFFFu;  // event not resolved (the call fails or retries)
 
+// ---- one call's control block -------------------------------------------------------
+// Words of a device buffer: the ingest's counters, stamps of the device's fixed-rate clock
+// (one kernel at each phase's start writes its own: an event between kernels costs a small
+// call 3 us), the emission's and the trie's control words, then the scan's block sums.
+constexpr int kCtlCounters = 0, kCtlStamps = 8, kCtlCanon = 16, kCtlTrie = 24, kCtlSums = 32;
+// call start, ingest, collection, ordering, node arrays; the end is stamped by launch_finish
+enum Stamp { kStampCall = 0, kStampIngest = 1, kStampCollect = 2, kStampOrder = 3, kStampNodes = 4, kStampEnd = 5 };
+__device__ inline void stamp(unsigned long long *at) {
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *at = (unsigned long long)wall_clock64();
+}
+
 // ---- path hashing ----------------------------------------------------------------
 // Checkpoint hashes (prefixes at 16-frame boundaries, used to order paths) are a sum
 // over the frames of a term of (frame, position), so partial sums over any split of
@@ -116,6 +127,24 @@ struct IngestArgs {
   unsigned long long *ctr;
 };
 
+// What a call clears before its ingest, in one launch: the control block, the batch sums,
+// the staging's counts (n_count may be 0), and a fresh table's slots (n_slots may be 0).
+struct InitArgs {
+  Slot *slot;
+  uint64_t n_slots;
+  uint64_t *delta;
+  uint64_t n_delta;          // words
+  uint32_t *count;
+  uint64_t n_count;
+  unsigned long long *ctl;
+  uint64_t n_ctl;            // words
+  int first;                 // the call's first attempt (stamps its start)
+};
+void launch_init(const InitArgs &a, hipStream_t s);
+// n words of the control block from `from` into pinned host memory; the end is stamped
+void launch_report(const unsigned long long *from, int n, unsigned long long *host, hipStream_t s);
+void launch_finish(unsigned long long *ctl, unsigned long long *host, hipStream_t s);
+
 // Host-side launch wrappers (one translation unit per kernel family).
 void launch_ingest(const IngestArgs &a, int grid, hipStream_t s);
 // Sum metrics [N][m] into delta[slot_of[e]][m] (delta starts zeroed).  Every workgroup
@@ -148,7 +177,7 @@ void launch_aggregate(const uint32_t *slot_of, const uint64_t *w, int64_t n, int
 constexpr int kNewShift = 33;
 constexpr unsigned long long kNewBlocksMask = (1ull << kNewShift) - 1;
 void launch_collect_new(const Slot *slot, uint64_t cap, const int64_t *off, uint32_t *new_slots, int64_t *src_len,
-                        uint64_t *starts, int64_t list_cap, unsigned long long *ctr, hipStream_t s);
+                        uint64_t *starts, int64_t list_cap, unsigned long long *ctl, hipStream_t s);
 
 // Path store: path d occupies frames [pstart[d], pstart[d] + round16(plen[d])) of
 // pframes (pstart is a multiple of kStoreAlign, the tail is zero-filled), and its
@@ -236,6 +265,7 @@ struct CanonArgs {
   uint32_t *subend;      // [U] end of each node's subtree: its descendants are the ids (u, subend[u])
   uint64_t *excl, *incl;
   unsigned long long *u_out;  // device: [0] node count, [1] order-violation flag
+  unsigned long long *stamps;
   int grid_nodes;
 };
 void launch_sort(CanonArgs &a, hipStream_t s);        // leaves the result in a.order
@@ -288,6 +318,7 @@ struct TrieArgs {
   uint32_t *spl;               // [large_cap][256] splitters (node ids)
   uint32_t *bcnt, *bsum;       // [large_cap][256] bucket sizes, path counts
   unsigned long long *ctr;     // [8], zeroed before
+  unsigned long long *stamps;
   uint32_t *order;             // [D] out: path ids in lexicographic order
 };
 // large groups listed, an empty path seen, nodes, failure

@@ -813,6 +813,38 @@ __global__ __launch_bounds__(kAggThreads) void agg_reduce_kernel(AggStage st, ui
   }
 }
 
+// Everything a call clears, 16 bytes per lane and store.
+__global__ __launch_bounds__(256) void init_kernel(InitArgs a) {
+  const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (uint64_t)gridDim.x * blockDim.x;
+  if (a.first) stamp(a.ctl + kCtlStamps + kStampCall);
+  for (uint64_t i = t; i < a.n_slots; i += stride) {
+    const u32x4 v = {~0u, ~0u, ~0u, ~0u};
+    *(u32x4 *)(a.slot + i) = v;
+  }
+  for (uint64_t i = t; i < a.n_delta / 2; i += stride) {
+    const u32x4 v = {0u, 0u, 0u, 0u};
+    *(u32x4 *)(a.delta + 2 * i) = v;
+  }
+  if (t == 0 && (a.n_delta & 1)) a.delta[a.n_delta - 1] = 0;
+  for (uint64_t i = t; i < a.n_count; i += stride) a.count[i] = 0;
+  for (uint64_t i = t; i < a.n_ctl; i += stride)
+    if (i < (uint64_t)kCtlStamps || i >= (uint64_t)kCtlStamps + 8) a.ctl[i] = 0;
+  stamp(a.ctl + kCtlStamps + kStampIngest);
+  stamp(a.ctl + kCtlStamps + kStampCollect);
+  stamp(a.ctl + kCtlStamps + kStampOrder);
+  stamp(a.ctl + kCtlStamps + kStampNodes);
+}
+// (a kernel's stores to pinned memory are 2 us quicker than a copy)
+__global__ __launch_bounds__(64) void report_kernel(const unsigned long long *from, int n, unsigned long long *host) {
+  if ((int)threadIdx.x < n) host[threadIdx.x] = from[threadIdx.x];
+}
+// stamps, emission and trie words to the host, the call's end among the stamps
+__global__ __launch_bounds__(64) void finish_kernel(unsigned long long *ctl, unsigned long long *host) {
+  const int i = threadIdx.x;
+  if (i < kCtlSums - kCtlStamps)
+    host[i] = i == kStampEnd ? (unsigned long long)wall_clock64() : ctl[kCtlStamps + i];
+}
+
 // Slots claimed in this call: a block of 1024 threads scans 4096 slots, counts its claims,
 // reserves list positions and store blocks for them, and writes them.  One 64-bit atomic
 // reserves both (the count in the bits from kNewShift on, 16-frame store blocks below), so
@@ -824,7 +856,9 @@ constexpr int kCollectThreads = 1024, kCollectPerThread = 4;
 __global__ __launch_bounds__(kCollectThreads) void collect_new_kernel(const Slot *slot, uint64_t cap,
                                                                       const int64_t *off, uint32_t *new_slots,
                                                                       int64_t *src_len, uint64_t *starts,
-                                                                      uint64_t list_cap, unsigned long long *ctr) {
+                                                                      uint64_t list_cap, unsigned long long *ctl) {
+  unsigned long long *ctr = ctl + kCtlCounters;
+  stamp(ctl + kCtlStamps + kStampCollect);
   __shared__ unsigned long long mine, base, lens;
   if (threadIdx.x == 0) { mine = 0; lens = 0; }
   __syncthreads();
@@ -1004,6 +1038,18 @@ inline unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1)
 
 }  // namespace
 
+void launch_init(const InitArgs &a, hipStream_t s) {
+  const uint64_t n = std::max(std::max(a.n_slots, a.n_delta / 2), std::max(a.n_ctl, a.n_count));
+  const unsigned grid = (unsigned)std::min<uint64_t>((n + 255) / 256 + 1, 4096);
+  hipLaunchKernelGGL(init_kernel, dim3(grid), dim3(256), 0, s, a);
+}
+void launch_report(const unsigned long long *from, int n, unsigned long long *host, hipStream_t s) {
+  hipLaunchKernelGGL(report_kernel, dim3(1), dim3(64), 0, s, from, n, host);
+}
+void launch_finish(unsigned long long *ctl, unsigned long long *host, hipStream_t s) {
+  hipLaunchKernelGGL(finish_kernel, dim3(1), dim3(64), 0, s, ctl, host);
+}
+
 void launch_ingest(const IngestArgs &a, int grid, hipStream_t s) {
   hipLaunchKernelGGL(ingest_kernel, dim3(grid), dim3(kIngestThreads), 0, s, a);
 }
@@ -1048,10 +1094,10 @@ void launch_aggregate(const uint32_t *slot_of, const uint64_t *w, int64_t n, int
   }
 }
 void launch_collect_new(const Slot *slot, uint64_t cap, const int64_t *off, uint32_t *new_slots, int64_t *src_len,
-                        uint64_t *starts, int64_t list_cap, unsigned long long *ctr, hipStream_t s) {
+                        uint64_t *starts, int64_t list_cap, unsigned long long *ctl, hipStream_t s) {
   const uint64_t per = (uint64_t)kCollectThreads * kCollectPerThread;
   hipLaunchKernelGGL(collect_new_kernel, dim3((unsigned)((cap + per - 1) / per)), dim3(kCollectThreads), 0, s, slot,
-                     cap, off, new_slots, src_len, starts, (uint64_t)list_cap, ctr);
+                     cap, off, new_slots, src_len, starts, (uint64_t)list_cap, ctl);
 }
 void launch_publish(const PublishArgs &a, hipStream_t s) {
   if (a.n_new <= 0) return;

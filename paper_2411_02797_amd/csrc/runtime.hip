@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -173,6 +174,7 @@ StreamPool &stream_pool() {
 struct SideGuard {
   hipStream_t st = nullptr;
   int dev = 0;
+  bool idle = false;  // nothing is left on it: no wait
   hipStream_t acquire() {
     if (hipGetDevice(&dev) != hipSuccess) { (void)hipGetLastError(); return nullptr; }
     StreamPool &P = stream_pool();
@@ -193,7 +195,7 @@ struct SideGuard {
   }
   ~SideGuard() {
     if (!st) return;
-    (void)hipStreamSynchronize(st);
+    if (!idle) (void)hipStreamSynchronize(st);
     StreamPool &P = stream_pool();
     std::lock_guard<std::mutex> lock(P.mu);
     P.free.emplace_back(dev, st);
@@ -249,6 +251,7 @@ struct cct_tree {
   int32_t m = 1;
   // unique-path table (slot words); sums live per path in psums
   uint64_t cap = 0;
+  bool fresh = false;  // the slots are not cleared yet (the first call does it)
   Buf slot;
   // path store
   int64_t d = 0, dcap = 0;
@@ -306,10 +309,9 @@ cct_status grow(Buf &b, size_t need, size_t keep, hipStream_t s) {
   return CCT_OK;
 }
 
-// HIP events on the call's stream: 0 call start, 1/2 around the ingest kernel, 3 after
-// publish, 4 after the sort, 5 after node emission.
+// Two HIP events on a call's stream.
 struct Timer {
-  hipEvent_t ev[6] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
+  hipEvent_t ev[2] = {nullptr, nullptr};
   bool ok = true;
   Timer() {
     for (auto &e : ev)
@@ -327,23 +329,37 @@ struct Timer {
     if (hipEventElapsedTime(&ms, ev[a], ev[b]) != hipSuccess) { (void)hipGetLastError(); return 0; }
     return ms;
   }
-  // timings: ingest kernel, publish, sort, emission, whole call
-  void collect(bool ingested) {
-    for (int i = 0; i < 5; ++i) g_timings[i] = 0;
-    if (!ok) return;
-    if (ingested) g_timings[0] = span(1, 2);
-    g_timings[1] = span(2, 3);
-    g_timings[2] = span(3, 4);
-    g_timings[3] = span(4, 5);
-    g_timings[4] = span(0, 5);
-  }
 };
 
+// ticks of the device's fixed-rate clock (wall_clock64) per millisecond
+double clock_ticks_per_ms(int dev) {
+  static std::atomic<int> cached[64];
+  if (dev < 0 || dev >= 64) return 1e5;
+  int khz = cached[dev].load();
+  if (khz <= 0) {
+    if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev) != hipSuccess || khz <= 0) {
+      (void)hipGetLastError();
+      khz = 100000;
+    }
+    cached[dev].store(khz);
+  }
+  return (double)khz;
+}
+// timings of a build or merge from its stamps: ingest, publish, ordering, node arrays, whole call
+void collect_timings(const unsigned long long *st, int dev, bool ingested) {
+  const double per_ms = clock_ticks_per_ms(dev);
+  auto span = [&](int a, int b) { return st[b] > st[a] ? (double)(st[b] - st[a]) / per_ms : 0.0; };
+  g_timings[0] = ingested ? span(kStampIngest, kStampCollect) : 0;
+  g_timings[1] = span(kStampCollect, kStampOrder);
+  g_timings[2] = span(kStampOrder, kStampNodes);
+  g_timings[3] = span(kStampNodes, kStampEnd);
+  g_timings[4] = span(kStampCall, kStampEnd);
+}
+
 // Staging of the metric aggregation (launch_aggregate) for `n_rows` rows keyed by slots
-// below `cap`: bucket counts zeroed on `s`.  Leaves st.nbuckets = 0 (atomic flush) when
-// the slots need more buckets than a workgroup can count.
-cct_status setup_stage(int32_t m, uint64_t cap, int agg_grid, Buf &count, Buf &keys, Buf &sums, AggStage &st,
-                       hipStream_t s) {
+// below `cap`; the caller zeroes the bucket counts (st.count, st.nbuckets of them).  Leaves
+// st.nbuckets = 0 (atomic flush) when the slots need more buckets than a workgroup can count.
+cct_status setup_stage(int32_t m, uint64_t cap, int agg_grid, Buf &count, Buf &keys, Buf &sums, AggStage &st) {
   st = AggStage{};
   st.bshift = agg_bucket_shift(m);
   const int64_t nbk = std::max<int64_t>(1, (int64_t)((cap + (1ull << st.bshift) - 1) >> st.bshift));
@@ -353,7 +369,6 @@ cct_status setup_stage(int32_t m, uint64_t cap, int agg_grid, Buf &count, Buf &k
   st.bucket_cap = 2 * ((total + nbk - 1) / nbk) + 256;  // twice the even share (slots are hashed)
   if (!count.alloc(nbk * 4) || !keys.alloc(nbk * st.bucket_cap * 4) || !sums.alloc(nbk * st.bucket_cap * m * 8))
     return fail(CCT_ENOMEM, "device allocation failed");
-  HIP_TRY(hipMemsetAsync(count.p, 0, nbk * 4, s));
   st.count = count.as<uint32_t>();
   st.keys = keys.as<uint32_t>();
   st.sums = sums.as<uint64_t>();
@@ -406,12 +421,9 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
   const uint64_t hash_mask = hash_bits >= 64 ? ~0ull : ((1ull << (hash_bits < 0 ? 0 : hash_bits)) - 1);
   unsigned long long *hs = host_scratch();
   if (!hs) return fail(CCT_ENOMEM, "pinned host allocation failed");
-  Timer tm;
-  tm.mark(0, s);
-
-  Buf ctr;
-  if (!ctr.alloc(kCtrCount * 8 + 64)) return fail(CCT_ENOMEM, "device allocation failed");
-  unsigned long long *dctr = ctr.as<unsigned long long>();
+  const int C = 1 + m;
+  Buf ctl;  // the call's control block
+  size_t ctl_words = 0;
 
   // Failure path: this call's claims (before they are published) or its published slots
   // are emptied again, and both of the call's streams are synchronised before any of its
@@ -444,8 +456,14 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
     AGG_TRY(hipStreamSynchronize(s));
     if (hs[0] != 0) return fail(CCT_EINVAL, "offsets[0] != 0");
     if (t->parent.p) return CCT_OK;
-    tm.mark(1, s);
-    tm.mark(2, s);
+    ctl_words = kCtlSums + (t->d / 1024 + 1) * C;
+    if (!ctl.alloc(ctl_words * 8)) return fail(CCT_ENOMEM, "device allocation failed");
+    InitArgs ia{};
+    ia.ctl = ctl.as<unsigned long long>(); ia.n_ctl = ctl_words; ia.first = 1;
+    if (t->fresh) { ia.slot = t->slot.as<Slot>(); ia.n_slots = t->cap; }
+    launch_init(ia, s);
+    AGG_TRY(hipGetLastError());
+    t->fresh = false;
   }
 
   // ---- A1-A3: ingest (retry with a larger table on overflow) -------------------------
@@ -485,39 +503,43 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
       if (!delta.alloc(t->cap * m * 8) || !new_slots.alloc(t->cap * 4) ||
           !nsrc.alloc((size_t)max_new * 16) || !nstart.alloc((size_t)max_new * 8))
         return fail(CCT_ENOMEM, "device allocation failed");
-      AGG_TRY(hipMemsetAsync(delta.p, 0, t->cap * m * 8, s));
-      AGG_TRY(hipMemsetAsync(dctr, 0, kCtrCount * 8, s));
+      // (the sums of the scan's blocks: room for every path the tree may then have)
+      ctl_words = kCtlSums + ((t->d + max_new) / 1024 + 1) * C;
+      if (!ctl.alloc(ctl_words * 8)) return fail(CCT_ENOMEM, "device allocation failed");
+      if (N > kOneStreamEvents) {
+        cct_status sst = setup_stage(m, t->cap, agg_grid, agg_count, agg_keys, agg_sums, stg);
+        if (sst) return sst;
+      }
+      InitArgs ia{};
+      if (t->fresh) { ia.slot = t->slot.as<Slot>(); ia.n_slots = t->cap; }
+      ia.delta = delta.as<uint64_t>(); ia.n_delta = t->cap * m;
+      ia.count = stg.count; ia.n_count = (uint64_t)stg.nbuckets;
+      ia.ctl = ctl.as<unsigned long long>(); ia.n_ctl = ctl_words; ia.first = attempt == 0;
+      launch_init(ia, s);
+      t->fresh = false;
       IngestArgs a{};
       a.off = p->offsets; a.fr = p->frames;
       a.n_events = N; a.n_frames = p->n_frames;
       a.slot = t->slot.as<Slot>(); a.cap_mask = t->cap - 1; a.hash_mask = hash_mask;
       a.slot_of = slot_of.as<uint32_t>();
       a.pframes = t->pframes.as<uint32_t>(); a.pstart = t->pstart.as<int64_t>(); a.plen = t->plen.as<uint32_t>();
-      a.ctr = dctr;
+      a.ctr = ia.ctl + kCtlCounters;
       // one workgroup per CU; every wave owns an equal share of the events
       const int64_t wg_needed = (N + kIngestThreads / 64 - 1) / (kIngestThreads / 64);
       const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(wg_needed, (int64_t)cu_count()));
-      tm.mark(1, s);
       launch_ingest(a, grid, s);
-      tm.mark(2, s);
       launch_collect_new(t->slot.as<Slot>(), t->cap, p->offsets, new_slots.as<uint32_t>(), nsrc.as<int64_t>(),
-                         nstart.as<uint64_t>(), max_new, dctr, s);
+                         nstart.as<uint64_t>(), max_new, ia.ctl, s);
       claimed = true;  // (from the launch on: the table may hold this call's claims)
       AGG_TRY(hipGetLastError());
-      AGG_TRY(hipMemcpyAsync(hs, dctr, kCtrCount * 8, hipMemcpyDeviceToHost, s));
+      launch_report(ia.ctl + kCtlCounters, kCtrCount, hs, s);
       AGG_TRY(hipEventRecord(counted.ev, s));
-      {
-        // (the side stream's work, the staging's zeroing included, starts after the collection;
-        // on one stream the sums follow the counters' copy, which the host reads meanwhile)
-        if (side != s) AGG_TRY(hipStreamWaitEvent(side, counted.ev, 0));
-        if (N > kOneStreamEvents) {
-          cct_status sst = setup_stage(m, t->cap, agg_grid, agg_count, agg_keys, agg_sums, stg, side);
-          if (sst) return undo(sst);
-        }
-        launch_aggregate(slot_of.as<uint32_t>(), p->metrics, N, m, delta.as<uint64_t>(), t->cap, agg_grid, stg, side);
-        AGG_TRY(hipGetLastError());
-        if (side != s) AGG_TRY(hipEventRecord(summed.ev, side));
-      }
+      // (the side stream's work starts after the collection; on one stream the sums follow
+      // the counters' report, which the host reads meanwhile)
+      if (side != s) AGG_TRY(hipStreamWaitEvent(side, counted.ev, 0));
+      launch_aggregate(slot_of.as<uint32_t>(), p->metrics, N, m, delta.as<uint64_t>(), t->cap, agg_grid, stg, side);
+      AGG_TRY(hipGetLastError());
+      if (side != s) AGG_TRY(hipEventRecord(summed.ev, side));
       AGG_TRY(spin_event(counted.ev));
       if (hs[kCtrError]) return undo(fail(CCT_EINVAL, "malformed offsets"));
       if (hs[kCtrOverflow]) {
@@ -628,19 +650,15 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
          hipMemcpyAsync(nsq.p, t->psq.p, t->d * m * 16, hipMemcpyDeviceToDevice, s) != hipSuccess))
       return undo(fail(CCT_EDEVICE, "copy failed"));
   }
-  const int C = 1 + m;
   const int64_t n1 = D + 1;
-  const int64_t nblk = (n1 + 1023) / 1024;
   CanonArgs ca{};
   const int64_t min_words = min_level_words(n1, ca);
   const int64_t u_max = sum_len + 1;
-  // control words: 8 of the emission, 8 of the trie; then the sums of the scan's blocks
-  const size_t ctl_bytes = 128 + nblk * C * 8;
-  Buf order, order_tmp, lcp, scan_in, scan_out, mins, recs, chain, win_path, cursor;
+  Buf order, order_tmp, lcp, scan_in, scan_out, mins, recs, chain, win_path;
   Buf n_parent, n_frame, n_depth, n_subend, n_excl, n_incl;  // canonical arrays of the new tree
   if (!order.alloc(dneed * 4) || !order_tmp.alloc(dneed * 4) || !lcp.alloc((n1 + 15) / 16 * 64) || !scan_in.alloc(dneed * C * 8) ||
       !scan_out.alloc(n1 * C * 8) || !mins.alloc(min_words * 4) || !recs.alloc(dneed * sizeof(CanonRec)) ||
-      !chain.alloc(dneed * 4) || !win_path.alloc((u_max / 64 + 2) * 4) || !cursor.alloc(ctl_bytes) || !n_parent.alloc(u_max * 4) || !n_subend.alloc(u_max * 4) ||
+      !chain.alloc(dneed * 4) || !win_path.alloc((u_max / 64 + 2) * 4) || !n_parent.alloc(u_max * 4) || !n_subend.alloc(u_max * 4) ||
       !n_frame.alloc(u_max * 4) || !n_depth.alloc(u_max * 4) || !n_excl.alloc(u_max * m * 8) ||
       !n_incl.alloc(u_max * m * 8))
     return undo(fail(CCT_ENOMEM, "device allocation failed"));
@@ -685,14 +703,14 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
     ta.rootbase = tr_rb.as<uint32_t>();
     ta.lists = tr_lg.as<uint64_t>(); ta.large_cap = large_cap;
     ta.spl = tr_bc.as<uint32_t>(); ta.bcnt = ta.spl + large_cap * 256; ta.bsum = ta.bcnt + large_cap * 256;
-    ta.ctr = cursor.as<unsigned long long>() + 8; ta.order = order.as<uint32_t>();
+    ta.ctr = ctl.as<unsigned long long>() + kCtlTrie; ta.stamps = ctl.as<unsigned long long>() + kCtlStamps;
+    ta.order = order.as<uint32_t>();
   }
 
   Timer ts;
   g_stats_ms = 0;
 
   // ---- publish new paths ----------------------------------------------------------------
-  AGG_TRY(hipMemsetAsync(cursor.p, 0, ctl_bytes, s));
   if (n_new) {
     PublishArgs pa{};
     pa.off = p->offsets; pa.fr = p->frames; pa.n_frames = p->n_frames; pa.slot = t->slot.as<Slot>();
@@ -718,7 +736,6 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
     ts.mark(1, s);
   }
   AGG_TRY(hipGetLastError());
-  tm.mark(3, s);
   // test setting: fail once everything is published, to check that the
   // tree is left as it was
   if (env_int("CCT_TEST_FAIL_AFTER_PUBLISH", 0)) return undo(fail(CCT_EDEVICE, "test failure after publish"));
@@ -730,14 +747,15 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
   ca.d_old = t->d; ca.pslot = t->pslot.as<uint32_t>(); ca.delta = delta.as<uint64_t>();
   ca.old_sums = t->psums.as<uint64_t>();
   ca.order = order.as<uint32_t>(); ca.order_tmp = order_tmp.as<uint32_t>(); ca.lcp = lcp.as<uint32_t>();
-  ca.scan_in = scan_in.as<uint64_t>(); ca.scan_out = scan_out.as<uint64_t>(); ca.scan_blk = cursor.as<uint64_t>() + 16;
+  ca.scan_in = scan_in.as<uint64_t>(); ca.scan_out = scan_out.as<uint64_t>(); ca.scan_blk = ctl.as<uint64_t>() + kCtlSums;
   set_min_levels(ca, mins.as<uint32_t>());
   ca.rec = recs.as<CanonRec>();
   ca.chain_parent = chain.as<uint32_t>(); ca.win_path = win_path.as<uint32_t>(); ca.u_max = u_max;
   ca.parent = n_parent.as<uint32_t>(); ca.frame = n_frame.as<uint32_t>(); ca.depth = n_depth.as<uint32_t>();
   ca.subend = n_subend.as<uint32_t>();
   ca.excl = n_excl.as<uint64_t>(); ca.incl = n_incl.as<uint64_t>();
-  ca.u_out = cursor.as<unsigned long long>() + 2;
+  ca.u_out = ctl.as<unsigned long long>() + kCtlCanon;
+  ca.stamps = ctl.as<unsigned long long>() + kCtlStamps;
   ca.grid_nodes = (int)std::max<int64_t>(1, std::min<int64_t>((u_max + 255) / 256, (int64_t)cu_count() * 64));
   // 0: block trie, 1: comparison sort with checkpoint hashes, 2: exact comparisons only,
   // 3: the previous order with this call's new paths merged in
@@ -747,31 +765,31 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
     if (mode == 0) launch_trie_sort(ta, t->d, s);
     else if (mode == 3) launch_merge_order(run, t->order.as<uint32_t>(), t->lcp.as<uint32_t>(), t->d, merge_scratch.as<uint32_t>(), s);
     else launch_sort(run, s);
-    tm.mark(4, s);
     if (N > 0 && side != s) AGG_TRY(hipStreamWaitEvent(s, summed.ev, 0));  // launch_canon folds the sums
     launch_canon(run, s);
     AGG_TRY(hipGetLastError());
-    tm.mark(5, s);
-    AGG_TRY(hipMemcpyAsync(hs, cursor.p, 128, hipMemcpyDeviceToHost, s));
+    launch_finish(ctl.as<unsigned long long>(), hs, s);  // (from the stamps on)
+    AGG_TRY(hipGetLastError());
     AGG_TRY(spin_sync(s));
-    const bool trie_failed = mode == 0 && hs[8 + kTrieCtrFail] != 0;
-    if (!hs[3] && !trie_failed) {  // order verified strictly increasing
+    const bool trie_failed = mode == 0 && hs[kCtlTrie - kCtlStamps + kTrieCtrFail] != 0;
+    if (!hs[kCtlCanon - kCtlStamps + 1] && !trie_failed) {  // order verified strictly increasing
       if (run.order != ca.order) std::swap(order, order_tmp);
       break;
     }
     if (mode == 2) return undo(fail(CCT_EDEVICE, "canonical order failed exact verification"));
     if (mode == 0 && env_int("CCT_TEST_REQUIRE_TRIE", 0)) return undo(fail(CCT_EDEVICE, "block-trie order not usable"));
     mode = 2;  // a hash collision misled the fast order: sort again with exact compares
-    AGG_TRY(hipMemsetAsync(cursor.p, 0, ctl_bytes, s));
+    AGG_TRY(hipMemsetAsync(ctl.as<unsigned long long>() + kCtlCanon, 0, (ctl_words - kCtlCanon) * 8, s));
   }
-  tm.collect(N > 0);
+  side_guard.idle = true;  // (the node arrays waited for the side stream's last work)
+  collect_timings(hs, t->device, N > 0);
   if (keep_stats && ts.ok) g_stats_ms = ts.span(0, 1);
 
   // ---- commit -------------------------------------------------------------------------------
   t->store_used += (int64_t)new_store;
   t->d = D;
   t->sum_len = sum_len;
-  t->u = (int64_t)hs[2];
+  t->u = (int64_t)hs[kCtlCanon - kCtlStamps];
   t->parent = std::move(n_parent); t->frame = std::move(n_frame); t->depth = std::move(n_depth);
   t->subend = std::move(n_subend);
   t->bu_k = -1;        // the bottom-up view of the old tree is stale
@@ -807,11 +825,7 @@ cct_status build_tree(const cct_paths *events, void *hip_stream, bool stats, cct
   cap = (int64_t)pow2_at_least((uint64_t)std::max<int64_t>(cap, 16));
   if (!t->slot.alloc(cap * sizeof(Slot))) { delete t; return fail(CCT_ENOMEM, "device allocation failed"); }
   t->cap = (uint64_t)cap;
-  if (hipMemsetAsync(t->slot.p, 0xFF, cap * sizeof(Slot), s) != hipSuccess) {
-    (void)hipGetLastError();
-    delete t;
-    return fail(CCT_EDEVICE, "memset failed");
-  }
+  t->fresh = true;
   st = aggregate(t, events, s);
   if (st) { delete t; return st; }
   *out = t;
@@ -985,9 +999,11 @@ cct_status compute_bottom_up(cct_tree *t, hipStream_t s) {
   AggStage st_e{}, st_i{};
   if (!f_out.alloc(G * 4) || !e_out.alloc(G * m * 8) || !i_out.alloc(G * m * 8))
     return fail(CCT_ENOMEM, "device allocation failed");
-  cct_status st = setup_stage(m, (uint64_t)G, agg_grid, cnt_e, keys_e, sums_e, st_e, s);
-  if (!st) st = setup_stage(m, (uint64_t)G, agg_grid, cnt_i, keys_i, sums_i, st_i, s);
+  cct_status st = setup_stage(m, (uint64_t)G, agg_grid, cnt_e, keys_e, sums_e, st_e);
+  if (!st) st = setup_stage(m, (uint64_t)G, agg_grid, cnt_i, keys_i, sums_i, st_i);
   if (st) return st;
+  if (st_e.nbuckets) HIP_TRY(hipMemsetAsync(st_e.count, 0, st_e.nbuckets * 4, s));
+  if (st_i.nbuckets) HIP_TRY(hipMemsetAsync(st_i.count, 0, st_i.nbuckets * 4, s));
   HIP_TRY(hipMemsetAsync(e_out.p, 0, G * m * 8, s));
   HIP_TRY(hipMemsetAsync(i_out.p, 0, G * m * 8, s));
   launch_bu_frames(K, gstart.as<int64_t>(), G, f_out.as<uint32_t>(), s);

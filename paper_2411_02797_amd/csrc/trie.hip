@@ -54,6 +54,7 @@ __device__ inline uint32_t block_frames(uint32_t depth) { return ((depth - 1) & 
 
 // empty the node table; zero the bucket counts and the root's child count
 __global__ void clear_kernel(TrieArgs a) {
+  stamp(a.stamps + kStampOrder);
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < (int64_t)a.cap) a.tkey[i] = 0;
   if (i < a.large_cap * kMaxBuckets) { a.bcnt[i] = 0; a.bsum[i] = 0; }

@@ -857,6 +857,22 @@ __global__ __launch_bounds__(256, M <= 4 ? 7 : 5) void emit_kernel(CanonArgs a) 
   }
 }
 
+// Array blockIdx.y: 16 bytes per lane and step where both ends allow it.  The copies are not
+// read again here (non-temporal).
+__global__ __launch_bounds__(256) void copy_kernel(CopyArgs a) {
+  const uint32_t *src = a.src[blockIdx.y];
+  uint32_t *dst = a.dst[blockIdx.y];
+  const uint64_t n = a.words[blockIdx.y], t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x,
+                 stride = (uint64_t)gridDim.x * blockDim.x;
+  uint64_t done = 0;
+  if ((((uintptr_t)src | (uintptr_t)dst) & 15) == 0) {
+    done = n / 4 * 4;
+    for (uint64_t i = t; i < n / 4; i += stride)
+      __builtin_nontemporal_store(__builtin_nontemporal_load((const u32x4 *)src + i), (u32x4 *)dst + i);
+  }
+  for (uint64_t i = done + t; i < n; i += stride) dst[i] = src[i];
+}
+
 inline unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1) / per); }
 
 }  // namespace
@@ -931,6 +947,13 @@ void launch_scan(const uint64_t *in, int64_t rows, int C, uint64_t *blk, uint64_
   } else {
     (void)hipMemsetAsync(out, 0, sizeof(uint64_t) * C, s);
   }
+}
+
+void launch_copy(const CopyArgs &a, hipStream_t s) {
+  uint64_t most = 1;
+  for (int i = 0; i < a.n; ++i) most = std::max(most, a.words[i]);
+  const unsigned grid = (unsigned)std::min<uint64_t>((most + 1023) / 1024, 4096);
+  hipLaunchKernelGGL(copy_kernel, dim3(grid, a.n), dim3(256), 0, s, a);
 }
 
 int64_t min_level_words(int64_t n, CanonArgs &a) {

@@ -332,6 +332,14 @@ void launch_trie_sort(const TrieArgs &a, int64_t d_old, hipStream_t s);
 // 1 and up as the result, and set_min_levels points mins at them (level 0 at lcp).
 int64_t min_level_words(int64_t n, CanonArgs &a);
 void set_min_levels(CanonArgs &a, uint32_t *words);
+// n arrays of 4-byte words copied in one launch
+struct CopyArgs {
+  int n;
+  const uint32_t *src[5];
+  uint32_t *dst[5];
+  uint64_t words[5];
+};
+void launch_copy(const CopyArgs &a, hipStream_t s);
 void launch_canon(const CanonArgs &a, hipStream_t s);  // lcp, sums, minima, emission
 
 struct alignas(32) PathRec {  // the path at a canonical position

@@ -146,10 +146,11 @@ int cu_count() {
   return cached[dev];
 }
 
-// pinned host staging for small device -> host reads
+// pinned host staging for small device -> host reads (kernels write it directly)
 unsigned long long *host_scratch() {
   thread_local unsigned long long *h = nullptr;
-  if (!h && hipHostMalloc((void **)&h, 64 * sizeof(unsigned long long), hipHostMallocDefault) != hipSuccess) {
+  if (!h && hipHostMalloc((void **)&h, 64 * sizeof(unsigned long long),
+                          hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
     (void)hipGetLastError();
     h = nullptr;
   }
@@ -230,6 +231,16 @@ struct Event {
     if (ev) (void)hipEventDestroy(ev);
   }
 };
+
+// whether p is memory of device dev
+bool on_device(const void *p, int dev) {
+  hipPointerAttribute_t at;
+  if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return at.type == hipMemoryTypeDevice && at.device == dev;
+}
 
 uint64_t pow2_at_least(uint64_t x) {
   uint64_t p = 1;
@@ -1275,11 +1286,27 @@ cct_status cct_export(const cct_tree *tree, void *hip_stream, uint32_t *parent, 
   if (!tree) return fail(CCT_EINVAL, "tree is NULL");
   hipStream_t s = (hipStream_t)hip_stream;
   const size_t U = (size_t)tree->u, m = (size_t)tree->m;
-  if (parent) HIP_TRY(hipMemcpyAsync(parent, tree->parent.p, U * 4, hipMemcpyDefault, s));
-  if (frame) HIP_TRY(hipMemcpyAsync(frame, tree->frame.p, U * 4, hipMemcpyDefault, s));
-  if (depth) HIP_TRY(hipMemcpyAsync(depth, tree->depth.p, U * 4, hipMemcpyDefault, s));
-  if (excl) HIP_TRY(hipMemcpyAsync(excl, tree->excl.p, U * m * 8, hipMemcpyDefault, s));
-  if (incl) HIP_TRY(hipMemcpyAsync(incl, tree->incl.p, U * m * 8, hipMemcpyDefault, s));
+  int dev = -1;
+  (void)hipGetDevice(&dev);
+  // arrays on the tree's device take one launch; anything else (host memory, another
+  // device) a copy each
+  CopyArgs c{};
+  const void *src[5] = {tree->parent.p, tree->frame.p, tree->depth.p, tree->excl.p, tree->incl.p};
+  void *dst[5] = {parent, frame, depth, excl, incl};
+  const size_t bytes[5] = {U * 4, U * 4, U * 4, U * m * 8, U * m * 8};
+  bool local = dev == tree->device;
+  for (int i = 0; i < 5; ++i) {
+    if (!dst[i]) continue;
+    c.src[c.n] = (const uint32_t *)src[i]; c.dst[c.n] = (uint32_t *)dst[i]; c.words[c.n++] = bytes[i] / 4;
+    local = local && ((uintptr_t)dst[i] & 3) == 0 && on_device(dst[i], dev);
+  }
+  if (local) {
+    if (c.n) launch_copy(c, s);
+    HIP_TRY(hipGetLastError());
+  } else {
+    for (int i = 0; i < 5; ++i)
+      if (dst[i]) HIP_TRY(hipMemcpyAsync(dst[i], src[i], bytes[i], hipMemcpyDefault, s));
+  }
   HIP_TRY(spin_sync(s));
   return CCT_OK;
 }

@@ -454,22 +454,19 @@ struct FilterArgs {
 };
 constexpr int kFilterTile = 2048;  // nodes per tile of the two passes
 int64_t filter_tiles(int64_t u);
-// mask [filter_tiles(U) * kFilterTile / 64] (bit per node), count [filter_tiles(U)]
-void launch_filter_mask(const FilterArgs &a, uint64_t *mask, uint32_t *count, hipStream_t s);
-// pos [tiles + 1]: exclusive scan of count, pos[tiles] = all matches
-void launch_filter_scan(const uint32_t *count, int64_t tiles, uint64_t *pos, hipStream_t s);
-// writes the first `capacity` matches to out
-void launch_filter_write(int64_t u, const uint64_t *mask, const uint64_t *pos, int64_t capacity, int64_t *out,
-                         hipStream_t s);
 // The filter that allocates nothing keeps its mask, counts and offsets in a static device
 // array of kFilterStaticBytes per GPU, enough for kFilterStaticTiles tiles.
 constexpr int64_t kFilterStaticTiles = 15360;  // trees of up to 31,457,280 nodes
 constexpr size_t kFilterStaticBytes = 4u << 20;
 struct FilterScratch {
-  uint64_t *mask;   // [tiles * kFilterTile / 64]
-  uint32_t *count;  // [tiles]
-  uint64_t *pos;    // [tiles + 1]
+  uint64_t *mask;   // [tiles * kFilterTile / 64], a bit per node
+  uint32_t *count;  // [tiles] matches
+  uint64_t *pos;    // [tiles + 1] their exclusive scan, where it is needed
 };
+// writes the first `capacity` matches to out, their number to *total (device or pinned host
+// memory) and, if times is not null, the clock at the start and the end to times[0..2)
+void launch_filter(const FilterArgs &a, const FilterScratch &f, int64_t capacity, int64_t *out,
+                   unsigned long long *total, unsigned long long *times, hipStream_t s);
 // Device address of the current device's static array (looked up once per device), or
 // nullptr if the lookup failed; and the array's parts at that address.
 void *filter_static_scratch();

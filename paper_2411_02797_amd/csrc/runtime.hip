@@ -1089,20 +1089,6 @@ cct_status filter_args(const cct_tree *tree, const cct_filter_spec *spec, int64_
   return CCT_OK;
 }
 
-// The filter's three passes over the given scratch; the match count is copied to *dst
-// (host memory) and the stream synchronised.
-cct_status run_filter(const FilterArgs &a, const FilterScratch &f, int64_t capacity, int64_t *node_ids,
-                      unsigned long long *dst, hipStream_t s) {
-  const int64_t T = filter_tiles(a.u);
-  launch_filter_mask(a, f.mask, f.count, s);
-  launch_filter_scan(f.count, T, f.pos, s);
-  launch_filter_write(a.u, f.mask, f.pos, capacity, node_ids, s);
-  HIP_TRY(hipGetLastError());
-  HIP_TRY(hipMemcpyAsync(dst, f.pos + T, 8, hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipStreamSynchronize(s));  // blocking: cct_filter_noalloc shares this path and creates no event
-  return CCT_OK;
-}
-
 }  // namespace
 
 extern "C" {
@@ -1122,12 +1108,10 @@ cct_status cct_filter(const cct_tree *tree, const cct_filter_spec *spec, void *h
   if (!mask.alloc(T * (kFilterTile / 64) * 8) || !count.alloc(T * 4) || !pos.alloc((T + 1) * 8))
     return fail(CCT_ENOMEM, "device allocation failed");
   FilterScratch f{mask.as<uint64_t>(), count.as<uint32_t>(), pos.as<uint64_t>()};
-  Timer tm;
-  tm.mark(0, s);
-  st = run_filter(a, f, capacity, node_ids, hs, s);
-  if (st) return st;
-  tm.mark(1, s);
-  g_filter_ms = tm.ok ? tm.span(0, 1) : 0.0;
+  launch_filter(a, f, capacity, node_ids, hs, hs + 1, s);
+  HIP_TRY(hipGetLastError());
+  HIP_TRY(spin_sync(s));
+  g_filter_ms = hs[2] > hs[1] ? (double)(hs[2] - hs[1]) / clock_ticks_per_ms(tree->device) : 0.0;
   *n_matches = (int64_t)hs[0];
   return CCT_OK;
 }
@@ -1142,9 +1126,14 @@ cct_status cct_filter_noalloc(const cct_tree *tree, const cct_filter_spec *spec,
     return fail(CCT_EOVERFLOW, "tree has more nodes than cct_filter_noalloc's scratch holds (31,457,280)");
   void *base = filter_static_scratch();
   if (!base) return fail(CCT_EDEVICE, "address of the static filter scratch not available");
-  unsigned long long k = 0;  // pageable: no pinned staging is allocated
-  st = run_filter(a, filter_static_layout(base), capacity, node_ids, &k, (hipStream_t)hip_stream);
-  if (st) return st;
+  hipStream_t s = (hipStream_t)hip_stream;
+  const FilterScratch f = filter_static_layout(base);
+  unsigned long long *total = reinterpret_cast<unsigned long long *>(f.pos + filter_tiles(a.u));
+  launch_filter(a, f, capacity, node_ids, total, nullptr, s);
+  HIP_TRY(hipGetLastError());
+  unsigned long long k = 0;  // pageable: no pinned staging is allocated, nor an event for the wait
+  HIP_TRY(hipMemcpyAsync(&k, total, 8, hipMemcpyDeviceToHost, s));
+  HIP_TRY(hipStreamSynchronize(s));
   *n_matches = (int64_t)k;
   return CCT_OK;
 }

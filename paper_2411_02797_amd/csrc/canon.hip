@@ -462,7 +462,7 @@ __global__ __launch_bounds__(256) void scan_reduce_kernel(const uint64_t *in, in
   __shared__ uint64_t part[4];
   const int tid = threadIdx.x;
   const int64_t r0 = (int64_t)blockIdx.x * kScanRows;
-  for (int c = 0; c < C; ++c) {
+  for (int c = blockIdx.y; c < C; c += gridDim.y) {
     uint64_t s = 0;
     for (int64_t r = r0 + tid; r < min(rows, r0 + kScanRows); r += 256) s += in[r * C + c];
     for (int o = 32; o > 0; o >>= 1) {
@@ -515,7 +515,7 @@ __global__ __launch_bounds__(256) void scan_final_kernel(const uint64_t *in, int
   __shared__ uint64_t pre;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t r0 = (int64_t)blockIdx.x * kScanRows + tid * 4;
-  for (int c = 0; c < C; ++c) {
+  for (int c = blockIdx.y; c < C; c += gridDim.y) {
     if (direct) {  // sum of the earlier blocks' sums of column c
       uint64_t x = 0;
       for (int64_t j = tid; j < (int64_t)blockIdx.x; j += 256) x += blk[j * C + c];
@@ -941,9 +941,11 @@ void launch_scan(const uint64_t *in, int64_t rows, int C, uint64_t *blk, uint64_
   if (rows > 0) {
     const int64_t nblk = (rows + kScanRows - 1) / kScanRows;
     const int direct = nblk <= kScanDirectBlocks ? 1 : 0;
-    hipLaunchKernelGGL(scan_reduce_kernel, dim3((unsigned)nblk), dim3(256), 0, s, in, rows, C, blk);
+    // few blocks: the columns side by side as well (each then reads the rows for itself)
+    const unsigned cols = nblk <= 256 ? (unsigned)C : 1u;
+    hipLaunchKernelGGL(scan_reduce_kernel, dim3((unsigned)nblk, cols), dim3(256), 0, s, in, rows, C, blk);
     if (!direct) hipLaunchKernelGGL(scan_blocks_kernel, dim3(1), dim3(256), 0, s, blk, nblk, C, out, rows);
-    hipLaunchKernelGGL(scan_final_kernel, dim3((unsigned)nblk), dim3(256), 0, s, in, rows, C, blk, out, direct);
+    hipLaunchKernelGGL(scan_final_kernel, dim3((unsigned)nblk, cols), dim3(256), 0, s, in, rows, C, blk, out, direct);
   } else {
     (void)hipMemsetAsync(out, 0, sizeof(uint64_t) * C, s);
   }

@@ -720,6 +720,8 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
 
   Timer ts;
   g_stats_ms = 0;
+  Event published_ev, kept;  // order the statistics after the publish, the call's end after them
+  if (keep_stats && side != s && (!published_ev.ev || !kept.ev)) return undo(fail(CCT_EDEVICE, "event creation failed"));
 
   // ---- publish new paths ----------------------------------------------------------------
   if (n_new) {
@@ -739,12 +741,19 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
     launch_publish(pa, s);
   }
   if (keep_stats) {  // the batch's samples into the fresh path arrays (new paths start empty)
-    ts.mark(0, s);
+    // beside the ordering, which needs none of them (4,194,304 events of 2 metrics and
+    // their statistics: 1,369 us on the caller's stream, 1,209 beside)
+    if (side != s) {
+      AGG_TRY(hipEventRecord(published_ev.ev, s));
+      AGG_TRY(hipStreamWaitEvent(side, published_ev.ev, 0));
+    }
+    ts.mark(0, side);
     PathStats ps{ncnt.as<uint64_t>(), nmin.as<uint64_t>(), nsq.as<uint64_t>()};
-    launch_stats_prepare(D, t->d, m, t->pslot.as<uint32_t>(), sg_pos.as<uint32_t>(), ps, s);
+    launch_stats_prepare(D, t->d, m, t->pslot.as<uint32_t>(), sg_pos.as<uint32_t>(), ps, side);
     launch_stats_agg(slot_of.as<uint32_t>(), sg_pos.as<uint32_t>(), p->metrics, N, m, D, st_grid, ps, sst,
-                     sg_blk.as<uint64_t>(), s);
-    ts.mark(1, s);
+                     sg_blk.as<uint64_t>(), side);
+    ts.mark(1, side);
+    if (side != s) AGG_TRY(hipEventRecord(kept.ev, side));
   }
   AGG_TRY(hipGetLastError());
   // test setting: fail once everything is published, to check that the
@@ -779,6 +788,7 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
     if (N > 0 && side != s) AGG_TRY(hipStreamWaitEvent(s, summed.ev, 0));  // launch_canon folds the sums
     launch_canon(run, s);
     AGG_TRY(hipGetLastError());
+    if (keep_stats && side != s) AGG_TRY(hipStreamWaitEvent(s, kept.ev, 0));
     launch_finish(ctl.as<unsigned long long>(), hs, s);  // (from the stamps on)
     AGG_TRY(hipGetLastError());
     AGG_TRY(spin_sync(s));

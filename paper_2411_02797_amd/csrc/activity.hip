@@ -17,18 +17,18 @@
 //   3. corr_unique_kernel: every registered ID must find its own entry (a repeated ID
 //      finds the entry of one of its copies only, so repeats are reported whatever the
 //      order of the stores was);
-//   4. corr_join_kernel: every record looks up its ID; it gets the registry index of
-//      its path (or none: counted as unmatched) and stores its own index + 1 into the
-//      path's ref word (any record of the path may win: that one owns the path's sums);
-//   5. corr_sums_kernel: every owning record stores its metrics as its path's sums and
-//      lists the workgroup's other matched records (an LDS counter per workgroup, its
-//      own stripe of the list); corr_adds_kernel then adds those records' metrics with
-//      atomics (a path is usually named by one record: few atomics, and no zero fill);
-//   6. compaction: a scan over (referenced, length) places the referenced paths;
+//   4. corr_join_kernel: every record looks up its ID (none: counted as unmatched) and
+//      claims the path's ref word with its own index + 1; the claimer owns the path's sums,
+//      any other record of the path is listed (an LDS counter per workgroup, its own stripe
+//      of the list);
+//   5. corr_gather_kernel: every referenced path takes its owner's metrics as its sums and is
+//      counted; corr_adds_kernel then adds the listed records' metrics with atomics (a path
+//      is usually named by one record: few atomics, and no zero fill);
+//   6. compaction, unless every registered path is referenced (then the registry itself is
+//      the batch and nothing is copied): a scan over (referenced, length) places the referenced paths;
 //      compact_meta_kernel writes their batch offsets, source starts and summed metrics,
-//      and compact_copy_kernel copies their frames (one thread per 16 batch frames).
-//      When every registered path is referenced, the registry itself is the batch and
-//      nothing is copied.  The caller merges the batch like any other.
+//      and compact_copy_kernel copies their frames (one thread per 16 batch frames).  The
+//      caller merges the batch like any other.
 // Merging that batch equals merging one event per matched record with the registered
 // path: the tree's sums are additive over events with the same path.
 #include <algorithm>
@@ -73,6 +73,11 @@ __device__ inline int64_t dense_find(const ActivityArgs &a, uint64_t key) {
 
 __device__ inline int64_t reg_find(const ActivityArgs &a, uint64_t key) {
   return a.dense ? dense_find(a, key) : corr_find(a, key);
+}
+
+__global__ __launch_bounds__(64) void corr_start_kernel(ActivityArgs a) {
+  stamp(a.ctr + kActCtrStart);
+  if (threadIdx.x < kActCtrStart) a.ctr[threadIdx.x] = threadIdx.x == kActCtrMin ? ~0ull : 0ull;
 }
 
 // min / max of the registered IDs: per workgroup, then one atomic pair per workgroup
@@ -132,17 +137,33 @@ __global__ void corr_unique_kernel(ActivityArgs a) {
   if (reg_find(a, a.reg_corr[i]) != i) atomicOr(&a.ctr[kActCtrError], (unsigned long long)kActRepeatedId);
 }
 
-// Grid-stride over the records; the unmatched count is summed per workgroup and added
-// with one atomic per workgroup (the counter is a single address).
+// Empty table and ref words, 16 bytes per lane and store (both are padded to 16 bytes).
+__global__ __launch_bounds__(256) void corr_clear_kernel(uint4 *table, uint64_t n_table, uint4 *ref, uint64_t n_ref) {
+  const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (uint64_t)gridDim.x * blockDim.x;
+  for (uint64_t i = t; i < n_table; i += stride) table[i] = make_uint4(0, 0, 0, 0);
+  for (uint64_t i = t; i < n_ref; i += stride) ref[i] = make_uint4(0, 0, 0, 0);
+}
+
+// Grid-stride over the records.  The first record to claim a path's ref word owns it; the
+// others go with their path into this workgroup's stripe of `list` (stripe b starts at
+// b * stride, stride >= the records one workgroup visits), their number into cnt[b].  The
+// unmatched count is summed per workgroup and added with one atomic per workgroup.  (With the
+// owner named by the last store, a second pass over the records had to find it: 40 + 77 + 23
+// us for 1,174,405 records of 4 metrics; join, gather and adds 63 + 37 +
+// 22 us so.)
 constexpr int kJoinThreads = 256;
-__global__ __launch_bounds__(kJoinThreads) void corr_join_kernel(ActivityArgs a) {
+__global__ __launch_bounds__(kJoinThreads) void corr_join_kernel(ActivityArgs a, uint64_t *list, int64_t stride,
+                                                                 uint32_t *cnt) {
   __shared__ unsigned long long wsum[kJoinThreads / 64];
+  __shared__ uint32_t n;
+  if (threadIdx.x == 0) n = 0;
+  __syncthreads();
   unsigned long long unmatched = 0;
+  uint64_t *mine = list + (int64_t)blockIdx.x * stride;
   for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < a.n_rec; r += (int64_t)gridDim.x * blockDim.x) {
     const int64_t f = reg_find(a, a.rec_corr[r]);
-    a.rec_reg[r] = f < 0 ? kNoSlot : (uint32_t)f;
     if (f < 0) ++unmatched;
-    else a.ref[f] = (uint32_t)(r + 1);  // the last store names the path's owner
+    else if (atomicCAS(&a.ref[f], 0u, (uint32_t)(r + 1)) != 0u) mine[atomicAdd(&n, 1u)] = ((uint64_t)f << 32) | (uint64_t)r;
   }
   for (int o = 32; o > 0; o >>= 1) unmatched += __shfl_xor(unmatched, o, 64);
   if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = unmatched;
@@ -151,43 +172,47 @@ __global__ __launch_bounds__(kJoinThreads) void corr_join_kernel(ActivityArgs a)
     unsigned long long t = 0;
     for (int w = 0; w < kJoinThreads / 64; ++w) t += wsum[w];
     if (t) atomicAdd(&a.ctr[kActCtrUnmatched], t);
+    cnt[blockIdx.x] = n;
   }
 }
 
-// Sums of each referenced path, first part: the owning record stores its metric row;
-// every other matched record is listed in this workgroup's stripe of `list` (stripe b
-// starts at b * stride, stride >= the records one workgroup visits), its count in
-// cnt[b].
-constexpr int kSumThreads = 256;
-__global__ __launch_bounds__(kSumThreads) void corr_sums_kernel(ActivityArgs a, const uint64_t *metrics, int32_t m,
-                                                                uint64_t *sums, uint32_t *list, int64_t stride,
-                                                                uint32_t *cnt) {
-  __shared__ uint32_t n;
-  if (threadIdx.x == 0) n = 0;
-  __syncthreads();
-  uint32_t *mine = list + (int64_t)blockIdx.x * stride;
-  for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < a.n_rec; r += (int64_t)gridDim.x * blockDim.x) {
-    const uint32_t f = a.rec_reg[r];
-    if (f == kNoSlot) continue;
-    if (a.ref[f] == (uint32_t)(r + 1)) {
-      for (int j = 0; j < m; ++j) sums[(int64_t)f * m + j] = metrics[r * m + j];
-    } else {
-      mine[atomicAdd(&n, 1u)] = (uint32_t)r;
-    }
+// Sums of each referenced path, first part: its owner's row (read from anywhere, written in
+// order); the referenced paths are counted.
+template <int M>
+__global__ __launch_bounds__(kJoinThreads) void corr_gather_kernel(ActivityArgs a, const uint64_t *metrics,
+                                                                   uint64_t *sums) {
+  __shared__ uint32_t wsum[kJoinThreads / 64];
+  uint32_t used = 0;
+  for (int64_t f = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; f < a.n_reg; f += (int64_t)gridDim.x * blockDim.x) {
+    const uint32_t r = a.ref[f];
+    if (!r) continue;
+    ++used;
+    const uint64_t *row = metrics + (int64_t)(r - 1) * M;
+    uint64_t v[M];
+#pragma unroll
+    for (int j = 0; j < M; ++j) v[j] = row[j];
+#pragma unroll
+    for (int j = 0; j < M; ++j) sums[f * M + j] = v[j];
   }
+  for (int o = 32; o > 0; o >>= 1) used += __shfl_xor(used, o, 64);
+  if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = used;
   __syncthreads();
-  if (threadIdx.x == 0) cnt[blockIdx.x] = n;
+  if (threadIdx.x == 0) {
+    uint32_t t = 0;
+    for (int w = 0; w < kJoinThreads / 64; ++w) t += wsum[w];
+    if (t) atomicAdd(&a.ctr[kActCtrUsed], (unsigned long long)t);
+  }
 }
 
 // Second part (after the first has completed): the listed records add their rows.
-__global__ __launch_bounds__(kSumThreads) void corr_adds_kernel(ActivityArgs a, const uint64_t *metrics, int32_t m,
-                                                                uint64_t *sums, const uint32_t *list, int64_t stride,
-                                                                const uint32_t *cnt) {
-  const uint32_t *mine = list + (int64_t)blockIdx.x * stride;
+__global__ __launch_bounds__(kJoinThreads) void corr_adds_kernel(const uint64_t *metrics, int32_t m, uint64_t *sums,
+                                                                 const uint64_t *list, int64_t stride,
+                                                                 const uint32_t *cnt) {
+  const uint64_t *mine = list + (int64_t)blockIdx.x * stride;
   const uint32_t n = cnt[blockIdx.x];
   for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) {
-    const int64_t r = mine[i];
-    const int64_t f = a.rec_reg[r];
+    const uint64_t e = mine[i];
+    const int64_t r = (int64_t)(uint32_t)e, f = (int64_t)(e >> 32);
     for (int j = 0; j < m; ++j)
       atomicAdd((unsigned long long *)&sums[f * m + j], (unsigned long long)metrics[r * m + j]);
   }
@@ -246,34 +271,43 @@ inline unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1)
 
 void launch_corr_range(const ActivityArgs &a, hipStream_t s) {
   if (a.n_reg <= 0) return;
-  const unsigned grid = (unsigned)std::min<int64_t>(blocks_for(a.n_reg, kRangeThreads), 1024);
+  hipLaunchKernelGGL(corr_start_kernel, dim3(1), dim3(64), 0, s, a);
+  // (two atomics per workgroup on the same words: 28 us for 1,048,576 IDs in 1,024 workgroups,
+  // 14 us in 256)
+  const unsigned grid = (unsigned)std::min<int64_t>(blocks_for(a.n_reg, kRangeThreads), 256);
   hipLaunchKernelGGL(corr_range_kernel, dim3(grid), dim3(kRangeThreads), 0, s, a);
 }
 
-void launch_corr_table(const ActivityArgs &a, hipStream_t s) {
+void launch_corr_table(const ActivityArgs &a, uint64_t table_bytes, hipStream_t s) {
   if (a.n_reg <= 0) return;
+  const uint64_t n_table = (table_bytes + 15) / 16, n_ref = ((uint64_t)a.n_reg * 4 + 15) / 16;
+  const unsigned clear = (unsigned)std::min<uint64_t>((std::max(n_table, n_ref) + 255) / 256, 4096);
+  hipLaunchKernelGGL(corr_clear_kernel, dim3(clear), dim3(256), 0, s, (uint4 *)(a.dense ? (void *)a.dtab : (void *)a.table),
+                     n_table, (uint4 *)a.ref, n_ref);
   hipLaunchKernelGGL(corr_insert_kernel, dim3(blocks_for(a.n_reg, 256)), dim3(256), 0, s, a);
   hipLaunchKernelGGL(corr_unique_kernel, dim3(blocks_for(a.n_reg, 256)), dim3(256), 0, s, a);
 }
 
-void launch_corr_join(const ActivityArgs &a, hipStream_t s) {
-  if (a.n_rec <= 0) return;
-  const unsigned grid = (unsigned)std::min<int64_t>(blocks_for(a.n_rec, kJoinThreads), 2048);
-  hipLaunchKernelGGL(corr_join_kernel, dim3(grid), dim3(kJoinThreads), 0, s, a);
-}
+int64_t corr_join_grid(int64_t n_rec) { return std::max<int64_t>(1, std::min<int64_t>(blocks_for(n_rec, kJoinThreads), 2048)); }
 
-int64_t corr_sums_grid(int64_t n_rec) { return std::max<int64_t>(1, std::min<int64_t>(blocks_for(n_rec, kSumThreads), 4096)); }
-
-void launch_corr_sums(const ActivityArgs &a, const uint64_t *metrics, int32_t m, uint64_t *sums, uint32_t *list,
+void launch_corr_join(const ActivityArgs &a, const uint64_t *metrics, int32_t m, uint64_t *sums, uint64_t *list,
                       uint32_t *cnt, hipStream_t s) {
   if (a.n_rec <= 0) return;
-  const int64_t grid = corr_sums_grid(a.n_rec);
+  const int64_t grid = corr_join_grid(a.n_rec);
   // a workgroup visits at most ceil(n_rec / (grid * threads)) records per thread
-  const int64_t stride = (a.n_rec + grid * kSumThreads - 1) / (grid * kSumThreads) * kSumThreads;
-  hipLaunchKernelGGL(corr_sums_kernel, dim3((unsigned)grid), dim3(kSumThreads), 0, s, a, metrics, m, sums, list,
-                     stride, cnt);
-  hipLaunchKernelGGL(corr_adds_kernel, dim3((unsigned)grid), dim3(kSumThreads), 0, s, a, metrics, m, sums, list,
-                     stride, cnt);
+  const int64_t stride = (a.n_rec + grid * kJoinThreads - 1) / (grid * kJoinThreads) * kJoinThreads;
+  hipLaunchKernelGGL(corr_join_kernel, dim3((unsigned)grid), dim3(kJoinThreads), 0, s, a, list, stride, cnt);
+  const dim3 paths((unsigned)std::min<int64_t>(blocks_for(a.n_reg, kJoinThreads), 2048));
+  switch (m) {
+#define CCT_GATHER_CASE(M) \
+  case M: hipLaunchKernelGGL(corr_gather_kernel<M>, paths, dim3(kJoinThreads), 0, s, a, metrics, sums); break;
+    CCT_GATHER_CASE(1) CCT_GATHER_CASE(2) CCT_GATHER_CASE(3) CCT_GATHER_CASE(4)
+    CCT_GATHER_CASE(5) CCT_GATHER_CASE(6) CCT_GATHER_CASE(7) CCT_GATHER_CASE(8)
+#undef CCT_GATHER_CASE
+    default: break;
+  }
+  hipLaunchKernelGGL(corr_adds_kernel, dim3((unsigned)grid), dim3(kJoinThreads), 0, s, metrics, m, sums, list, stride,
+                     cnt);
 }
 
 void launch_compact_lengths(const ActivityArgs &a, uint64_t *rows, hipStream_t s) {

@@ -141,7 +141,7 @@ struct InitArgs {
   int first;                 // the call's first attempt (stamps its start)
 };
 void launch_init(const InitArgs &a, hipStream_t s);
-// n words of the control block from `from` into pinned host memory; the end is stamped
+// n < 64 words from `from` into pinned host memory, and the clock after them
 void launch_report(const unsigned long long *from, int n, unsigned long long *host, hipStream_t s);
 void launch_finish(unsigned long long *ctl, unsigned long long *host, hipStream_t s);
 
@@ -381,7 +381,8 @@ void launch_query_check(const QueryArgs &a, hipStream_t s);
 void launch_query(const QueryArgs &a, hipStream_t s);
 
 // Correlation-ID join of an activity flush with the registered call paths (activity.hip)
-enum : int32_t { kActCtrError = 0, kActCtrUnmatched = 1, kActCtrMin = 2, kActCtrMax = 3, kActCtrCount = 4 };
+enum : int32_t { kActCtrError = 0, kActCtrUnmatched = 1, kActCtrMin = 2, kActCtrMax = 3, kActCtrUsed = 4,
+                 kActCtrStart = 5, kActCtrCount = 6 };  // (kActCtrStart: the clock at the join's start)
 enum : uint32_t { kActBadOffsets = 1, kActRepeatedId = 2, kActTableFull = 4 };
 struct alignas(16) CorrSlot {
   uint64_t key;    // correlation ID (valid once claim != 0)
@@ -402,17 +403,17 @@ struct ActivityArgs {
   CorrSlot *table;           // [cap]
   int64_t n_rec;             // activity records
   const uint64_t *rec_corr;  // [n_rec]
-  uint32_t *rec_reg;         // [n_rec] registry index of the record's path, kNoSlot if unmatched
   uint32_t *ref;             // [n_reg] 0, or 1 + the index of a record naming the path (its owner)
   unsigned long long *ctr;   // [kActCtrCount]
 };
-void launch_corr_range(const ActivityArgs &a, hipStream_t s);  // min and max registered ID into ctr
-void launch_corr_table(const ActivityArgs &a, hipStream_t s);  // validate offsets, insert, repeated IDs
-void launch_corr_join(const ActivityArgs &a, hipStream_t s);
-// per-path sums of the matched records; list: scratch of corr_sums_grid(n_rec) stripes
-// (n_rec + corr_sums_grid * 256 entries suffice), cnt: [corr_sums_grid(n_rec)]
-int64_t corr_sums_grid(int64_t n_rec);
-void launch_corr_sums(const ActivityArgs &a, const uint64_t *metrics, int32_t m, uint64_t *sums, uint32_t *list,
+void launch_corr_range(const ActivityArgs &a, hipStream_t s);  // counters; min and max registered ID
+// clear the table (table_bytes, room for a multiple of 16) and ref (likewise), validate the
+// offsets, insert, repeated IDs
+void launch_corr_table(const ActivityArgs &a, uint64_t table_bytes, hipStream_t s);
+// join and per-path sums of the matched records; list: scratch of corr_join_grid(n_rec)
+// stripes (n_rec + corr_join_grid * 256 entries suffice), cnt: [corr_join_grid(n_rec)]
+int64_t corr_join_grid(int64_t n_rec);
+void launch_corr_join(const ActivityArgs &a, const uint64_t *metrics, int32_t m, uint64_t *sums, uint64_t *list,
                       uint32_t *cnt, hipStream_t s);
 void launch_compact_lengths(const ActivityArgs &a, uint64_t *rows, hipStream_t s);
 // the batch of referenced paths: offsets [n_paths + 1], frames and metrics; src_start is

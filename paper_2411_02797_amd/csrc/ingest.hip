@@ -837,6 +837,7 @@ __global__ __launch_bounds__(256) void init_kernel(InitArgs a) {
 // (a kernel's stores to pinned memory are 2 us quicker than a copy)
 __global__ __launch_bounds__(64) void report_kernel(const unsigned long long *from, int n, unsigned long long *host) {
   if ((int)threadIdx.x < n) host[threadIdx.x] = from[threadIdx.x];
+  if ((int)threadIdx.x == n) host[n] = (unsigned long long)wall_clock64();
 }
 // stamps, emission and trie words to the host, the call's end among the stamps
 __global__ __launch_bounds__(64) void finish_kernel(unsigned long long *ctl, unsigned long long *host) {

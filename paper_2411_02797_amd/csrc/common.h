@@ -422,23 +422,28 @@ void launch_compact_gather(const ActivityArgs &a, const uint32_t *reg_frames, co
                            const uint64_t *sums, int32_t m, int64_t n_paths, int64_t n_frames, int64_t *off_out,
                            int64_t *src_start, uint32_t *fr_out, uint64_t *met_out, hipStream_t s);
 
-// Bottom-up view (bottomup.hip): stable radix sort of uint32 (key, value) pairs (four
-// passes; hist [256 * radix_blocks(n)], offs [256 * radix_blocks(n) + 1], scan_blk for
-// launch_scan over 256 * radix_blocks(n) rows; result back in keys / vals), exclusive
-// max-scan of uint64 (blk [maxscan_blocks(n)]), and the view's kernels.
+// Bottom-up view (bottomup.hip).  Stable radix sort of uint32 (key, value) pairs by 8 bits
+// a pass: hist [256 * radix_blocks(n)], offs [256 * radix_blocks(n) + 1], scan_blk for
+// launch_scan over as many rows.  launch_radix_bits prepares the first pass and writes the
+// bits in which any keys differ and the time to host[0 .. 1] (bits [radix_blocks(n) + 1]);
+// launch_radix_first completes it with the values 1 .. n.
 int64_t radix_blocks(int64_t n);
-int64_t maxscan_blocks(int64_t n);
-void launch_radix_sort(uint32_t *keys, uint32_t *vals, uint32_t *keys_tmp, uint32_t *vals_tmp, int64_t n,
-                       uint64_t *hist, uint64_t *offs, uint64_t *scan_blk, hipStream_t s);
-void launch_maxscan(const uint64_t *in, int64_t n, uint64_t *blk, uint64_t *out, hipStream_t s);
-void launch_bu_keys(const uint32_t *frame, int64_t n, uint32_t *keys, uint32_t *vals, hipStream_t s);
-void launch_bu_heads(const uint32_t *K, int64_t n, uint64_t *head, hipStream_t s);
-void launch_bu_tag(const uint32_t *V, const uint64_t *head, const uint64_t *gscan, const uint32_t *subend, int64_t n,
-                   uint64_t *tag, int64_t *gstart, hipStream_t s);
-// slot_ex / slot_in: [n + 1] in node order (the root gets kNoSlot)
-void launch_bu_slots(const uint32_t *V, const uint64_t *head, const uint64_t *gscan, const uint64_t *mx, int64_t n,
-                     uint32_t *slot_ex, uint32_t *slot_in, hipStream_t s);
-void launch_bu_frames(const uint32_t *K, const int64_t *gstart, int64_t G, uint32_t *frames, hipStream_t s);
+void launch_radix_bits(const uint32_t *keys, int64_t n, uint64_t *hist, unsigned long long *bits,
+                       unsigned long long *host, hipStream_t s);
+void launch_radix_first(const uint32_t *keys, int64_t n, const uint64_t *hist, uint64_t *offs, uint64_t *scan_blk,
+                        uint32_t *keys_out, uint32_t *vals_out, hipStream_t s);
+void launch_radix_pass(const uint32_t *keys, const uint32_t *vals, int64_t n, int shift, uint64_t *hist, uint64_t *offs,
+                       uint64_t *scan_blk, uint32_t *keys_out, uint32_t *vals_out, hipStream_t s);
+// The view of n > 0 nodes sorted by frame (K, V): group heads per tile [bu_tiles(n)]; tags [n]
+// and the exclusive max-scan of the tiles' largest, blk [bu_tiles(n)] (first: scan of heads);
+// frames [G], ex and in [G][m].
+int64_t bu_tiles(int64_t n);
+void launch_bu_heads(const uint32_t *K, int64_t n, uint64_t *heads, hipStream_t s);
+void launch_bu_tag(const uint32_t *K, const uint32_t *V, const uint64_t *first, const uint32_t *subend, int64_t n,
+                   uint64_t *tag, uint64_t *blk, hipStream_t s);
+void launch_bu_sums(const uint32_t *K, const uint32_t *V, const uint64_t *tag, const uint64_t *blk, const uint64_t *excl,
+                    const uint64_t *incl, int64_t n, int64_t G, int32_t m, uint32_t *frames, uint64_t *ex, uint64_t *in,
+                    hipStream_t s);
 
 // Ratio filters over the tree's nodes (filter.hip)
 enum : int32_t { kDenOne = 0, kDenMetric = 1, kDenRoot = 2 };

@@ -979,7 +979,6 @@ namespace {
 // on failure.
 cct_status compute_bottom_up(cct_tree *t, hipStream_t s) {
   const int64_t n = t->u - 1;  // nodes other than the root
-  const int64_t U = t->u;
   const int32_t m = t->m;
   unsigned long long *hs = host_scratch();
   if (!hs) return fail(CCT_ENOMEM, "pinned host allocation failed");
@@ -987,54 +986,51 @@ cct_status compute_bottom_up(cct_tree *t, hipStream_t s) {
     t->bu_k = 0;
     return CCT_OK;
   }
-  const int64_t rb = radix_blocks(n), hist_rows = 256 * rb;
-  const int64_t scan_rows = std::max<int64_t>(hist_rows, n);
-  Buf keys, vals, keys_t, vals_t, hist, offs, scan_blk, head, gscan, tag, mx, ms_blk, gstart, slot_ex, slot_in;
+  const int64_t rb = radix_blocks(n), hist_rows = 256 * rb, tiles = bu_tiles(n);
+  const int64_t scan_rows = std::max<int64_t>(hist_rows, tiles);
+  Buf keys, vals, keys_t, vals_t, hist, offs, bits, scan_blk, heads, first, tag, blk;
   if (!keys.alloc(n * 4) || !vals.alloc(n * 4) || !keys_t.alloc(n * 4) || !vals_t.alloc(n * 4) ||
-      !hist.alloc(hist_rows * 8) || !offs.alloc((hist_rows + 1) * 8) || !scan_blk.alloc((scan_rows / 1024 + 2) * 8) ||
-      !head.alloc(n * 8) || !gscan.alloc((n + 1) * 8) || !tag.alloc(n * 8) || !mx.alloc(n * 8) ||
-      !ms_blk.alloc((maxscan_blocks(n) + 1) * 8) || !gstart.alloc((n + 1) * 8) || !slot_ex.alloc(U * 4) ||
-      !slot_in.alloc(U * 4))
+      !hist.alloc(hist_rows * 8) || !offs.alloc((hist_rows + 1) * 8) || !bits.alloc((rb + 1) * 8) ||
+      !scan_blk.alloc((scan_rows / 1024 + 2) * 8) || !heads.alloc(tiles * 8) || !first.alloc((tiles + 1) * 8) ||
+      !tag.alloc(n * 8) || !blk.alloc(tiles * 8))
     return fail(CCT_ENOMEM, "device allocation failed");
-  Timer tm;
-  tm.mark(0, s);
-  uint32_t *K = keys.as<uint32_t>(), *V = vals.as<uint32_t>();
-  launch_bu_keys(t->frame.as<uint32_t>(), n, K, V, s);
-  launch_radix_sort(K, V, keys_t.as<uint32_t>(), vals_t.as<uint32_t>(), n, hist.as<uint64_t>(), offs.as<uint64_t>(),
-                    scan_blk.as<uint64_t>(), s);
-  launch_bu_heads(K, n, head.as<uint64_t>(), s);
-  launch_scan(head.as<uint64_t>(), n, 1, scan_blk.as<uint64_t>(), gscan.as<uint64_t>(), s);
-  launch_bu_tag(V, head.as<uint64_t>(), gscan.as<uint64_t>(), t->subend.as<uint32_t>(), n, tag.as<uint64_t>(),
-                gstart.as<int64_t>(), s);
-  launch_maxscan(tag.as<uint64_t>(), n, ms_blk.as<uint64_t>(), mx.as<uint64_t>(), s);
-  launch_bu_slots(V, head.as<uint64_t>(), gscan.as<uint64_t>(), mx.as<uint64_t>(), n, slot_ex.as<uint32_t>(),
-                  slot_in.as<uint32_t>(), s);
+  Event sorted_by, counted;  // the host has what it waits for while the device goes on
+  if (!sorted_by.ev || !counted.ev) return fail(CCT_EDEVICE, "event creation failed");
+  const uint32_t *frame = t->frame.as<uint32_t>() + 1;
+  uint32_t *K = keys.as<uint32_t>(), *V = vals.as<uint32_t>(), *K2 = keys_t.as<uint32_t>(), *V2 = vals_t.as<uint32_t>();
+  launch_radix_bits(frame, n, hist.as<uint64_t>(), bits.as<unsigned long long>(), hs, s);
+  HIP_TRY(hipEventRecord(sorted_by.ev, s));
+  launch_radix_first(frame, n, hist.as<uint64_t>(), offs.as<uint64_t>(), scan_blk.as<uint64_t>(), K, V, s);
   HIP_TRY(hipGetLastError());
-  HIP_TRY(hipMemcpyAsync(hs, gscan.as<uint64_t>() + n, 8, hipMemcpyDeviceToHost, s));
-  HIP_TRY(spin_sync(s));
-  const int64_t G = (int64_t)hs[0];
-  // per-group sums: exclusive sums of every node, inclusive sums of the topmost ones
-  Buf f_out, e_out, i_out, cnt_e, keys_e, sums_e, cnt_i, keys_i, sums_i;
-  const int agg_grid = (int)std::max<int64_t>(1, std::min<int64_t>((U + 8191) / 8192, (int64_t)cu_count() * 2));
-  AggStage st_e{}, st_i{};
-  if (!f_out.alloc(G * 4) || !e_out.alloc(G * m * 8) || !i_out.alloc(G * m * 8))
+  HIP_TRY(spin_event(sorted_by.ev));
+  const uint32_t differ = (uint32_t)hs[0];
+  for (int shift = 8; shift < 32; shift += 8) {
+    if (!((differ >> shift) & 255u)) continue;  // the same digit everywhere: nothing would move
+    launch_radix_pass(K, V, n, shift, hist.as<uint64_t>(), offs.as<uint64_t>(), scan_blk.as<uint64_t>(), K2, V2, s);
+    std::swap(K, K2);
+    std::swap(V, V2);
+  }
+  launch_bu_heads(K, n, heads.as<uint64_t>(), s);
+  launch_scan(heads.as<uint64_t>(), tiles, 1, scan_blk.as<uint64_t>(), first.as<uint64_t>(), s);
+  launch_report(first.as<unsigned long long>() + tiles, 1, hs + 2, s);
+  HIP_TRY(hipEventRecord(counted.ev, s));
+  launch_bu_tag(K, V, first.as<uint64_t>(), t->subend.as<uint32_t>(), n, tag.as<uint64_t>(), blk.as<uint64_t>(), s);
+  HIP_TRY(hipGetLastError());
+  HIP_TRY(spin_event(counted.ev));
+  const int64_t G = (int64_t)hs[2];
+  Buf f_out, e_out, i_out;
+  if (!f_out.alloc(G * 4) || !e_out.alloc(G * m * 8) || !i_out.alloc(G * m * 8)) {
+    (void)hipStreamSynchronize(s);  // the scratch goes back to the pool idle
     return fail(CCT_ENOMEM, "device allocation failed");
-  cct_status st = setup_stage(m, (uint64_t)G, agg_grid, cnt_e, keys_e, sums_e, st_e);
-  if (!st) st = setup_stage(m, (uint64_t)G, agg_grid, cnt_i, keys_i, sums_i, st_i);
-  if (st) return st;
-  if (st_e.nbuckets) HIP_TRY(hipMemsetAsync(st_e.count, 0, st_e.nbuckets * 4, s));
-  if (st_i.nbuckets) HIP_TRY(hipMemsetAsync(st_i.count, 0, st_i.nbuckets * 4, s));
-  HIP_TRY(hipMemsetAsync(e_out.p, 0, G * m * 8, s));
-  HIP_TRY(hipMemsetAsync(i_out.p, 0, G * m * 8, s));
-  launch_bu_frames(K, gstart.as<int64_t>(), G, f_out.as<uint32_t>(), s);
-  launch_aggregate(slot_ex.as<uint32_t>(), t->excl.as<uint64_t>(), U, m, e_out.as<uint64_t>(), (uint64_t)G, agg_grid,
-                   st_e, s);
-  launch_aggregate(slot_in.as<uint32_t>(), t->incl.as<uint64_t>(), U, m, i_out.as<uint64_t>(), (uint64_t)G, agg_grid,
-                   st_i, s);
+  }
+  launch_bu_sums(K, V, tag.as<uint64_t>(), blk.as<uint64_t>(), t->excl.as<uint64_t>(), t->incl.as<uint64_t>(), n, G, m,
+                 f_out.as<uint32_t>(), e_out.as<uint64_t>(), i_out.as<uint64_t>(), s);
+  launch_report(nullptr, 0, hs + 4, s);  // (the time)
   HIP_TRY(hipGetLastError());
-  tm.mark(1, s);
   HIP_TRY(spin_sync(s));
-  g_view_ms = tm.ok ? tm.span(0, 1) : 0.0;
+  int dev = 0;
+  (void)hipGetDevice(&dev);
+  g_view_ms = hs[4] > hs[1] ? (double)(hs[4] - hs[1]) / clock_ticks_per_ms(dev) : 0.0;
   t->bu_frames = std::move(f_out);
   t->bu_excl = std::move(e_out);
   t->bu_incl = std::move(i_out);

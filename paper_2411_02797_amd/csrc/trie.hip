@@ -339,7 +339,10 @@ __device__ inline uint64_t large_groups(const TrieArgs &a) {
 
 // Sample -> splitters (node ids).  A workgroup stages the group's sample in LDS and ranks
 // kSplitPer of its entries, a wave an entry, by counting the entries before it; an entry of
-// even rank r > 0 is splitter r / 2 - 1.  The comparisons bound it, so they are spread over
+// even rank r > 0 is splitter r / 2 - 1.  Equal blocks (which siblings have only where a hash
+// collision joined their parents) rank in the order of the sample, so that the ranks are a
+// permutation and every splitter is written whatever the blocks hold: classify_kernel reads
+// them as node ids.  The comparisons bound it, so they are spread over
 // 32 workgroups.  (1,048,576 events: a bitonic sort of the sample in one workgroup 28 us,
 // every thread counting for an entry by itself 107 us, eight workgroups with sixteen lanes
 // an entry 21 us, 9 us so.)
@@ -366,9 +369,10 @@ __global__ __launch_bounds__(kSplitThreads) void split_kernel(TrieArgs a) {
       BlockRow y;
 #pragma unroll
       for (int c = 0; c < kRowWords; ++c) y.w[c] = sb[i][c];
-      y.nf = sn[i];
+      y.nf = 2 * sn[i] + 1;  // (frames doubled: room for the order in the sample)
       uint32_t rank = 0;
-      for (int j = l; j < ns; j += kSplitLanes) rank += j != i && row_less(sb[j], sn[j], y);
+      for (int j = l; j < ns; j += kSplitLanes)
+        rank += j != i && row_less(sb[j], 2 * sn[j] + (j > i ? 2u : 0u), y);
 #pragma unroll
       for (int o = kSplitLanes / 2; o > 0; o >>= 1) rank += __shfl_xor(rank, o, 64);
       if (l == 0 && rank > 0 && rank % kOversample == 0)

@@ -33,3 +33,23 @@ def test_groups_of_siblings(sizes, shared, monkeypatch):
     o, f = csr(paths)
     w = rng.integers(0, 1 << 62, (len(paths), 1), dtype=np.uint64)
     assert_same(gpu_tree(o, f, w), oracle.build_tree(o, f, w))
+
+
+@pytest.mark.parametrize("bits", [1, 2])
+def test_equal_blocks_among_siblings(bits, monkeypatch):
+    # checkpoint hashes of one or two bits join the paths' full blocks in a few nodes, whose
+    # children hold the same blocks many times over (the same ends at different depths): the
+    # sampled splitters tie, the exact check refuses the order and the comparison sort takes
+    # over.  A first build leaves large values in the scratch memory the second one reuses.
+    torch_or_skip()
+    rng = np.random.default_rng(bits)
+    big = [[int(x) for x in rng.integers(1 << 31, 1 << 32, 40)] for _ in range(6000)]
+    o, f = csr(big)
+    w = np.ones((len(big), 1), np.uint64)
+    assert_same(gpu_tree(o, f, w), oracle.build_tree(o, f, w))
+    monkeypatch.setenv("CCT_TEST_CP_HASH_BITS", str(bits))
+    paths = [[1 + d % 5] * (16 * d) + [e, e % 3] for d in range(40) for e in range(60)]
+    paths = [paths[i] for i in rng.permutation(len(paths))]
+    o, f = csr(paths)
+    w = rng.integers(0, 1 << 62, (len(paths), 1), dtype=np.uint64)
+    assert_same(gpu_tree(o, f, w), oracle.build_tree(o, f, w))

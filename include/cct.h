@@ -251,7 +251,7 @@ const char *cct_last_error(void);
 
 /* Per-call timing of the most recent cct_build/cct_merge/cct_merge_activity on the
  * calling thread, in milliseconds of the device's fixed-rate clock, read by the first kernel
- * of each phase (the other times are measured with HIP events on the call's stream): [0]
+ * of each phase ([8] to [11] are measured with HIP events): [0]
  * ingest (hash, dedup, exclusive aggregation), [1] publish of new paths, [2] canonical
  * ordering (sort, LCP, scans), [3] node emission (parents, exclusive, inclusive), [4]
  * whole merge, [5] the correlation-ID join before the merge (cct_merge_activity only;

@@ -389,6 +389,9 @@ __global__ __launch_bounds__(256) void lcp_kernel(CanonArgs a) {
   __shared__ uint64_t rows[kLcpPer][9];
   const int C = 1 + a.m, lane = threadIdx.x & 63, g = lane % kLcpLanes, r = threadIdx.x / kLcpLanes;
   stamp(a.stamps + kStampNodes);
+  // what the merge order knows holds in a whole order only: a place that no path claimed keeps
+  // what the memory held before, so once the order is known to have one every pair is compared
+  const bool known = a.lcp_known && a.u_out[1] == 0;
   // levels of the minima from 3 up are met by atomics in the next kernel
   if (blockIdx.x == 0)
     for (int v = 3; v < a.min_levels; ++v)
@@ -406,7 +409,7 @@ __global__ __launch_bounds__(256) void lcp_kernel(CanonArgs a) {
       if (bad) p = 0;
       const uint32_t len = a.plen[p], sl = a.pslot[p];
       rc.start = a.pstart[p];
-      l = a.lcp_known ? a.lcp[i] : kInf;
+      l = known && i > 0 ? a.lcp[i] : kInf;  // (position 0 has LCP 0 whatever the memory holds)
       if (l > len) l = lcp_at(a, i, p, len, rc.start, lane);
       rc.len = len;
       rc.lcp = l;

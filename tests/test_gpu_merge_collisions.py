@@ -1,0 +1,61 @@
+"""Merges whose new paths the prefix hashes mislead: the exact comparisons have to find out
+whatever the ranks do.  The paths are searched for here with the library's hash of a prefix of
+16 frames, cut to a few bits by a test setting."""
+import numpy as np
+import pytest
+
+import oracle
+from gpu_util import assert_same, csr, to_dev, torch_or_skip
+
+pytestmark = pytest.mark.gpu
+BITS = 6
+
+
+def _hashes(paths):
+    """hash of the first 16 (k + 1) frames, [paths][k], of paths [n][16 K]"""
+    f = np.asarray(paths, np.uint32)
+    k = np.arange(f.shape[1], dtype=np.uint32)
+    with np.errstate(over="ignore"):
+        x = f + k * np.uint32(0x9E3779B9)
+        y = ((f ^ np.uint32(0x5BD1E995)) + k * np.uint32(0x85EBCA6B)) | np.uint32(1)
+        s = np.cumsum(x.astype(np.uint64) * y.astype(np.uint64), axis=1)[:, 15::16]
+        h = s + (np.arange(1, s.shape[1] + 1, dtype=np.uint64) * np.uint64(16)) * np.uint64(0x9E3779B97F4A7C15)
+        for mul in (0xFF51AFD7ED558CCD, 0xC4CEB9FE1A85EC53):
+            h = (h ^ (h >> np.uint64(33))) * np.uint64(mul)
+        return (h ^ (h >> np.uint64(33))) & np.uint64((1 << BITS) - 1)
+
+
+def _merged(old, new, rng):
+    import paper_2411_02797_amd as cct
+    w = rng.integers(0, 1 << 62, (len(old) + len(new), 1), dtype=np.uint64)
+    tree = cct.build(*to_dev(*csr(old), w[:len(old)]))
+    tree.merge(*to_dev(*csr(new), w[len(old):]))
+    got = tree.to_numpy()
+    tree.free()
+    o, f = csr(old + new)
+    assert_same(got, oracle.build_tree(o, f, w))
+
+
+@pytest.mark.parametrize("head", [1, 9])
+def test_cycles_before_the_first_old_path(head, monkeypatch):
+    """Three new paths y < x < z by their first 16 frames, z < y by the second 16 where the hashes
+    of y's and z's first block are equal: each has one of the others before it, and no path takes
+    the first place of the order (head 1) or of a later gap."""
+    torch_or_skip()
+    monkeypatch.setenv("CCT_TEST_CP_HASH_BITS", str(BITS))
+    rng = np.random.default_rng(head)
+    for case in range(12):
+        c = rng.integers(10, 1 << 31, (4000, 32), dtype=np.uint32)
+        c[:, 0] = head
+        h = _hashes(c)
+        by0 = np.lexsort(c[:, 15::-1].T)
+        y = by0[0]
+        z = next(k for k in by0[::-1] if h[k, 0] == h[y, 0])
+        c[z, 16] = min(int(c[z, 16]), int(c[y, 16]) - 1)
+        h = _hashes(c)
+        if h[z, 1] == h[y, 1]:
+            continue
+        x = next(k for k in by0[len(by0) // 2:] if h[k, 0] != h[y, 0])
+        new = [[int(v) for v in c[k]] for k in (y, x, z)]
+        old = [[5] * 20, [5] * 20 + [3], [7, 2], [20] * (1 + case)]
+        _merged(old, [new[i] for i in rng.permutation(3)], rng)

@@ -141,7 +141,7 @@ __global__ __launch_bounds__(512) void sort_block_kernel(CanonArgs a, uint32_t *
 // paths go straight to their place in the new order.
 constexpr int kNewLanes = 16;
 __global__ __launch_bounds__(256) void sort_new_kernel(CanonArgs a, uint32_t *out, uint32_t *gsorted,
-                                                       uint32_t *place) {
+                                                       uint32_t *place, uint32_t *placed) {
   const int g = threadIdx.x % kNewLanes;
   const int64_t j = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kNewLanes;
   if (j >= a.d) return;
@@ -168,6 +168,7 @@ __global__ __launch_bounds__(256) void sort_new_kernel(CanonArgs a, uint32_t *ou
   if (place) {
     place[gx + before] = x;
     a.lcp[gx + before] = kInf;  // not known yet
+    placed[j] = 1;
   } else {
     out[base + before] = x;
   }
@@ -181,7 +182,7 @@ __global__ __launch_bounds__(256) void sort_new_kernel(CanonArgs a, uint32_t *ou
 // grow with the logarithm of the number of blocks, are used instead.
 constexpr int64_t kRankBlocks = 64;
 __global__ __launch_bounds__(256) void rank_new_kernel(CanonArgs a, const uint32_t *ids, const uint32_t *bgap,
-                                                       uint32_t *gsorted, uint32_t *place) {
+                                                       uint32_t *gsorted, uint32_t *place, uint32_t *placed) {
   const int g = threadIdx.x % kNewLanes;
   const int64_t j = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kNewLanes;
   if (j >= a.d) return;
@@ -216,6 +217,7 @@ __global__ __launch_bounds__(256) void rank_new_kernel(CanonArgs a, const uint32
     gsorted[before] = gx;
     place[gx + before] = x;
     a.lcp[gx + before] = kInf;  // not known yet
+    placed[x - a.id0] = 1;
   }
 }
 
@@ -251,7 +253,7 @@ __global__ __launch_bounds__(256) void merge_pass_kernel(CanonArgs a, const uint
 // (each comparison is a chain of dependent loads).
 constexpr int kGapLanes = 16;
 __global__ __launch_bounds__(256) void gap_kernel(CanonArgs a, const uint32_t *old_order, int64_t d_old, uint32_t *gap,
-                                                  uint32_t *ids, uint32_t *bgap, uint32_t *gsorted) {
+                                                  uint32_t *ids, uint32_t *bgap, uint32_t *gsorted, uint32_t *placed) {
   stamp(a.stamps + kStampOrder);
   const int lane = threadIdx.x & 63, g = lane % kGapLanes, g0 = lane - g;
   const int64_t j = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kGapLanes;
@@ -283,12 +285,14 @@ __global__ __launch_bounds__(256) void gap_kernel(CanonArgs a, const uint32_t *o
   }
   if (active && g == 0) {
     gap[j] = (uint32_t)lo;
-    // a hash collision can make two paths claim one place of an order below: the place no
-    // path claims then still holds a path and its gap in a block's order, and is found
-    // unclaimed in the whole one (place_old_kernel)
+    // a hash collision can make two paths claim one place of an order below.  The place no path
+    // claims then keeps these values: in a block's order a path and its gap, so that what reads
+    // them stays in bounds, though that path then comes twice; in the whole order a gap that
+    // none has.  A path that lost its place in either is not marked as placed.
     ids[j] = x;
     bgap[j] = (uint32_t)lo;
     gsorted[j] = kInf;
+    placed[j] = 0;
   }
 }
 
@@ -297,7 +301,8 @@ __global__ __launch_bounds__(256) void gap_kernel(CanonArgs a, const uint32_t *o
 // gap is <= i.  Where no new path comes between old paths i - 1 and i, their LCP is the one
 // the tree keeps (lcp: kInf elsewhere): only pairs with a new path are compared again.
 __global__ __launch_bounds__(256) void place_new_kernel(const uint32_t *B, int64_t n_new, int64_t d_old,
-                                                        const uint32_t *gap, uint32_t *gsorted, uint32_t *dst, uint32_t *lcp) {
+                                                        const uint32_t *gap, uint32_t *gsorted, uint32_t *dst, uint32_t *lcp,
+                                                        uint32_t *placed) {
   const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (r >= n_new) return;
   const uint32_t x = B[r];
@@ -305,16 +310,23 @@ __global__ __launch_bounds__(256) void place_new_kernel(const uint32_t *B, int64
   gsorted[r] = g;
   dst[g + r] = x;
   lcp[g + r] = kInf;  // not known yet
+  placed[x - d_old] = 1;
 }
 __global__ __launch_bounds__(256) void place_old_kernel(const uint32_t *A, int64_t d_old, const uint32_t *gsorted,
-                                                        int64_t n_new, const uint32_t *old_lcp, uint32_t *dst,
-                                                        uint32_t *lcp, unsigned long long *u_out,
+                                                        const uint32_t *placed, int64_t n_new, const uint32_t *old_lcp,
+                                                        uint32_t *dst, uint32_t *lcp, unsigned long long *u_out,
                                                         unsigned long long *stamps) {
   if (n_new == 0) stamp(stamps + kStampOrder);
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  // a rank no path took (two took another one, after a hash collision): the order has a
-  // hole there, and the host sorts again by exact comparisons
-  if (i < n_new && gsorted[i] == kInf) atomicOr(&u_out[1], 1ull);
+  // Comparisons that collided hashes misled (neither of two paths before the other, or three in
+  // a cycle) can give one rank to two paths.  The new paths' order is whole iff every path was
+  // placed, every rank taken (as many ranks as paths: each once) and the gaps ascend; then all
+  // places of the order are written, and neighbours whose LCP is not kept are compared.
+  // Otherwise nothing below is believed and the host sorts again by exact comparisons.
+  if (i < n_new) {
+    const uint32_t g = gsorted[i];
+    if (g == kInf || !placed[i] || (i > 0 && gsorted[i - 1] > g)) atomicOr(&u_out[1], 1ull);
+  }
   if (i >= d_old) return;
   int64_t lo = 0, hi = n_new;  // new paths with gap <= i
   while (lo < hi) {
@@ -906,24 +918,24 @@ void launch_merge_order(CanonArgs &a, const uint32_t *old_order, const uint32_t 
                         uint32_t *scratch, hipStream_t s) {
   const int64_t n_new = a.d - d_old;
   const int64_t room = (n_new + kSortBlock - 1) / kSortBlock * kSortBlock;
-  uint32_t *gap = scratch, *gsorted = scratch + room;
+  uint32_t *gap = scratch, *gsorted = scratch + room, *placed = scratch + 3 * room;
   uint32_t *dst = a.order;
   a.lcp_known = 1;
   if (n_new > 0) {
     const int64_t nb = room / kSortBlock;
     uint32_t *src = a.order, *tmp = a.order_tmp, *bgap = scratch + 2 * room;
     hipLaunchKernelGGL(gap_kernel, dim3(blocks_for(n_new * kGapLanes, 256)), dim3(256), 0, s, a, old_order, d_old, gap,
-                       nb > 1 ? src : tmp, bgap, gsorted);
+                       nb > 1 ? src : tmp, bgap, gsorted, placed);
     CanonArgs r = a;  // the new ids by (gap, path)
     r.d = n_new;
     r.id0 = d_old;
     r.gap = gap;
     hipLaunchKernelGGL(sort_new_kernel, dim3(blocks_for(n_new * kNewLanes, 256)), dim3(256), 0, s, r, src,
-                       nb > 1 ? bgap : gsorted, nb > 1 ? (uint32_t *)nullptr : dst);
+                       nb > 1 ? bgap : gsorted, nb > 1 ? (uint32_t *)nullptr : dst, placed);
     if (nb > 1 && nb <= kRankBlocks) {
       dst = tmp;
       hipLaunchKernelGGL(rank_new_kernel, dim3(blocks_for(n_new * kNewLanes, 256)), dim3(256), 0, s, r, src, bgap,
-                         gsorted, dst);
+                         gsorted, dst, placed);
     } else if (nb > 1) {
       // (a misleading hash can make these passes lose or repeat a path: every pair is
       // compared again, nothing is taken as known)
@@ -931,11 +943,11 @@ void launch_merge_order(CanonArgs &a, const uint32_t *old_order, const uint32_t 
       uint32_t *sorted = merge_blocks(r, src, tmp, s);
       dst = sorted == src ? tmp : src;
       hipLaunchKernelGGL(place_new_kernel, dim3(blocks_for(n_new, 256)), dim3(256), 0, s, sorted, n_new, d_old, gap,
-                         gsorted, dst, a.lcp);
+                         gsorted, dst, a.lcp, placed);
     }
   }
   hipLaunchKernelGGL(place_old_kernel, dim3(blocks_for(std::max(d_old, n_new), 256)), dim3(256), 0, s, old_order,
-                     d_old, gsorted, n_new, old_lcp, dst, a.lcp, a.u_out, a.stamps);
+                     d_old, gsorted, placed, n_new, old_lcp, dst, a.lcp, a.u_out, a.stamps);
   a.order_tmp = dst == a.order ? a.order_tmp : a.order;
   a.order = dst;
 }

@@ -273,7 +273,7 @@ void launch_sort(CanonArgs &a, hipStream_t s);        // leaves the result in a.
 // gap in the previous order (d_old ids, sorted; the old paths keep their relative
 // order) by binary search, the new paths are sorted by (gap, path), and both lists
 // are placed by integer arithmetic; the LCPs of old neighbours that stay neighbours are
-// taken from old_lcp.  scratch: 3 words for every new path,
+// taken from old_lcp.  scratch: 4 words for every new path,
 // rounded up to a multiple of kSortBlock.  Leaves the result in a.order.
 void launch_merge_order(CanonArgs &a, const uint32_t *old_order, const uint32_t *old_lcp, int64_t d_old,
                         uint32_t *scratch, hipStream_t s);

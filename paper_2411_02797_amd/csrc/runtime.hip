@@ -685,7 +685,7 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
   const bool incremental = t->d > 0 && t->order.p && !exact_sort && !env_int("CCT_TEST_FULL_SORT", 0);
   const bool use_trie = !incremental && !exact_sort && !env_int("CCT_TEST_MERGE_SORT", 0) && D > 0;
   Buf merge_scratch;
-  if (incremental && !merge_scratch.alloc(3 * (((int64_t)n_new + kSortBlock - 1) / kSortBlock * kSortBlock) * 4))
+  if (incremental && !merge_scratch.alloc(4 * (((int64_t)n_new + kSortBlock - 1) / kSortBlock * kSortBlock) * 4))
     return undo(fail(CCT_ENOMEM, "device allocation failed"));
   Buf tr_key, tr_node, tr_block, tr_lg, tr_bc, tr_rb;
   TrieArgs ta{};

@@ -59,3 +59,29 @@ def test_cycles_before_the_first_old_path(head, monkeypatch):
         new = [[int(v) for v in c[k]] for k in (y, x, z)]
         old = [[5] * 20, [5] * 20 + [3], [7, 2], [20] * (1 + case)]
         _merged(old, [new[i] for i in rng.permutation(3)], rng)
+
+
+@pytest.mark.parametrize("n_old,n_new,pairs", [(40, 60, 12), (1500, 1030, 1), (1500, 1100, 12), (1500, 3000, 150)])
+def test_pairs_that_tie_in_one_gap(n_old, n_new, pairs, monkeypatch):
+    """Pairs of new paths of one gap with equal hashes, lengths and ends: neither is before the other,
+    so both take one rank, and one of them is lost where another path comes twice.  Every merge
+    leaves an order of as many paths in the memory that the next one takes."""
+    torch_or_skip()
+    monkeypatch.setenv("CCT_TEST_CP_HASH_BITS", str(BITS))
+    for case in range(12):
+        rng = np.random.default_rng(1000 * pairs + case)
+        old = [[10 + 2 * h] + [int(v) for v in rng.integers(0, 1 << 32, 3)] for h in range(n_old)]
+        c = rng.integers(0, 1 << 32, (64 * pairs + n_new, 16), dtype=np.uint32)
+        c[:, 0] = 11 + 2 * rng.integers(0, n_old, len(c))
+        c[:64 * pairs, 0] = np.repeat(c[:pairs, 0], 64)
+        h = _hashes(c)[:, 0]
+        new = []
+        for p in range(pairs):
+            first = {}
+            for k in range(64 * p, 64 * p + 64):
+                if first.setdefault(int(h[k]), k) != k:
+                    tail = [int(v) for v in rng.integers(0, 9, 4)]
+                    new += [[int(v) for v in c[i]] + tail for i in (first[int(h[k])], k)]
+                    break
+        new += [[int(v) for v in r] for r in c[64 * pairs:][:n_new - len(new)]]
+        _merged(old, [new[i] for i in rng.permutation(len(new))], rng)

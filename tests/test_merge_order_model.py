@@ -8,18 +8,19 @@ import random
 UNKNOWN = None
 
 
-def _merge(rng, new, d_old, less, gap, block, left_over):
+def _merge(rng, new, d_old, less, gap, block, left_over, checked):
     """Places of the new paths among the old ones as the kernels leave them: order, LCPs ("kept", a
     kept one; UNKNOWN, to be compared; a number, left over in memory at a place that nobody claimed),
     and whether the order is known to be broken.  Writers of one place come in any order."""
     n, d = len(new), len(new) + d_old
     nb = -(-n // block)
-    ids, bgap, gsorted = list(new), [gap[x] for x in new], [UNKNOWN] * n
+    ids, bgap, gsorted, placed = list(new), [gap[x] for x in new], [UNKNOWN] * n, set()
     order, lcp = list(left_over), [rng.randrange(4) for _ in range(d)]
 
     def place(rank, x, g):
         gsorted[rank] = g
         order[g + rank], lcp[g + rank] = ("new", x), UNKNOWN
+        placed.add(x)
 
     writes = []
     for j, x in enumerate(new):  # ranks by counting within the block
@@ -60,6 +61,8 @@ def _merge(rng, new, d_old, less, gap, block, left_over):
         for w in writes:
             place(*w)
     broken = any(g is UNKNOWN for g in gsorted)
+    if checked:
+        broken |= len(placed) < n or any(a is UNKNOWN or b is UNKNOWN or a > b for a, b in zip(gsorted, gsorted[1:]))
     for i in range(d_old):
         lo, hi = 0, n
         while lo < hi:
@@ -72,7 +75,8 @@ def _merge(rng, new, d_old, less, gap, block, left_over):
 
 def _trial(seed, checked=True):
     """(order the host would accept or None, the true order, a chain's parent searched before
-    position 0); checked: what the kernels check, against taking every LCP below kInf as kept."""
+    position 0); checked: what the kernels check, against looking for ranks that
+    no path took and taking every LCP below kInf as kept."""
     rng = random.Random(seed)
     d_old, n, block = rng.randrange(1, 7), rng.randrange(1, 13), rng.choice([4, 8])
     cut = [rng.randrange(d_old + 1) for _ in range(n)]  # old paths before each new one
@@ -96,7 +100,7 @@ def _trial(seed, checked=True):
     rng.shuffle(new)
     # the memory of the order holds another order of the paths (a buffer of an earlier merge), or nothing
     left_over = [p if rng.random() < 0.95 else rng.choice(truth + [None]) for p in truth]
-    order, lcp, broken = _merge(rng, new, d_old, less, cut, block, left_over)
+    order, lcp, broken = _merge(rng, new, d_old, less, cut, block, left_over, checked)
     # the exact pass: entries that are no path raise the flag and read as path 0
     kept = [v is not UNKNOWN and not (checked and (broken or i == 0)) for i, v in enumerate(lcp)]
     before0 = kept[0] and lcp[0] != 0
@@ -110,3 +114,14 @@ def _trial(seed, checked=True):
 def test_no_parent_is_searched_before_the_first_position():
     assert any(_trial(seed, checked=False)[2] for seed in range(3000))  # (the model gets there)
     assert not any(_trial(seed)[2] for seed in range(20000))
+
+
+def test_no_wrong_order_is_accepted():
+    wrong = [seed for seed in range(20000) for o, truth, _ in [_trial(seed, checked=False)] if o not in (None, truth)]
+    assert len(wrong) > 5  # (lost paths go unnoticed without the checks)
+    accepted = 0
+    for seed in list(range(20000)) + wrong:
+        o, truth, _ = _trial(seed)
+        assert o in (None, truth), seed
+        accepted += o is not None
+    assert accepted > 5000

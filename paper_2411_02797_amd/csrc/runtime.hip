@@ -485,6 +485,7 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
   }
   Buf delta, slot_of, agg_count, agg_keys, agg_sums, nstart, nsrc;
   uint64_t new_frames = 0, new_store = 0;
+  unsigned long long started = 0;  // the first attempt's stamp: a larger table takes another control block
   // The metric sums run on a second stream of the library, from the moment the ingest's
   // slot ids are complete: they overlap the host's reading of the counters, the publish
   // and the ordering.  Per-workgroup LDS maps, flushed through staging buckets of slots.
@@ -543,7 +544,8 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
                          nstart.as<uint64_t>(), max_new, ia.ctl, s);
       claimed = true;  // (from the launch on: the table may hold this call's claims)
       AGG_TRY(hipGetLastError());
-      launch_report(ia.ctl + kCtlCounters, kCtrCount, hs, s);
+      static_assert(kCtlCounters + kCtrCount == kCtlStamps && kStampCall == 0, "the call's start follows the counters");
+      launch_report(ia.ctl + kCtlCounters, kCtrCount + 1, hs, s);
       AGG_TRY(hipEventRecord(counted.ev, s));
       // (the side stream's work starts after the collection; on one stream the sums follow
       // the counters' report, which the host reads meanwhile)
@@ -552,6 +554,7 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
       AGG_TRY(hipGetLastError());
       if (side != s) AGG_TRY(hipEventRecord(summed.ev, side));
       AGG_TRY(spin_event(counted.ev));
+      if (attempt == 0) started = hs[kCtrCount];
       if (hs[kCtrError]) return undo(fail(CCT_EINVAL, "malformed offsets"));
       if (hs[kCtrOverflow]) {
         // the sums of this attempt are discarded: their buffers are reused once idle (on
@@ -803,6 +806,7 @@ cct_status aggregate(cct_tree *t, const cct_paths *p, hipStream_t s) {
     AGG_TRY(hipMemsetAsync(ctl.as<unsigned long long>() + kCtlCanon, 0, (ctl_words - kCtlCanon) * 8, s));
   }
   side_guard.idle = true;  // (the node arrays waited for the side stream's last work)
+  if (N > 0) hs[kStampCall] = started;
   collect_timings(hs, t->device, N > 0);
   if (keep_stats && ts.ok) g_stats_ms = ts.span(0, 1);
 

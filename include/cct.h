@@ -256,7 +256,8 @@ const char *cct_last_error(void);
  * ordering (sort, LCP, scans), [3] node emission (parents, exclusive, inclusive), [4]
  * whole merge, [5] the correlation-ID join before the merge (cct_merge_activity only;
  * 0 otherwise), [6] the most recent computation of a bottom-up view by cct_bottom_up
- * (calls that only copy a kept view leave it as it is), [7] the last cct_filter, [8] the
+ * (calls that only copy a kept view leave it as it is), [7] the last cct_filter (until the
+ * ids of the tree's last 2,048 nodes are written, which the device takes up last), [8] the
  * statistics kept by the last build or merge (the batch's samples folded into the paths;
  * 0 for a tree without statistics), [9] the last cct_stats, [10] the last cct_query's
  * lookups, [11] the prefix index that call built (0 when the tree's index was kept).

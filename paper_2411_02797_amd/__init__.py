@@ -328,12 +328,13 @@ def build(offsets, frames, metrics, stats=False):
 
 
 def last_timings():
-    """Per-phase HIP-event times (ms) of this thread's last calls: ingest, publish, sort,
+    """Per-phase device times (ms) of this thread's last calls: ingest, publish, sort,
     canonical emission and total of the last build/merge, the correlation-ID join of a
     merge_activity call (0 otherwise), the most recent computation of a bottom-up view
-    (bottom_up), the last filter, the statistics kept by the last build/merge (0 without),
-    the last ``Tree.stats``, the last query's lookups, and the prefix index it built (0 if
-    the tree's index was kept)."""
+    (bottom_up), the last filter (these from the device's clock, read by the kernels), the
+    statistics kept by the last build/merge (0 without), the last ``Tree.stats``, the last
+    query's lookups, and the prefix index it built (0 if the tree's index was kept; these
+    four from HIP events)."""
     buf = (ctypes.c_double * 12)()
     n = load_library().cct_last_timings(buf, 12)
     return list(buf)[:n]

@@ -470,7 +470,8 @@ struct FilterScratch {
   uint64_t *pos;    // [tiles + 1] their exclusive scan, where it is needed
 };
 // writes the first `capacity` matches to out, their number to *total (device or pinned host
-// memory) and, if times is not null, the clock at the start and the end to times[0..2)
+// memory) and, if times is not null, the clock at the start and when the last tile's matches
+// are written to times[0..2)
 void launch_filter(const FilterArgs &a, const FilterScratch &f, int64_t capacity, int64_t *out,
                    unsigned long long *total, unsigned long long *times, hipStream_t s);
 // Device address of the current device's static array (looked up once per device), or

@@ -124,7 +124,10 @@ __global__ __launch_bounds__(kScanThreads) void filter_scan_kernel(const uint32_
 // One wave per tile, kFilterWaves tiles per workgroup.  pos null: the workgroup adds up the
 // counts of the tiles before its own.  Lanes below kTileWords hold the tile's mask words and
 // an inclusive scan of their bit counts; then word by word, each set bit's lane writes its
-// node id.  The last tile's wave writes the number of matches, and the time if asked.  (With
+// node id.  The last tile's wave writes the number of matches and, if asked, the time once its own
+// ids are written: its workgroup is dispatched last (4,222,948 nodes: 18.0 us for 67 matches, 18.7
+// for 3,967,503; 16.2 and 16.3 if it is read before the ids; 20.0 and 21.4 with the launch of a
+// kernel after this one, which made the call 1.7 us longer).  (With
 // the scan as a launch between the passes, a copy of the count, two timing events and a
 // blocking wait, a call over 4,222,948 nodes took 47 us, 40 us so, 13 of them the mask.)
 constexpr int64_t kFilterDirect = 8192;
@@ -156,13 +159,9 @@ __global__ __launch_bounds__(64 * kFilterWaves) void filter_write_kernel(const u
     const int t = __shfl_up(incl, d);
     if (lane >= d) incl += t;
   }
-  if (tile == T - 1 && lane == kTileWords - 1) {
-    *total = (unsigned long long)base + (unsigned long long)incl;
-    if (ended) *ended = (unsigned long long)wall_clock64();
-  }
-  if (base >= capacity) return;  // uniform across the wave
+  if (tile == T - 1 && lane == kTileWords - 1) *total = (unsigned long long)base + (unsigned long long)incl;
   const uint64_t below = (1ull << lane) - 1;
-  for (int j = 0; j < kTileWords; ++j) {
+  for (int j = 0; j < kTileWords && base < capacity; ++j) {
     const uint32_t lo = __shfl((uint32_t)mine, j), hi = __shfl((uint32_t)(mine >> 32), j);
     const uint64_t word = ((uint64_t)hi << 32) | lo;
     const int before = __shfl(incl, j) - __popcll(word);  // matches of the tile's earlier words
@@ -170,6 +169,10 @@ __global__ __launch_bounds__(64 * kFilterWaves) void filter_write_kernel(const u
       const int64_t k = base + before + __popcll(word & below);
       if (k < capacity) __builtin_nontemporal_store(tile * kFilterTile + j * 64 + lane, &out[k]);
     }
+  }
+  if (ended && tile == T - 1) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (lane == 0) *ended = (unsigned long long)wall_clock64();
   }
 }
 

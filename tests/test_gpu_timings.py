@@ -30,3 +30,17 @@ def test_whole_call_counts_the_attempts_before_a_regrow(n, monkeypatch):
         assert all(np.isfinite(got)), got
         assert sum(got[:4]) <= got[4] * 1.001 <= wall * 1.01, (cap, got, wall)
         assert got[4] > plain[4] * 0.5, (cap, got, plain)
+
+
+@pytest.mark.parametrize("n", [20, 3000])  # one tile of nodes, several
+def test_filter_time_lies_within_the_call(n):
+    torch = torch_or_skip()
+    import paper_2411_02797_amd as cct
+    tree = cct.build(*to_dev(*tracegen.random_paths(n, 300, 20, 1, seed=n)))
+    for thr in (0, 1 << 60):  # every node with a sum, none
+        torch.cuda.synchronize()
+        t0 = time.perf_counter()
+        tree.filter(0, +1, thr, 1)
+        wall = (time.perf_counter() - t0) * 1e3
+        assert 0 < cct.last_timings()[7] <= wall * 1.01
+    tree.free()

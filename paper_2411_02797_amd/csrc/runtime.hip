@@ -232,14 +232,18 @@ struct Event {
   }
 };
 
-// whether p is memory of device dev
-bool on_device(const void *p, int dev) {
+// whether the `bytes` from p on are memory of device dev, in one allocation
+bool on_device(void *p, size_t bytes, int dev) {
   hipPointerAttribute_t at;
-  if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+  hipDeviceptr_t base = nullptr;
+  size_t size = 0;
+  if (hipPointerGetAttributes(&at, p) != hipSuccess ||
+      (at.type == hipMemoryTypeDevice && hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)p) != hipSuccess)) {
     (void)hipGetLastError();
     return false;
   }
-  return at.type == hipMemoryTypeDevice && at.device == dev;
+  const size_t before = (size_t)((char *)p - (char *)base);
+  return at.type == hipMemoryTypeDevice && at.device == dev && before <= size && bytes <= size - before;
 }
 
 uint64_t pow2_at_least(uint64_t x) {
@@ -1287,7 +1291,8 @@ cct_status cct_export(const cct_tree *tree, void *hip_stream, uint32_t *parent, 
   int dev = -1;
   (void)hipGetDevice(&dev);
   // arrays on the tree's device take one launch; anything else (host memory, another
-  // device) a copy each
+  // device, an array longer than what is left of its allocation, which the copy refuses) a
+  // copy each
   CopyArgs c{};
   const void *src[5] = {tree->parent.p, tree->frame.p, tree->depth.p, tree->excl.p, tree->incl.p};
   void *dst[5] = {parent, frame, depth, excl, incl};
@@ -1296,7 +1301,7 @@ cct_status cct_export(const cct_tree *tree, void *hip_stream, uint32_t *parent, 
   for (int i = 0; i < 5; ++i) {
     if (!dst[i]) continue;
     c.src[c.n] = (const uint32_t *)src[i]; c.dst[c.n] = (uint32_t *)dst[i]; c.words[c.n++] = bytes[i] / 4;
-    local = local && ((uintptr_t)dst[i] & 3) == 0 && on_device(dst[i], dev);
+    local = local && ((uintptr_t)dst[i] & 3) == 0 && on_device(dst[i], bytes[i], dev);
   }
   if (local) {
     if (c.n) launch_copy(c, s);

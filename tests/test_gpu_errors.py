@@ -254,3 +254,34 @@ def test_malformed_query_offsets_leave_outputs_untouched(kind):
     assert st == -1
     assert bool((ids == -7).all()) and bool((ex == -7).all()) and bool((inc == -7).all())
     tree.free()
+
+
+@pytest.mark.parametrize("short", range(5))
+def test_export_to_a_short_array_is_refused(short):
+    # one of the arrays is an allocation of 256 bytes (the runtime maps a whole page for it),
+    # shorter than the tree's array; nothing is written to it
+    import ctypes
+    import paper_2411_02797_amd as cct
+    torch = torch_or_skip()
+    tree = cct.build(*to_dev(*tracegen.random_paths(60, 40, 6, 1, seed=3)))
+    u = tree.n_nodes
+    assert 64 < u < 400
+    hip = lib = cct.load_library()  # (its runtime's symbols are found through it)
+    p, host = ctypes.c_void_p(), (ctypes.c_uint8 * 256)()
+    assert hip.hipMalloc(ctypes.byref(p), ctypes.c_size_t(256)) == 0
+    assert hip.hipMemset(p, 0xA5, ctypes.c_size_t(256)) == 0
+    long = [torch.full((8 * u,), 7, dtype=torch.uint8, device="cuda") for _ in range(5)]
+    args = [ctypes.c_void_p(t.data_ptr()) for t in long]
+    args[short] = p
+    assert lib.cct_export(tree.handle, cct._stream(), *args) != 0
+    torch.cuda.synchronize()
+    assert hip.hipMemcpy(host, p, ctypes.c_size_t(256), 2) == 0
+    assert bytes(host) == b"\xa5" * 256
+    args[short] = ctypes.c_void_p(long[short].data_ptr())  # the same arrays, long enough
+    assert lib.cct_export(tree.handle, cct._stream(), *args) == 0
+    want = tree.to_numpy()
+    for t, k in zip(long, ("parent", "frame", "depth", "excl", "incl")):
+        n = want[k].nbytes
+        assert t[:n].cpu().numpy().tobytes() == want[k].tobytes() and bool((t[n:] == 7).all()), k
+    assert hip.hipFree(p) == 0
+    tree.free()

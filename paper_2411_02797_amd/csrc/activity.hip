@@ -149,8 +149,13 @@ __global__ __launch_bounds__(256) void corr_clear_kernel(uint4 *table, uint64_t 
 // b * stride, stride >= the records one workgroup visits), their number into cnt[b].  The
 // unmatched count is summed per workgroup and added with one atomic per workgroup.  (With the
 // owner named by the last store, a second pass over the records had to find it: 40 + 77 + 23
-// us for 1,174,405 records of 4 metrics; join, gather and adds 63 + 37 +
-// 22 us so.)
+// us for 1,174,405 records of 4 metrics; join, gather and adds 63 + 37 + 22 us so.)
+// Claims of one word wait for each other, 11 ns each, so a wave looks at a word before it claims
+// it: in its first pass, and in every pass once it has met a path that another record owns (a
+// look is one more round trip where every record has its own path).  The fewer workgroups, the
+// fewer records are claimed before the first looks can tell.  1,000,000 records of 1 path, of 1,000 paths, of 1,000,000 paths: claiming
+// blindly in 2,048 workgroups 11,336, 251 and 46 us; looking always 203, 36 and 61 us (with
+// 2,048 workgroups 112 us for 1,000 paths); so 222, 36 and 47 us.
 constexpr int kJoinThreads = 256;
 __global__ __launch_bounds__(kJoinThreads) void corr_join_kernel(ActivityArgs a, uint64_t *list, int64_t stride,
                                                                  uint32_t *cnt) {
@@ -160,10 +165,18 @@ __global__ __launch_bounds__(kJoinThreads) void corr_join_kernel(ActivityArgs a,
   __syncthreads();
   unsigned long long unmatched = 0;
   uint64_t *mine = list + (int64_t)blockIdx.x * stride;
+  bool look = true, met = false;  // whether to look at a word before claiming it
   for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < a.n_rec; r += (int64_t)gridDim.x * blockDim.x) {
     const int64_t f = reg_find(a, a.rec_corr[r]);
     if (f < 0) ++unmatched;
-    else if (atomicCAS(&a.ref[f], 0u, (uint32_t)(r + 1)) != 0u) mine[atomicAdd(&n, 1u)] = ((uint64_t)f << 32) | (uint64_t)r;
+    bool later = false;  // another record owns the path
+    if (f >= 0) {
+      later = look && a.ref[f] != 0u;
+      if (!later) later = atomicCAS(&a.ref[f], 0u, (uint32_t)(r + 1)) != 0u;
+      if (later) mine[atomicAdd(&n, 1u)] = ((uint64_t)f << 32) | (uint64_t)r;
+    }
+    met |= later;
+    look = __any(met);
   }
   for (int o = 32; o > 0; o >>= 1) unmatched += __shfl_xor(unmatched, o, 64);
   if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = unmatched;
@@ -288,7 +301,7 @@ void launch_corr_table(const ActivityArgs &a, uint64_t table_bytes, hipStream_t 
   hipLaunchKernelGGL(corr_unique_kernel, dim3(blocks_for(a.n_reg, 256)), dim3(256), 0, s, a);
 }
 
-int64_t corr_join_grid(int64_t n_rec) { return std::max<int64_t>(1, std::min<int64_t>(blocks_for(n_rec, kJoinThreads), 2048)); }
+int64_t corr_join_grid(int64_t n_rec) { return std::max<int64_t>(1, std::min<int64_t>(blocks_for(n_rec, kJoinThreads), 512)); }
 
 void launch_corr_join(const ActivityArgs &a, const uint64_t *metrics, int32_t m, uint64_t *sums, uint64_t *list,
                       uint32_t *cnt, hipStream_t s) {

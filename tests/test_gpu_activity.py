@@ -214,3 +214,12 @@ def test_dense_ids_with_holes(seed):
     to, tf, _ = to_dev(ro, rf, np.zeros((ro.size - 1, 1), np.uint64))
     assert _status(lambda: tree.merge_activity(to, tf, _u64(rep), _u64(rec), _u64(rw))) == "CCT_EINVAL"
     tree.free()
+
+
+@pytest.mark.parametrize("n_reg,n_rec,repeat", [(1, 150_000, 0.0), (3, 140_001, 1.0), (60_000, 300_000, 0.0), (400, 131_073, 0.01)])
+def test_more_passes_of_the_join_than_one(n_reg, n_rec, repeat):
+    # 512 workgroups of 256 pass over 131,072 records at once: paths that many records of the
+    # first pass name, paths that only later passes find owned, and one record past a pass
+    base = tracegen.random_paths(500, 40, 12, 2, seed=n_reg)
+    got, want = run_case(base, flush(n_reg, n_rec, 2, n_reg + 9, repeat=repeat), 2)
+    assert_same(got, want, f"{n_reg} paths, {n_rec} records")

@@ -135,33 +135,37 @@ __global__ void sorted_paths_kernel(QueryArgs a) {
 }
 
 // ---- lookup through the index -----------------------------------------------------------
-// Eight lanes per query (eight queries per wave).  A lookup is a chain of dependent reads
-// (offsets, frames, table entry, path record, stored frames, sums), so its time is the
-// number of queries in flight; with one lane per query every 16-byte load of a wave
-// touched 64 different lines, and the frames of a query were read in a serial loop.  The
-// eight lanes read 32 consecutive frames per instruction, keep up to kQueryKeep of them in
-// registers for the comparison with the stored path (longer queries read theirs again),
-// and meet by cross-lane moves.  1,048,576 queries of 68 frames on average in a tree of
-// 4.2 million nodes: one lane per query 694 us; sixteen lanes 268 us (too few queries in
-// flight); four lanes 218 us; eight lanes 214 us with three pieces at 7 waves per SIMD,
-// 219 us with four at 6, 222 us with two at 8.  It moves about 0.9 GB (queries, stored
+// Several lanes per query.  A lookup is a chain of dependent reads (offsets, frames, table
+// entry, path record, stored frames, sums), so its time is the number of queries in flight; with
+// one lane per query every 16-byte load of a wave touched 64 different lines, and the frames of
+// a query were read in a serial loop.  L lanes read 4 L consecutive frames per instruction, keep
+// up to V pieces of them in registers for the comparison with the stored path (longer queries
+// read theirs again), and meet by cross-lane moves.  1,048,576 queries of 68 frames on average
+// in a tree of 4.2 million nodes: one lane per query 694 us; sixteen lanes 268 us (too few
+// queries in flight); four lanes 218 us; eight lanes 214 us with three pieces at 7 waves per
+// SIMD, 219 us with four at 6, 222 us with two at 8.  It moves about 0.9 GB (queries, stored
 // frames, a table line and two rows of sums per query), 4.2 TB/s.
-constexpr int kQueryLanes = 8;
-constexpr int kQueryVecs = 3;                               // 16-byte pieces of a query per lane
-constexpr int kQueryStep = 4 * kQueryLanes;                 // frames per piece of the eight lanes
-constexpr int kQueryKeep = kQueryStep * kQueryVecs;         // frames held in registers
+// Short queries leave most of eight lanes' work to padding, so a batch takes the lanes that its
+// mean length fills: 32 frames on four lanes of two pieces, 16 frames on two lanes of two where
+// no lane has more than two metrics to fetch.  Microseconds for 8,000,000 queries of 1,
+// 8 and 16 frames (2 metrics, 40,000 nodes): eight lanes 877, 973 and 999, four 480, 541 and
+// 565, two 311, 360 and 383, one lane with a serial loop 304, 497 and 774; for 1,000,000 of 32
+// frames in 4,000,000 nodes 186 on eight lanes and 130 on four.  Two lanes lose to four from 4
+// metrics on (1,000,000 queries of 8 frames in 4,000,000 nodes: 113 on four, 130 on two; with 8
+// metrics 132 and 243) and from 20 frames on.
 
-// sum over the eight lanes of a query, on all of them
-__device__ inline uint64_t sum8(uint64_t v) {
+// sum over the L (2, 4 or 8) lanes of a query, on all of them
+template <int L>
+__device__ inline uint64_t sum_lanes(uint64_t v) {
 #define CCT_DPP_ADD(ctrl)                                                                                    \
   {                                                                                                          \
     const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)v, ctrl, 0xF, 0xF, true);          \
     const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(v >> 32), ctrl, 0xF, 0xF, true);  \
     v += ((uint64_t)hi << 32) | lo;                                                                          \
   }
-  CCT_DPP_ADD(0xB1)   // quad_perm 1,0,3,2
-  CCT_DPP_ADD(0x4E)   // quad_perm 2,3,0,1
-  CCT_DPP_ADD(0x141)  // row_half_mirror: the other quad of the eight lanes
+  CCT_DPP_ADD(0xB1)              // quad_perm 1,0,3,2
+  if (L > 2) CCT_DPP_ADD(0x4E)   // quad_perm 2,3,0,1
+  if (L > 4) CCT_DPP_ADD(0x141)  // row_half_mirror: the other quad of the eight lanes
 #undef CCT_DPP_ADD
   return v;
 }
@@ -181,7 +185,11 @@ __device__ inline Frames4 query_frames(const uint32_t *qf, Int k, Int n, Int ava
   return v;
 }
 
+// kQueryLanes lanes per query, kQueryVecs 16-byte pieces of it per lane
+template <int kQueryLanes, int kQueryVecs>
 __device__ inline void query_one(const QueryArgs &a, int64_t q, int lane) {
+  constexpr int kQueryStep = 4 * kQueryLanes;          // frames per piece of the query's lanes
+  constexpr int kQueryKeep = kQueryStep * kQueryVecs;  // frames held in registers
   int g = lane % kQueryLanes;
   // (opaque to the compiler here, or it keeps every lane-derived constant of the pieces
   // in registers across the queries: 138 VGPRs instead of 72)
@@ -214,7 +222,7 @@ __device__ inline void query_one(const QueryArgs &a, int64_t q, int lane) {
         sum += k < ql ? prefix_term(x.f[j], (uint32_t)k) : 0ull;
       }
     }
-    const uint64_t key = prefix_key(sum8(sum), (uint64_t)ql, a.qhash_mask);
+    const uint64_t key = prefix_key(sum_lanes<kQueryLanes>(sum), (uint64_t)ql, a.qhash_mask);
     uint64_t slot = key & a.qcap_mask;
     // probe from the query's key: an empty slot ends the sequence; an entry with the same
     // key and length is checked frame by frame against its path
@@ -266,12 +274,13 @@ __device__ inline void query_one(const QueryArgs &a, int64_t q, int lane) {
   }
 }
 
+template <int L, int V>
 __global__ __launch_bounds__(256, 7) void query_kernel(QueryArgs a) {
   if (*a.err) return;  // malformed offsets (query_check_kernel): nothing is written
   const int lane = threadIdx.x & 63;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x / kQueryLanes;
-  for (int64_t q = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kQueryLanes; q < a.q; q += stride)
-    query_one(a, q, lane);
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x / L;
+  for (int64_t q = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / L; q < a.q; q += stride)
+    query_one<L, V>(a, q, lane);
 }
 
 // ---- lookup by binary search ------------------------------------------------------------
@@ -347,8 +356,12 @@ void launch_query(const QueryArgs &a, hipStream_t s) {
   if (a.q <= 0) return;
   if (a.qtab) {
     // (a launch holds fewer than 2^32 work items: larger batches loop)
-    const int64_t blocks = std::min<int64_t>((a.q * kQueryLanes + 255) / 256, 1 << 22);
-    hipLaunchKernelGGL(query_kernel, dim3((unsigned)blocks), dim3(256), 0, s, a);
+    const bool brief = a.qn_frames <= 16 * a.q && a.m <= 3, medium = a.qn_frames <= 32 * a.q;
+    const int lanes = brief ? 2 : medium ? 4 : 8;
+    const dim3 blocks((unsigned)std::min<int64_t>((a.q * lanes + 255) / 256, 1 << 22));
+    if (brief) hipLaunchKernelGGL((query_kernel<2, 2>), blocks, dim3(256), 0, s, a);
+    else if (medium) hipLaunchKernelGGL((query_kernel<4, 2>), blocks, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((query_kernel<8, 3>), blocks, dim3(256), 0, s, a);
   } else {
     hipLaunchKernelGGL(query_search_kernel, dim3((unsigned)((a.q + 255) / 256)), dim3(256), 0, s, a);
   }

@@ -35,6 +35,13 @@ constexpr int kScanRows = 1024;    // rows per scan block
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
+// the order is not strictly increasing: the host sorts again by exact comparisons.  (A fast
+// order that failed breaks nearly every pair, and atomics on one word wait for each other, 11 ns
+// each: 400,000 paths 570 us in lcp_kernel when every pair raised the flag, 99 us so.)
+__device__ inline void violated(unsigned long long *u_out) {
+  if (*(volatile unsigned long long *)&u_out[1] == 0) atomicOr(&u_out[1], 1ull);
+}
+
 __device__ inline u32x4 ld4(const uint32_t *p) { return *(const u32x4 *)p; }
 
 // Exact comparison of two stored paths: returns <0, 0, >0 and their lcp.  Starts are
@@ -325,7 +332,7 @@ __global__ __launch_bounds__(256) void place_old_kernel(const uint32_t *A, int64
   // Otherwise nothing below is believed and the host sorts again by exact comparisons.
   if (i < n_new) {
     const uint32_t g = gsorted[i];
-    if (g == kInf || !placed[i] || (i > 0 && gsorted[i - 1] > g)) atomicOr(&u_out[1], 1ull);
+    if (g == kInf || !placed[i] || (i > 0 && gsorted[i - 1] > g)) violated(u_out);
   }
   if (i >= d_old) return;
   int64_t lo = 0, hi = n_new;  // new paths with gap <= i
@@ -390,7 +397,7 @@ __device__ inline uint32_t lcp_at(const CanonArgs &a, int64_t i, uint32_t p, uin
       }
     }
   }
-  if (!less && g == 0) atomicOr(&a.u_out[1], 1ull);  // not strictly increasing
+  if (!less && g == 0) violated(a.u_out);  // not strictly increasing
   return l;
 }
 
@@ -426,7 +433,7 @@ __global__ __launch_bounds__(256) void lcp_kernel(CanonArgs a) {
       rc.len = len;
       rc.lcp = l;
       if (bad && g == 0) {
-        atomicOr(&a.u_out[1], 1ull);
+        violated(a.u_out);
         a.order[i] = 0;
       }
       // the path's sums after the batch: every path sits at one position of a good order,
@@ -727,7 +734,7 @@ __global__ void chain_kernel(CanonArgs a) {
   const uint64_t b = node_base(a, i);
   const uint32_t cnt = a.rec[i].len - L;
   if (b + cnt > (uint64_t)a.u_max) {
-    atomicOr(&a.u_out[1], 1ull);
+    violated(a.u_out);
     return;
   }
   if (cnt == 0) return;
@@ -761,7 +768,7 @@ __global__ __launch_bounds__(256, M <= 4 ? 7 : 5) void emit_kernel(CanonArgs a) 
   const int64_t U = U_all < a.u_max ? U_all : a.u_max;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     a.u_out[0] = (unsigned long long)U;
-    if (U_all > a.u_max) atomicOr(&a.u_out[1], 1ull);
+    if (U_all > a.u_max) violated(a.u_out);
   }
   uint32_t *mark = emit_mark + w0;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -785,7 +792,7 @@ __global__ __launch_bounds__(256, M <= 4 ? 7 : 5) void emit_kernel(CanonArgs a) 
     // path past the first has at least one node, so they cover the window); a node's
     // path is the last of them whose first node is at or before it
     if (i0 >= d && (base > 0 || U > 1)) {  // a window chain_kernel did not write (the order is not a permutation)
-      if (lane == 0) atomicOr(&a.u_out[1], 1ull);
+      if (lane == 0) violated(a.u_out);
       i0 = 0;
       nb = first_node(lane);
     }
@@ -816,7 +823,7 @@ __global__ __launch_bounds__(256, M <= 4 ? 7 : 5) void emit_kernel(CanonArgs a) 
     } else if (base + lane < U) {
       uint32_t i = i0 + off;
       if (i >= d || b > u) {  // (only when the order is not a permutation)
-        atomicOr(&a.u_out[1], 1ull);
+        violated(a.u_out);
         i = 0;
         b = first_node(0);
       }
@@ -824,7 +831,7 @@ __global__ __launch_bounds__(256, M <= 4 ? 7 : 5) void emit_kernel(CanonArgs a) 
       const uint32_t after = a.lcp[i + 1];
       uint32_t l = rc.lcp + 1 + (u - b);
       if (l > rc.len || u - b >= rc.len) {  // (only when the order is not a permutation)
-        atomicOr(&a.u_out[1], 1ull);
+        violated(a.u_out);
         l = rc.len;
       }
       const uint32_t fr = l ? a.pframes[rc.start + l - 1] : 0u;

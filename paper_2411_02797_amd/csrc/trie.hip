@@ -29,7 +29,11 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kBlk = kStoreAlign;           // frames per block
 constexpr int kLarge = 512;                 // larger sibling groups are split into buckets ...
 constexpr int64_t kSmallTrie = 2048;        // ... unless the trie has no more blocks than this
-constexpr int kMaxBucket = 8192;            // largest bucket that is ordered by counting
+// Largest bucket that is ordered by counting; beyond it the call fails over to the comparison sort.
+// Builds of n paths of 20 frames that part in the first block, with 2,048, 4,096 and 8,192 here:
+// n = 200,000 1.60, 0.80 and 0.80 ms; 300,000 1.72, 1.30 and 1.27; 400,000 2.12, 2.10 and 1.79;
+// from 700,000 on a bucket passes all three (3.87 ms).
+constexpr int kMaxBucket = 8192;
 constexpr uint64_t kRootSeed = 0x5851F42D4C957F2Dull;
 constexpr int kMaxBuckets = 256, kOversample = 2, kBucketTarget = 32;  // large groups (split_kernel)
 constexpr int kFail = kTrieCtrFail;
@@ -510,7 +514,10 @@ __global__ __launch_bounds__(kClassPer) void rscatter_kernel(TrieArgs a) {
 // any mixture of small and large ranges.  (Sorted by counting up to 64 siblings, by bitonic
 // sorts up to 2,048 and in buckets, with the counts then gathered and scanned in sorted
 // order: nine launches on two streams, about 120 us of a 1,048,576-event build; with the
-// splitting four launches, 61 us, this one 22 us of them, 72 us for 405,319 nodes.)
+// splitting four launches, 61 us, this one 22 us of them, 72 us for 405,319 nodes.)  The work
+// grows with the ranges' sizes squared, up to a millisecond for 400,000 siblings, so a call that
+// has failed already does none of it (400,000 one-frame paths, whose hashes collide, 2.19 ->
+// 1.71 ms with the comparison sort that follows).
 template <int L, int Threads>
 __global__ __launch_bounds__(Threads) void order_kernel(TrieArgs a, const uint32_t *members, const uint64_t *unit,
                                                         const uint32_t *base) {
@@ -520,7 +527,7 @@ __global__ __launch_bounds__(Threads) void order_kernel(TrieArgs a, const uint32
   __shared__ uint8_t sn[Threads];
   __shared__ uint32_t first, end;
   const uint64_t nodes = node_count(a);
-  if ((uint64_t)blockIdx.x * kPer >= nodes) return;
+  if ((uint64_t)blockIdx.x * kPer >= nodes || a.ctr[kFail]) return;  // (after a failure no rank counts)
   const uint64_t p = (uint64_t)blockIdx.x * kPer + threadIdx.x / L;
   const int l = threadIdx.x % L;
   const bool in = p < nodes;

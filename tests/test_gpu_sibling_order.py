@@ -53,3 +53,17 @@ def test_equal_blocks_among_siblings(bits, monkeypatch):
     o, f = csr(paths)
     w = rng.integers(0, 1 << 62, (len(paths), 1), dtype=np.uint64)
     assert_same(gpu_tree(o, f, w), oracle.build_tree(o, f, w))
+
+
+@pytest.mark.parametrize("n,trie", [(150_000, True), (600_000, False)])
+def test_wide_groups(n, trie, monkeypatch):
+    # buckets of hundreds of siblings, and of more than are counted (the comparison sort takes over)
+    torch_or_skip()
+    if trie:
+        monkeypatch.setenv("CCT_TEST_REQUIRE_TRIE", "1")
+    rng = np.random.default_rng(n)
+    f = np.full((n, 16), 5, np.uint32)
+    f[:, 13:] = rng.integers(0, 1 << 32, (n, 3), dtype=np.uint32)
+    o = np.arange(n + 1, dtype=np.int64) * 16
+    w = rng.integers(0, 1 << 62, (n, 1), dtype=np.uint64)
+    assert_same(gpu_tree(o, f.ravel(), w), oracle.build_tree(o, f.ravel(), w))

@@ -116,10 +116,18 @@ __device__ inline bool key_less(const CanonArgs &a, uint32_t x, uint32_t y) {
 }
 
 // ---- sort -------------------------------------------------------------------------
-// Block-local bitonic sort by path.
-__global__ __launch_bounds__(512) void sort_block_kernel(CanonArgs a, uint32_t *out) {
+// A large merge orders its new paths in one of two ways, and gap_kernel's samples say which:
+// launches of the other way end at once.
+enum When : int { kAlways = 0, kFewGaps = 1, kManyGaps = 2 };
+__device__ inline bool skipped(const CanonArgs &a, When when) {
+  return when != kAlways && (a.u_out[2] >= a.few_gaps) != (when == kFewGaps);
+}
+
+// Block-local bitonic sort by path, or by (gap, path).
+__global__ __launch_bounds__(512) void sort_block_kernel(CanonArgs a, uint32_t *out, When when) {
   __shared__ uint32_t key[kSortBlock];
-  stamp(a.stamps + kStampOrder);
+  if (skipped(a, when)) return;
+  if (!a.gap) stamp(a.stamps + kStampOrder);
   const int tid = threadIdx.x;
   const int64_t base = (int64_t)blockIdx.x * kSortBlock;
   for (int i = tid; i < kSortBlock; i += 512) key[i] = base + i < a.d ? (uint32_t)(a.id0 + base + i) : kInf;
@@ -130,7 +138,7 @@ __global__ __launch_bounds__(512) void sort_block_kernel(CanonArgs a, uint32_t *
       const uint32_t x = key[i], y = key[l];
       // ascending where (i & k) == 0: swap if y < x; else swap if x < y
       const bool up = (i & k) == 0;
-      const bool swap = path_less(a, up ? y : x, up ? x : y);
+      const bool swap = key_less(a, up ? y : x, up ? x : y);
       __syncthreads();
       if (swap) { key[i] = y; key[l] = x; }
       __syncthreads();
@@ -148,7 +156,8 @@ __global__ __launch_bounds__(512) void sort_block_kernel(CanonArgs a, uint32_t *
 // paths go straight to their place in the new order.
 constexpr int kNewLanes = 16;
 __global__ __launch_bounds__(256) void sort_new_kernel(CanonArgs a, uint32_t *out, uint32_t *gsorted,
-                                                       uint32_t *place, uint32_t *placed) {
+                                                       uint32_t *place, uint32_t *placed, When when) {
+  if (skipped(a, when)) return;
   const int g = threadIdx.x % kNewLanes;
   const int64_t j = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kNewLanes;
   if (j >= a.d) return;
@@ -186,10 +195,26 @@ __global__ __launch_bounds__(256) void sort_new_kernel(CanonArgs a, uint32_t *ou
 // binary search.  Sixteen lanes share a path, a block each: the search by gap needs 4-byte
 // loads only; where the block holds paths in the same gap, a second one compares paths.
 // Every block costs each path the same searches, so past kRankBlocks the merge passes, which
-// grow with the logarithm of the number of blocks, are used instead.
+// grow with the logarithm of the number of blocks, are used instead: merges of new paths in
+// 50,000 gaps by ranks and by passes, 34,000 296 and 431 us, 60,000 385 and 485, 66,000 424 and
+// 535, 100,000 622 and 619, 130,000 823 and 682 (the line stays below 98 blocks because paths that
+// share a gap cost the ranks more).
 constexpr int64_t kRankBlocks = 64;
+// Counting and ranking compare paths for every pair that shares a gap, so where most new paths
+// lie in few gaps (a new phase of the program, a merge into a tree of few paths) their work grows
+// with the square.  Past kCountBlocks gap_kernel's samples decide between them and the
+// comparison sort of the blocks with merge passes; whichever is not needed costs its empty
+// launches (8 of them, 11 to 18 us).  The share of neighbours in one gap from which the sort is
+// taken falls as the blocks grow more (launch_merge_order).  New paths of 24 frames in 6 gaps, merged
+// by counting and by sorting: 33,000 603 and 617 us, 60,000 1,000 and 653, 150,000 1,678 and
+// 1,026; in 65 gaps: 33,000 385 and about 580, 60,000 700 and 616, 150,000 1,113 and 934; 200 gaps:
+// 60,000 592 and about 640, 150,000 1,016 and 888.  Paths that share 100 frames, in few gaps: 26,000
+// 824 and 863 us, 33,000 1,382 and 953, 60,000 2,188 and 1,056.
+constexpr int64_t kCountBlocks = 26;
 __global__ __launch_bounds__(256) void rank_new_kernel(CanonArgs a, const uint32_t *ids, const uint32_t *bgap,
-                                                       uint32_t *gsorted, uint32_t *place, uint32_t *placed) {
+                                                       uint32_t *gsorted, uint32_t *place, uint32_t *placed,
+                                                       When when) {
+  if (skipped(a, when)) return;
   const int g = threadIdx.x % kNewLanes;
   const int64_t j = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kNewLanes;
   if (j >= a.d) return;
@@ -229,7 +254,8 @@ __global__ __launch_bounds__(256) void rank_new_kernel(CanonArgs a, const uint32
 }
 
 __global__ __launch_bounds__(256) void merge_pass_kernel(CanonArgs a, const uint32_t *src, uint32_t *dst,
-                                                         int64_t run) {
+                                                         int64_t run, When when) {
+  if (skipped(a, when)) return;
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t o0 = t * kMergeItems;
   if (o0 >= a.d) return;
@@ -258,7 +284,7 @@ __global__ __launch_bounds__(256) void merge_pass_kernel(CanonArgs a, const uint
 // 16 old paths that cut the remaining range into 17 parts (a 17-ary search), so the
 // answer takes about log_17(d_old) rounds of path comparisons instead of log_2(d_old)
 // (each comparison is a chain of dependent loads).
-constexpr int kGapLanes = 16;
+constexpr int kGapLanes = 16, kGapSample = 16;
 __global__ __launch_bounds__(256) void gap_kernel(CanonArgs a, const uint32_t *old_order, int64_t d_old, uint32_t *gap,
                                                   uint32_t *ids, uint32_t *bgap, uint32_t *gsorted, uint32_t *placed) {
   stamp(a.stamps + kStampOrder);
@@ -290,6 +316,12 @@ __global__ __launch_bounds__(256) void gap_kernel(CanonArgs a, const uint32_t *o
       }
     }
   }
+  // every 16th workgroup counts the neighbours among its waves' four paths that share a gap
+  if (a.few_gaps && blockIdx.x % kGapSample == 0) {
+    const uint32_t next = __shfl((uint32_t)lo, (g0 + kGapLanes) & 63, 64);
+    const uint64_t same = __ballot(active && g == 0 && g0 + kGapLanes < 64 && next == (uint32_t)lo);
+    if (lane == 0 && same) atomicAdd(&a.u_out[2], (unsigned long long)__popcll(same));
+  }
   if (active && g == 0) {
     gap[j] = (uint32_t)lo;
     // a hash collision can make two paths claim one place of an order below.  The place no path
@@ -309,7 +341,8 @@ __global__ __launch_bounds__(256) void gap_kernel(CanonArgs a, const uint32_t *o
 // the tree keeps (lcp: kInf elsewhere): only pairs with a new path are compared again.
 __global__ __launch_bounds__(256) void place_new_kernel(const uint32_t *B, int64_t n_new, int64_t d_old,
                                                         const uint32_t *gap, uint32_t *gsorted, uint32_t *dst, uint32_t *lcp,
-                                                        uint32_t *placed) {
+                                                        uint32_t *placed, CanonArgs a, When when) {
+  if (skipped(a, when)) return;
   const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (r >= n_new) return;
   const uint32_t x = B[r];
@@ -901,10 +934,10 @@ inline unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1)
 
 namespace {
 // merge passes over blocks of kSortBlock sorted ids: the sorted list, in one of the buffers
-uint32_t *merge_blocks(const CanonArgs &a, uint32_t *src, uint32_t *dst, hipStream_t s) {
+uint32_t *merge_blocks(const CanonArgs &a, uint32_t *src, uint32_t *dst, When when, hipStream_t s) {
   for (int64_t run = kSortBlock; run < a.d; run *= 2) {
     hipLaunchKernelGGL(merge_pass_kernel, dim3(blocks_for((a.d + kMergeItems - 1) / kMergeItems, 256)), dim3(256),
-                       0, s, a, src, dst, run);
+                       0, s, a, src, dst, run, when);
     uint32_t *t = src; src = dst; dst = t;
   }
   return src;
@@ -913,8 +946,8 @@ uint32_t *merge_blocks(const CanonArgs &a, uint32_t *src, uint32_t *dst, hipStre
 
 void launch_sort(CanonArgs &a, hipStream_t s) {
   if (a.d <= 0) return;
-  hipLaunchKernelGGL(sort_block_kernel, dim3(blocks_for(a.d, kSortBlock)), dim3(512), 0, s, a, a.order);
-  uint32_t *sorted = merge_blocks(a, a.order, a.order_tmp, s);
+  hipLaunchKernelGGL(sort_block_kernel, dim3(blocks_for(a.d, kSortBlock)), dim3(512), 0, s, a, a.order, kAlways);
+  uint32_t *sorted = merge_blocks(a, a.order, a.order_tmp, kAlways, s);
   if (sorted != a.order) {
     a.order_tmp = a.order;
     a.order = sorted;
@@ -931,26 +964,37 @@ void launch_merge_order(CanonArgs &a, const uint32_t *old_order, const uint32_t 
   if (n_new > 0) {
     const int64_t nb = room / kSortBlock;
     uint32_t *src = a.order, *tmp = a.order_tmp, *bgap = scratch + 2 * room;
-    hipLaunchKernelGGL(gap_kernel, dim3(blocks_for(n_new * kGapLanes, 256)), dim3(256), 0, s, a, old_order, d_old, gap,
-                       nb > 1 ? src : tmp, bgap, gsorted, placed);
+    const dim3 lanes(blocks_for(n_new * kNewLanes, 256)), blocks((unsigned)nb), paths(blocks_for(n_new, 256));
     CanonArgs r = a;  // the new ids by (gap, path)
     r.d = n_new;
     r.id0 = d_old;
     r.gap = gap;
-    hipLaunchKernelGGL(sort_new_kernel, dim3(blocks_for(n_new * kNewLanes, 256)), dim3(256), 0, s, r, src,
-                       nb > 1 ? bgap : gsorted, nb > 1 ? (uint32_t *)nullptr : dst, placed);
-    if (nb > 1 && nb <= kRankBlocks) {
-      dst = tmp;
-      hipLaunchKernelGGL(rank_new_kernel, dim3(blocks_for(n_new * kNewLanes, 256)), dim3(256), 0, s, r, src, bgap,
-                         gsorted, dst, placed);
-    } else if (nb > 1) {
-      // (a misleading hash can make these passes lose or repeat a path: every pair is
-      // compared again, nothing is taken as known)
-      a.lcp_known = 0;
-      uint32_t *sorted = merge_blocks(r, src, tmp, s);
+    const bool either = nb > kCountBlocks;  // counting or comparing, as the gaps say
+    if (either) {
+      // the share of neighbours in one gap at which sorting pays: see kCountBlocks (a sampled
+      // workgroup compares 12 pairs; beyond kRankBlocks only the blocks' order is in question)
+      const int64_t pairs = (int64_t)blocks_for(blocks_for(n_new * kGapLanes, 256), kGapSample) * 12;
+      r.few_gaps = a.few_gaps = (uint64_t)std::max<int64_t>(1, pairs / (nb <= 40 ? 4 : nb <= 48 ? 16 : nb <= kRankBlocks ? 64 : 128));
+    }
+    hipLaunchKernelGGL(gap_kernel, dim3(blocks_for(n_new * kGapLanes, 256)), dim3(256), 0, s, a, old_order, d_old, gap,
+                       nb > 1 ? src : tmp, bgap, gsorted, placed);
+    hipLaunchKernelGGL(sort_new_kernel, lanes, dim3(256), 0, s, r, src, nb > 1 ? bgap : gsorted,
+                       nb > 1 ? (uint32_t *)nullptr : dst, placed, either ? kManyGaps : kAlways);
+    if (nb > 1) dst = tmp;
+    if (nb > 1 && nb <= kRankBlocks)
+      hipLaunchKernelGGL(rank_new_kernel, lanes, dim3(256), 0, s, r, src, bgap, gsorted, dst, placed,
+                         either ? kManyGaps : kAlways);
+    if (either) {
+      const When when = nb <= kRankBlocks ? kFewGaps : kAlways;
+      int passes = 0;
+      for (int64_t run = kSortBlock; run < n_new; run *= 2) ++passes;
+      // (up to kRankBlocks the sorted list has to end where rank_new_kernel read its blocks)
+      uint32_t *from = when == kFewGaps && passes % 2 ? tmp : src;
+      hipLaunchKernelGGL(sort_block_kernel, blocks, dim3(512), 0, s, r, from, kFewGaps);
+      uint32_t *sorted = merge_blocks(r, from, from == src ? tmp : src, when, s);
       dst = sorted == src ? tmp : src;
-      hipLaunchKernelGGL(place_new_kernel, dim3(blocks_for(n_new, 256)), dim3(256), 0, s, sorted, n_new, d_old, gap,
-                         gsorted, dst, a.lcp, placed);
+      hipLaunchKernelGGL(place_new_kernel, paths, dim3(256), 0, s, sorted, n_new, d_old, gap, gsorted, dst, a.lcp, placed,
+                         r, when);
     }
   }
   hipLaunchKernelGGL(place_old_kernel, dim3(blocks_for(std::max(d_old, n_new), 256)), dim3(256), 0, s, old_order,

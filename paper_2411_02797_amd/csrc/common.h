@@ -229,6 +229,7 @@ struct CanonArgs {
   // merge's new ones by (gap[id - id0], path)
   int64_t id0;
   const uint32_t *gap;
+  uint64_t few_gaps;     // a large merge: sampled neighbours in one gap (u_out[2]) from which on comparing pays
   int32_t lcp_known;     // launch_canon: lcp holds what launch_merge_order knows already, kInf elsewhere
   int32_t m;
   int32_t exact;         // 1: compare frames only (no checkpoint-hash shortcut)
@@ -264,7 +265,7 @@ struct CanonArgs {
   uint32_t *parent, *frame, *depth;
   uint32_t *subend;      // [U] end of each node's subtree: its descendants are the ids (u, subend[u])
   uint64_t *excl, *incl;
-  unsigned long long *u_out;  // device: [0] node count, [1] order-violation flag
+  unsigned long long *u_out;  // device: [0] node count, [1] order-violation flag, [2] neighbours in one gap
   unsigned long long *stamps;
   int grid_nodes;
 };

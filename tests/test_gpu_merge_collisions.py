@@ -85,3 +85,25 @@ def test_pairs_that_tie_in_one_gap(n_old, n_new, pairs, monkeypatch):
                     break
         new += [[int(v) for v in r] for r in c[64 * pairs:][:n_new - len(new)]]
         _merged(old, [new[i] for i in rng.permutation(len(new))], rng)
+
+
+@pytest.mark.parametrize("n_new", [26 * 1024, 26 * 1024 + 1, 33_000, 64 * 1024 + 1])
+@pytest.mark.parametrize("gaps", [1, 3000])
+@pytest.mark.parametrize("tied", [False, True])
+def test_large_merges_count_or_sort(n_new, gaps, tied, monkeypatch):
+    """Merges past the size from which the new paths' gaps decide how they are ordered: most of
+    them in one gap or spread over many, an odd and an even number of merge passes, ranks and
+    passes; and with hashes of few bits, which leave many pairs in a tie."""
+    torch_or_skip()
+    if tied:
+        if n_new > 30_000:
+            pytest.skip("the exact comparison sort of as many paths adds nothing here")
+        monkeypatch.setenv("CCT_TEST_CP_HASH_BITS", "14")
+    rng = np.random.default_rng(n_new + gaps)
+    old = [[10 + 2 * h] + [int(v) for v in rng.integers(0, 1 << 32, 3)] for h in range(3000)]
+    c = rng.integers(0, 1 << 32, (n_new, 18), dtype=np.uint32)
+    c[:, 0] = 11 + 2 * rng.integers(0, gaps, n_new)
+    if tied:
+        c[:, 16:] = rng.integers(0, 60, (n_new, 2))
+        c = np.unique(c, axis=0)
+    _merged(old, [[int(v) for v in r] for r in c[rng.permutation(len(c))]], rng)

@@ -299,7 +299,7 @@ __global__ void bu_clear_kernel(uint64_t *ex, uint64_t *in, int64_t n) {
 // Frames and sums of the groups.  blk: exclusive max-scan of the tiles' largest tags; ex
 // and in are zero.  The rows of the sums come from anywhere in the tree (an L2 line a
 // node and array); 32 KB of LDS hold two metrics of a tile's groups, so more metrics take
-// further turns and five workgroups still share a CU.
+// further turns and four workgroups (32,800 bytes each) still share a CU.
 template <int M>
 __global__ __launch_bounds__(kMsThreads) void bu_sums_kernel(const uint32_t *K, const uint32_t *V, const uint64_t *tag,
                                                             const uint64_t *blk, const uint64_t *excl,

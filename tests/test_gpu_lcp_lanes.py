@@ -1,5 +1,5 @@
 """Neighbouring paths that part at, before and after the edges of the LCP kernel's steps
-(sixteen lanes compare 64 frames at a time, four frames each)."""
+(eight lanes compare 64 frames at a time, two pieces of 32, four frames of each a lane)."""
 import numpy as np
 import pytest
 

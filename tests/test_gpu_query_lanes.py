@@ -1,5 +1,6 @@
 """Lookups through the prefix index at the edges of the lookup kernel's tiling: eight lanes
-share a query, four frames each, 32 per step, and the first 96 frames stay in registers."""
+share a query, four frames each, 32 per step, and the first 96 frames stay in registers; two or four
+lanes in batches of short queries (16 and 32 frames in registers)."""
 import numpy as np
 import pytest
 

@@ -787,8 +787,8 @@ __global__ void chain_kernel(CanonArgs a) {
 // reads them, and what they would evict from the caches is read (this kernel's rows, the next
 // call's frames).  A first reader finds less of them in the caches, but a build with its first
 // reader is no slower for it: build alone, with the first filter, with the view and with the
-// export, 9.8 million nodes of 2 metrics 772, 856, 1,461 and 930 us, with ordinary stores 817, 909,
-// 1,507 and 961; 4.4 million 556, 631, 945 and 655 against 560, 633, 942 and 652.  4,222,948 nodes of 2 metrics 114
+// export, about 10 million nodes of 2 metrics 772, 856, 1,461 and 930 us, with ordinary stores 817, 909,
+// 1,507 and 961; about 4.5 million 556, 631, 945 and 655 against 560, 633, 942 and 652.  4,222,948 nodes of 2 metrics 114
 // -> 81 us (2.5 TB/s of arrays written), 4.57 million of 4 metrics 149 -> 107 us (3.4), 4.0
 // million of 8 metrics 166 -> 95 us (6.1).
 template <int M>

@@ -151,12 +151,13 @@ __global__ __launch_bounds__(256) void corr_clear_kernel(uint4 *table, uint64_t 
 // owner named by the last store, a second pass over the records had to find it: 40 + 77 + 23
 // us for 1,174,405 records of 4 metrics; join, gather and adds 63 + 37 + 22 us so.)
 // Claims of one word wait for each other, 11 ns each, so a wave looks at a word before it claims
-// it: in its first pass, and in every pass once it has met a path that another record owns (a
-// look is one more round trip where every record has its own path).  The fewer workgroups, the
-// fewer records are claimed before the first looks can tell.  1,000,000 records of 1 path, of 1,000 paths, of 1,000,000 paths: claiming
-// blindly in 2,048 workgroups 11,336, 251 and 46 us; looking always 203, 36 and 61 us (with
-// 2,048 workgroups 112 us for 1,000 paths); so 222, 36 and 47 us.
-constexpr int kJoinThreads = 256;
+// it: in its first pass, and from the pass on in which a quarter of its records met owned paths or
+// two met the same one (a look is one more round trip, which records of many paths need not
+// take, even where some repeat).  The fewer workgroups, the fewer records are claimed before the
+// first looks can tell.  1,000,000 records of 1 path, of 1,000 paths, of 1,000,000 paths, and
+// of 1,000,000 with 100,000 repeats: claiming blindly in 2,048 workgroups 11,336, 251, 46 and 49 us;
+// looking always, in 512, 203, 36, 61 and 64; so about 280, 37, 46 and 50.
+constexpr int kJoinThreads = 256, kJoinMet = 16;
 __global__ __launch_bounds__(kJoinThreads) void corr_join_kernel(ActivityArgs a, uint64_t *list, int64_t stride,
                                                                  uint32_t *cnt) {
   __shared__ unsigned long long wsum[kJoinThreads / 64];
@@ -165,18 +166,22 @@ __global__ __launch_bounds__(kJoinThreads) void corr_join_kernel(ActivityArgs a,
   __syncthreads();
   unsigned long long unmatched = 0;
   uint64_t *mine = list + (int64_t)blockIdx.x * stride;
-  bool look = true, met = false;  // whether to look at a word before claiming it
+  bool look = true, hot = false;  // whether to look at a word before claiming it
   for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < a.n_rec; r += (int64_t)gridDim.x * blockDim.x) {
     const int64_t f = reg_find(a, a.rec_corr[r]);
     if (f < 0) ++unmatched;
-    bool later = false;  // another record owns the path
+    uint32_t owner = 0;  // another record that owns the path
     if (f >= 0) {
-      later = look && a.ref[f] != 0u;
-      if (!later) later = atomicCAS(&a.ref[f], 0u, (uint32_t)(r + 1)) != 0u;
-      if (later) mine[atomicAdd(&n, 1u)] = ((uint64_t)f << 32) | (uint64_t)r;
+      if (look) owner = a.ref[f];
+      if (!owner) owner = atomicCAS(&a.ref[f], 0u, (uint32_t)(r + 1));
+      if (owner) mine[atomicAdd(&n, 1u)] = ((uint64_t)f << 32) | (uint64_t)r;
     }
-    met |= later;
-    look = __any(met);
+    const uint64_t met = __ballot(owner != 0u);
+    if (met) {
+      const uint32_t first = __shfl(owner, __builtin_ctzll(met), 64), last = __shfl(owner, 63 - __builtin_clzll(met), 64);
+      hot |= __popcll(met) >= kJoinMet || __popcll(__ballot(owner == first)) > 1 || __popcll(__ballot(owner == last)) > 1;
+    }
+    look = hot;
   }
   for (int o = 32; o > 0; o >>= 1) unmatched += __shfl_xor(unmatched, o, 64);
   if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = unmatched;
